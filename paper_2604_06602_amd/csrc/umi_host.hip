@@ -225,6 +225,15 @@ struct PackView {
 // two, four and eight lanes share one.
 constexpr int kSmallBatchTiles[] = {1024, 512, 256, 128, 64};
 
+// Whether a curve's tiles take sorted cores: wide index windows with the
+// upper-RMS scale, one lane per window, and asymmetries whose two sides' cut-offs
+// are not far apart.
+bool takes_core(const CurveDesc& d, int32_t scale)
+{
+    return d.W >= kCoreMinW && d.tile > kSplitMaxTile && scale == UMI_SCALE_UPPER_RMS &&
+           !(d.window_days > 0.0) && d.alpha >= 0.25f && d.alpha <= 16.0f;
+}
+
 umi_status pack_into(const int64_t* offsets, const int64_t* lengths, int64_t n, const int32_t* W,
                      float alpha, float c, const umi_options& o, const umi_launch& opt, int n_cu,
                      int64_t max_tiles, PackView* out)
@@ -296,19 +305,25 @@ umi_status pack_into(const int64_t* offsets, const int64_t* lengths, int64_t n, 
         d.c = o.c ? o.c[b] : c;
         d.window_days = o.window_days ? o.window_days[b] : 0.0;
         d.chunk_base = (int32_t)out->nchunks;
-        d.reserved = 0;
+        d.core = takes_core(d, o.scale) ? 1 : 0;
         out->curve_tiles[i] = nt;
         out->ntiles += nt;
         out->nchunks += nch;
     }
     // the estimate-kernel paths this batch needs
     out->feat = o.scale == UMI_SCALE_MAD ? kFeatExtra : 0;
+    int cap = 0;  // the batch's largest sorted core
     for (int64_t i = 0; i < nord; ++i) {
         const CurveDesc& d = out->curves[i];
         if (d.W <= kSmallW) out->feat |= kFeatSmall;
         if (d.tile <= kSplitMaxTile) out->feat |= kFeatSplit;
         if (d.window_days > 0.0) out->feat |= kFeatExtra;
+        if (d.core) {
+            out->feat |= kFeatCore;
+            cap = std::max(cap, core_cap(d.W));
+        }
     }
+    out->feat |= cap << kFeatBits;
     out->gpc = kDefaultGroupsPerCU;
     if (nord > 0) {
         int t_unused;
@@ -798,6 +813,13 @@ CopyPool& copy_pool(int which = 0)
 // ---------------------------------------------------------------------------
 // replayable plans
 
+// Estimate kernels a plan's graphs launch.  Sorted cores take LDS in
+// proportion to the widest window, and LDS is what limits the workgroups per
+// CU, so a run takes the smallest that covers it: no cores (four workgroups
+// per CU), cores of windows up to kPlanMidW (three), of any window up to max_W.
+constexpr int kPlanKernels = 3;
+constexpr int kPlanMidW = 383;
+
 struct umi_plan {
     int device = 0;
     hipStream_t stream = nullptr;
@@ -812,17 +834,17 @@ struct umi_plan {
     float* median = nullptr;
     int main_grid = 0;
     umi::DeviceBuffers buf;
-    // Two captured graphs per slot: [0] for batches of at most
-    // kPrepSmallChunks pre-pass chunks (the chunked pre-pass over that many
-    // workgroups), [1] for any batch (the curve walker over max_curves
-    // workgroups).  Either pre-pass reads the slot's pinned block and copies
-    // it to the slot's device block for the estimate kernel.
+    // Captured graphs per slot and estimate kernel (kPlan*): [0] for batches
+    // of at most kPrepSmallChunks pre-pass chunks (the chunked pre-pass over
+    // that many workgroups), [1] for any batch (the curve walker over
+    // max_curves workgroups).  Either pre-pass reads the slot's pinned block
+    // and copies it to the slot's device block for the estimate kernel.
     struct Slot {
         uint8_t* host = nullptr;    // pinned header + curve table
         uint8_t* host_dev = nullptr;  // its device address
         uint8_t* dev = nullptr;     // its device copy
-        hipGraph_t graph[2] = {nullptr, nullptr};
-        hipGraphExec_t exec[2] = {nullptr, nullptr};
+        hipGraph_t graph[kPlanKernels][2] = {};
+        hipGraphExec_t exec[kPlanKernels][2] = {};
         hipEvent_t done = nullptr;  // recorded after the slot's last replay
         bool pending = false;
     } slot[2];
@@ -835,9 +857,11 @@ namespace {
 void plan_free(umi_plan* p)
 {
     for (auto& s : p->slot) {
-        for (int k = 0; k < 2; ++k) {
-            if (s.exec[k]) (void)hipGraphExecDestroy(s.exec[k]);
-            if (s.graph[k]) (void)hipGraphDestroy(s.graph[k]);
+        for (int v = 0; v < kPlanKernels; ++v) {
+            for (int k = 0; k < 2; ++k) {
+                if (s.exec[v][k]) (void)hipGraphExecDestroy(s.exec[v][k]);
+                if (s.graph[v][k]) (void)hipGraphDestroy(s.graph[v][k]);
+            }
         }
         if (s.done) (void)hipEventDestroy(s.done);
         if (s.host) (void)hipHostFree(s.host);
@@ -863,10 +887,30 @@ umi::PrepLaunch plan_kind_prep(const umi_plan* p, int kind)
                      : umi::PrepLaunch{true, (int)p->max_curves};
 }
 
-// Capture slot `si`'s graph of `kind`: the pre-pass (which reads the staged
-// block from pinned memory and copies it to the device) and the persistent
-// estimate kernel.  Nothing runs during capture.
-hipError_t plan_capture(umi_plan* p, int si, int kind)
+// The estimate kernel for a batch that needs `feat`, and kernel v's own bits.
+int plan_kernel(int feat)
+{
+    if (!(feat & umi::kFeatCore)) return 0;
+    return (feat >> umi::kFeatBits) <= umi::core_cap(kPlanMidW) ? 1 : 2;
+}
+
+int plan_kernel_feat(const umi_plan* p, int v)
+{
+    if (v == 0) return umi::kFeatSmall | umi::kFeatSplit | umi::kFeatExtra;
+    const int W = v == 1 ? std::min<int>(kPlanMidW, p->max_W) : p->max_W;
+    return umi::kFeatAll | umi::core_cap(W) << umi::kFeatBits;
+}
+
+// Kernels the plan's windows can need.
+int plan_kernels(const umi_plan* p)
+{
+    return p->max_W < umi::kCoreMinW ? 1 : (p->max_W <= kPlanMidW ? 2 : kPlanKernels);
+}
+
+// Capture slot `si`'s graph of `kind` with estimate kernel `v`: the pre-pass
+// (which reads the staged block from pinned memory and copies it to the
+// device) and the persistent estimate kernel.  Nothing runs during capture.
+hipError_t plan_capture(umi_plan* p, int si, int kind, int v)
 {
     umi_plan::Slot& s = p->slot[si];
     hipError_t e = hipStreamBeginCapture(p->stream, hipStreamCaptureModeThreadLocal);
@@ -874,16 +918,16 @@ hipError_t plan_capture(umi_plan* p, int si, int kind)
     const hipError_t ce = umi::enqueue_kernels(
         p->flux, p->time, p->trend, p->median, s.dev, s.host_dev, p->buf, UMI_MODE_PERSISTENT,
         nullptr, nullptr, (int)plan_kind_curves(p, kind), plan_kind_prep(p, kind), p->main_grid,
-        umi::kFeatAll, nullptr, nullptr, nullptr, p->stream);
+        plan_kernel_feat(p, v), nullptr, nullptr, nullptr, p->stream);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(p->stream, &g);
     if (ce != hipSuccess || e != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
         return ce != hipSuccess ? ce : e;
     }
-    s.graph[kind] = g;
-    if ((e = hipGraphInstantiate(&s.exec[kind], g, nullptr, nullptr, 0)) != hipSuccess) {
-        s.exec[kind] = nullptr;
+    s.graph[v][kind] = g;
+    if ((e = hipGraphInstantiate(&s.exec[v][kind], g, nullptr, nullptr, 0)) != hipSuccess) {
+        s.exec[v][kind] = nullptr;
         return e;
     }
     return hipSuccess;
@@ -1185,9 +1229,11 @@ umi_status umi_plan_create(umi_plan** out, int64_t capacity, int64_t max_curves,
     int t_unused, gpc;
     umi::tuned(max_W, -1, &t_unused, &gpc);
     p->main_grid = gpc * umi::cu_count(p->device);
-    // every slot's graphs of both kinds, now rather than on a serving step
+    // every slot's graphs, now rather than on a serving step
     for (int si = 0; si < 2 && e == hipSuccess; ++si)
-        for (int kind = 0; kind < 2 && e == hipSuccess; ++kind) e = plan_capture(p, si, kind);
+        for (int kind = 0; kind < 2 && e == hipSuccess; ++kind)
+            for (int v = 0; v < plan_kernels(p) && e == hipSuccess; ++v)
+                e = plan_capture(p, si, kind, v);
     if (e != hipSuccess) {
         plan_free(p);
         delete p;
@@ -1242,9 +1288,10 @@ umi_status umi_plan_run_ex(umi_plan* p, const int64_t* offsets, const int64_t* l
                      iters, o, p->time);
     // small batches (at most kPrepSmallChunks chunks) replay kind 0
     const int kind = pk.nchunks <= umi::kPrepSmallChunks ? 0 : 1;
-    if (!s.exec[kind] && (e = plan_capture(p, p->next, kind)) != hipSuccess)
+    const int v = n_curves > 0 ? plan_kernel(pk.feat) : 0;
+    if (!s.exec[v][kind] && (e = plan_capture(p, p->next, kind, v)) != hipSuccess)
         return umi::fail_hip(e, "graph capture");
-    if ((e = hipGraphLaunch(s.exec[kind], p->stream)) != hipSuccess)
+    if ((e = hipGraphLaunch(s.exec[v][kind], p->stream)) != hipSuccess)
         return umi::fail_hip(e, "hipGraphLaunch");
     if ((e = hipEventRecord(s.done, p->stream)) != hipSuccess)
         return umi::fail_hip(e, "hipEventRecord");

@@ -19,7 +19,33 @@ constexpr int kSmallW = 31;                  // full windows this small take reg
 constexpr int kFeatSmall = 1;                // small-window networks (W <= kSmallW)
 constexpr int kFeatSplit = 2;                // split tiles (tile <= kSplitMaxTile)
 constexpr int kFeatExtra = 4;                // MAD ablation, time windows
-constexpr int kFeatAll = kFeatSmall | kFeatSplit | kFeatExtra;
+constexpr int kFeatCore = 8;                 // sorted cores (wide windows)
+constexpr int kFeatAll = kFeatSmall | kFeatSplit | kFeatExtra | kFeatCore;
+constexpr int kFeatBits = 8;                 // the batch's largest core stands above these
+
+// Sorted cores: 64 consecutive windows share all but at most 63 samples of
+// each; the core is that shared run, a whole number of blocks of kCoreBlock.
+constexpr int kCoreMinW = 193;               // narrower windows sum their samples directly
+constexpr int kCoreBlock = 8;
+constexpr int kCoreWaves = 6;                // waves per SIMD the core instances are built for
+constexpr int kCoreEdge = 64 + 72;           // edge samples a wave stages (left, right)
+__host__ __device__ constexpr int core_cap(int W)
+{
+    return W > 63 ? (W - 63) & ~(kCoreBlock - 1) : 0;
+}
+// the power of two above the core's block count (the search's range)
+__host__ __device__ constexpr int core_search(int cap)
+{
+    int n = 1;
+    while (n <= cap / kCoreBlock) n <<= 1;
+    return n;
+}
+// floats of LDS one wave's core takes: values, first value of each block,
+// five moments per block edge, edge samples
+__host__ __device__ constexpr int core_floats_for(int cap)
+{
+    return (cap + core_search(cap) + 5 * (cap / kCoreBlock + 1) + kCoreEdge + 3) & ~3;
+}
 
 // Lanes that share one window for a tile of `tile` output positions: 1 above
 // kSplitMaxTile (each lane takes up to three windows), else the largest of 2,
@@ -66,7 +92,7 @@ struct CurveDesc {
     float c;            // bisquare tuning constant of this curve
     double window_days; // > 0: time window of this length (W still bounds it)
     int32_t chunk_base; // index of this curve's first pre-pass chunk
-    int32_t reserved;
+    int32_t core;       // its tiles sum windows by sorted cores
 };
 static_assert(sizeof(CurveDesc) == 48, "CurveDesc layout");
 

@@ -39,6 +39,8 @@
 //                       counter) or one workgroup per tile.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include <stdint.h>
 
 #include "umi.h"
@@ -785,7 +787,6 @@ __device__ __forceinline__ float key_value(uint32_t k)
 struct MainSmem {
     uint64_t sortbuf[kStageMax];          // (key << 32 | compacted index)
     float xv[kStageMax];                  // compacted valid samples
-    uint16_t seq[2][kStageMax];           // wavelet-matrix level sequences
     uint64_t bits[kStageLog2][kWords];    // wavelet-matrix level bit vectors
     uint32_t pre[kStageLog2][kWords];     // ones before each word
     uint32_t zeros[kStageLog2];           // zeros per level
@@ -1156,6 +1157,7 @@ __device__ __forceinline__ bool window_range(const MainSmem& sm, const CurveDesc
     }
     if (x < 0 || cnt < m_min) return false;
     int a = max(p - h, x);
+    if (kFeat & kFeatCore) a = max(a, s0);  // positions before the tile are asked for too
     // the window ends before the next segment's first sample: the first
     // start bit after p within reach of p + h
     const uint32_t from = (uint32_t)(p + 1 - s0);
@@ -1548,20 +1550,385 @@ __device__ __forceinline__ void tile_windows_split(const MainSmem& sm, int level
     }
 }
 
+// ---------------------------------------------------------------------------
+// Wide windows by sorted cores.
+//
+// The 64 windows of an aligned group of consecutive positions share all but
+// at most 63 samples of each.  One wave takes a group, a window per lane: it
+// compacts the shared samples (the core) in value order out of the sorted
+// tile, in blocks of kCoreBlock, and keeps at every block edge the first five
+// power sums of the core's deviations from a value near its centre, counted
+// from the centre outwards.  Eq. 3's weight is a polynomial of degree four in
+// the sample on either side of the location and zero beyond the cut-offs, so
+// the sums of Eq. 4 over the blocks strictly between two of the three
+// break points (lower cut-off, location, upper cut-off) follow from two block
+// edges' power sums, shifted to the location; the block that holds a break
+// point and the window's own samples outside the core (its edge samples) are
+// summed one by one as in the direct sweep.  Eq. 1's sum follows likewise.
+// An iteration of a 361-sample window takes some 65 + 24 samples instead of
+// 361.
+//
+// The polynomial is exact; what it costs is rounding where the location lies
+// far from the centre in units of the cut-off, so a lane sums its window (or
+// the part below the location) directly when it does, and when the scales
+// leave the range in which the powers neither overflow nor vanish.  A lane's
+// result depends only on the group and the window, never on the tile.
+
+struct CoreLds {
+    float* cv;    // core samples in value order
+    float* fst;   // first value of each block, then NaN up to the search range
+    float* g;     // five power sums per block edge
+    float* edge;  // samples before the core (64 slots), samples after it (72)
+};
+
+__device__ __forceinline__ CoreLds core_lds(float* base, int cap)
+{
+    CoreLds c;
+    c.cv = base;
+    c.fst = base + cap;
+    c.g = c.fst + core_search(cap);
+    c.edge = c.g + 5 * (cap / kCoreBlock + 1);
+    return c;
+}
+
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// v + (v of the lane a DPP control selects, 0 where it selects none)
+template <int kCtrl, int kRows>
+__device__ __forceinline__ float dpp_add(float v)
+{
+    return v + __int_as_float(
+                   __builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, kRows, 0xF, false));
+}
+
+// Inclusive sum over each half of the wave (lanes 0-31, lanes 32-63).
+__device__ __forceinline__ float half_scan(float v)
+{
+    v = dpp_add<0x111, 0xF>(v);  // row_shr:1
+    v = dpp_add<0x112, 0xF>(v);  // row_shr:2
+    v = dpp_add<0x114, 0xF>(v);  // row_shr:4
+    v = dpp_add<0x118, 0xF>(v);  // row_shr:8
+    return dpp_add<0x142, 0xA>(v);  // row_bcast:15 into the odd rows
+}
+
+__device__ __forceinline__ float lane_value(float v, int lane)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+
+// The wave's core: nc samples (a multiple of kCoreBlock) at compacted
+// positions [cca, cca + nc).  False when the deviations' scale is unusable.
+__device__ __forceinline__ bool core_build(const MainSmem& sm, const CoreLds& cw, int nv, int npad,
+                                           uint32_t cca, int nc, float alpha, float& centre,
+                                           float& unit)
+{
+    const int lane = __lane_id();
+    const int nb = nc / kCoreBlock;
+    int base = 0;
+    for (int j0 = 0; j0 < nv && base < nc; j0 += 256) {
+        uint64_t e[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            e[u] = j0 + 64 * u < npad ? sm.sortbuf[j0 + 64 * u + lane] : ~0ull;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool in = (uint32_t)e[u] - cca < (uint32_t)nc;
+            const uint64_t m = __ballot(in);
+            const int at = base + (int)__builtin_amdgcn_mbcnt_hi(
+                                      (uint32_t)(m >> 32),
+                                      __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            if (in) cw.cv[at] = key_value((uint32_t)(e[u] >> 32));
+            base += (int)__popcll(m);
+        }
+    }
+    // the samples on either side of the core
+    {
+        const int l = (int)cca - 64 + lane, r = (int)cca + nc + lane;
+        cw.edge[lane] = l >= 0 ? sm.xv[l] : 0.0f;
+        cw.edge[64 + lane] = r < nv ? sm.xv[r] : 0.0f;
+        if (lane < 8) cw.edge[128 + lane] = r + 64 < nv ? sm.xv[r + 64] : 0.0f;
+    }
+    wave_lds_sync();
+    for (int b = lane; b < core_search(nc); b += 64)
+        cw.fst[b] = b < nb ? cw.cv[kCoreBlock * b] : __builtin_nanf("");
+    // a centre about half-way from the median to where the iterations end
+    // (above it for alpha > 1), and a power of two near the core's spread
+    const float qf = alpha > 1.0f ? __builtin_fminf(0.5f + 0.1f * __builtin_log2f(alpha), 0.8f) : 0.5f;
+    const int cq = (int)(qf * (float)nc);
+    centre = cw.cv[cq];
+    const float spread = cw.cv[(27 * nc) >> 5] - cw.cv[(5 * nc) >> 5];
+    const int ex = __builtin_amdgcn_frexp_expf(spread);
+    if (!(spread > 0.0f) || ex < -60 || ex > 60) return false;
+    unit = __builtin_amdgcn_ldexpf(1.0f, -ex);
+    const int bc = cq / kCoreBlock;
+    // power sums from the centre's block edge outwards: upwards in the lower
+    // half of the wave, downwards (with a minus sign) in the upper half
+    const bool up = lane < 32;
+    float carry[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+    for (int r0 = 0; r0 < max(nb - bc, bc); r0 += 32) {
+        const int i = r0 + (lane & 31);
+        const int b = up ? bc + i : bc - 1 - i;
+        const bool act = up ? b < nb : b >= 0;
+        float s[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+        if (act) {
+            const float* v = cw.cv + kCoreBlock * b;
+#pragma unroll
+            for (int q = 0; q < kCoreBlock; ++q) {
+                const float d = (v[q] - centre) * unit;
+                const float d2 = d * d;
+                const float d4 = d2 * d2;
+                s[0] += d;
+                s[1] += d2;
+                s[2] = __builtin_fmaf(d2, d, s[2]);
+                s[3] += d4;
+                s[4] = __builtin_fmaf(d4, d, s[4]);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            const float t = half_scan(s[k]) + carry[k];
+            const float lo = lane_value(t, 31), hi = lane_value(t, 63);
+            carry[k] = up ? lo : hi;
+            if (act) cw.g[5 * (up ? b + 1 : b) + k] = up ? t : -t;
+        }
+    }
+    if (lane < 5) cw.g[5 * bc + lane] = 0.0f;
+    wave_lds_sync();
+    return true;
+}
+
+// The last block whose first value is <= each knot (0 where none is).
+template <int K>
+__device__ __forceinline__ void core_find(const float* __restrict__ fst, int top,
+                                          const float (&knot)[K], int (&b)[K])
+{
+#pragma unroll
+    for (int i = 0; i < K; ++i) b[i] = 0;
+    for (int s = top; s > 0; s >>= 1) {
+#pragma unroll
+        for (int i = 0; i < K; ++i) b[i] += fst[b[i] + s - 1] <= knot[i] ? s : 0;
+    }
+#pragma unroll
+    for (int i = 0; i < K; ++i) b[i] = max(b[i] - 1, 0);
+}
+
+// Sums of w and w z over blocks [e0, e1) with z = (d - delta) kappa, |z| < 1:
+// the blocks' power sums about the location, then (1 - z^2)^2 term by term.
+__device__ __forceinline__ void core_poly(const float* __restrict__ g, int e0, int e1, float delta,
+                                          float kappa, float& sw, float& swz)
+{
+    float d[6];
+    d[0] = (float)(kCoreBlock * (e1 - e0));
+#pragma unroll
+    for (int k = 0; k < 5; ++k) d[k + 1] = g[5 * e1 + k] - g[5 * e0 + k];
+#pragma unroll
+    for (int i = 1; i <= 5; ++i) {
+#pragma unroll
+        for (int k = 5; k >= i; --k) d[k] = __builtin_fmaf(-delta, d[k - 1], d[k]);
+    }
+    const float k2 = kappa * kappa;
+    sw = __builtin_fmaf(k2, __builtin_fmaf(k2, d[4], -2.0f * d[2]), d[0]);
+    swz = kappa * __builtin_fmaf(k2, __builtin_fmaf(k2, d[5], -2.0f * d[3]), d[1]);
+}
+
+// f over the samples of block b, in value order
+template <class F>
+__device__ __forceinline__ void core_block(const float* __restrict__ cv, int b, F&& f)
+{
+    float v[kCoreBlock];
+#pragma unroll
+    for (int q = 0; q < kCoreBlock; ++q) v[q] = cv[kCoreBlock * b + q];
+#pragma unroll
+    for (int q = 0; q < kCoreBlock; ++q) f(v[q]);
+}
+
+// Furthest a location may lie from the core's centre, in units of the
+// cut-off of the side summed by power sums.
+constexpr float kCoreReach = 0.5f;
+
+template <int kFeat>
+__device__ __forceinline__ void core_group(const MainSmem& sm, const CoreLds& cw, int levels,
+                                           int nv, int npad, const CurveDesc& cd, int h, int s0,
+                                           int N, int t0, int t1, int g0,
+                                           const int32_t* __restrict__ segid, float alpha, float c,
+                                           int iters, int scale, const double* __restrict__ time,
+                                           float* __restrict__ trend, float* __restrict__ median,
+                                           float* __restrict__ detrended)
+{
+    const int p = g0 + __lane_id();
+    const bool mine = p >= t0 && p < t1;
+    uint32_t ca = 0, n = 0;
+    // the ranges of positions outside the tile count too (cut at the staged
+    // span, which the core never reaches): the core is the group's
+    const bool alive = p < cd.len && window_range<kFeat>(sm, cd, segid, time, h, s0, N,
+                                                         max(1, cd.W / 3), p, ca, n);
+    const bool live = alive && mine;
+    const uint64_t alive_m = __ballot(alive);
+    const uint64_t live_m = __ballot(live);
+    float m = 0.0f, mu = 0.0f;
+    if (live_m != 0) {
+        uint32_t nplus = 0;
+        float sc = 0.0f;
+        if (live) window_phase1(sm, levels, nv, UMI_SCALE_UPPER_RMS, ca, n, m, sc, nplus);
+        // the core: from the last window's start to the first window's end
+        const int lane_lo = (int)__builtin_ctzll(alive_m), lane_hi = 63 - (int)__builtin_clzll(alive_m);
+        const int cca = __builtin_amdgcn_readlane((int)ca, lane_hi);
+        const int ccb = __builtin_amdgcn_readlane((int)(ca + n), lane_lo);
+        const int nc = min(ccb - cca, core_cap(cd.W)) & ~(kCoreBlock - 1);
+        float centre = 0.0f, unit = 1.0f;
+        const bool core = nc >= 8 * kCoreBlock &&
+                          core_build(sm, cw, nv, npad, (uint32_t)cca, nc, alpha, centre, unit);
+        const int top = core ? core_search(nc) >> 1 : 0;
+        const int nb = nc / kCoreBlock;
+        // edge samples: nl before the core, then those after it
+        const int nl = live ? cca - (int)ca : 0;
+        const float* const xe = cw.edge + 64 - nl;
+        const int ne = live ? (int)n - nc : 0;
+        const int src = (int)__builtin_ctzll(live_m);
+        const int ne_u = __builtin_amdgcn_readlane(ne, src);
+        const bool even = __all(!live || ne == ne_u);
+
+        // Phase 2 (Eq. 1)
+        float ssq = 0.0f;
+        bool direct = true;
+        if (core) {
+            auto up2 = [&](float x) {
+                const float d = __builtin_fmaxf(x - m, 0.0f);
+                ssq = __builtin_fmaf(d, d, ssq);
+            };
+            if (even) {
+#pragma unroll 8
+                for (int j = 0; j < ne_u; ++j) up2(xe[j]);
+            } else {
+                for (int j = 0; j < ne; ++j) up2(xe[j]);
+            }
+            const float knot[1] = {m};
+            int b[1];
+            core_find<1>(cw.fst, top, knot, b);
+            core_block(cw.cv, b[0], up2);
+            const int e = b[0] + 1;
+            const float d0 = (float)(kCoreBlock * (nb - e));
+            const float d1 = cw.g[5 * nb] - cw.g[5 * e];
+            const float d2 = cw.g[5 * nb + 1] - cw.g[5 * e + 1];
+            const float delta = (m - centre) * unit;
+            const float whole = __builtin_fmaf(delta * delta, d0, d2);
+            const float rest = __builtin_fmaf(-2.0f * delta, d1, whole);
+            const float back = 1.0f / unit;  // a power of two
+            ssq += rest * back * back;
+            direct = !(rest >= 0.125f * whole && whole < 1e30f);
+        }
+        if (live && direct) ssq = upper_ssq(sm.xv, (int)ca, (int)n, m);
+        if (live && nplus > 0) sc = upper_scale(ssq, nplus);
+
+        // Phase 3 (Eqs. 2-4)
+        const float kA = 0.5f * (1.0f + alpha);
+        const float beta = (1.0f - alpha) / (1.0f + alpha);
+        mu = m;
+        float k = 0.0f;
+        bool act = false;
+        if (live && sc > 0.0f && iters > 0) {
+            const float kk = bisquare_k(kA, c, sc);
+            if (isfinite(kk)) {
+                k = kk;
+                act = true;
+            }
+        }
+        const float cs = c * sc;          // upper cut-off
+        const float cl = cs / alpha;      // lower cut-off
+        const float ka = 1.0f / (cs * unit);  // per unit of the power sums
+        const float kb = alpha * ka;
+        const bool scaled = ka > 1e-4f && ka < 1e4f;
+        for (int it = 0; it < iters; ++it) {
+            const float bb = -mu * k;
+            float sw = 0.0f, swv = 0.0f;
+            direct = true;
+            if (core) {
+                auto acc = [&](float x) { bisquare_acc(x, k, bb, beta, sw, swv); };
+                if (even) {
+#pragma unroll 8
+                    for (int j = 0; j < ne_u; ++j) acc(xe[j]);
+                } else {
+                    for (int j = 0; j < ne; ++j) acc(xe[j]);
+                }
+                const float knot[3] = {mu - cl, mu, mu + cs};
+                int b[3];
+                core_find<3>(cw.fst, top, knot, b);
+                core_block(cw.cv, b[0], acc);
+                if (b[1] != b[0]) core_block(cw.cv, b[1], acc);
+                if (b[2] != b[1]) core_block(cw.cv, b[2], acc);
+                const float delta = (mu - centre) * unit;
+                const float far = __builtin_fabsf(delta);
+                const int eb = min(b[0] + 1, b[1]), ea = min(b[1] + 1, b[2]);
+                float pw, pz;
+                core_poly(cw.g, ea, b[2], delta, ka, pw, pz);
+                sw += pw;
+                swv = __builtin_fmaf(kA, pz, swv);
+                if (far * kb <= kCoreReach) {
+                    core_poly(cw.g, eb, b[1], delta, kb, pw, pz);
+                    sw += pw;
+                    swv = __builtin_fmaf(kA / alpha, pz, swv);
+                } else {
+                    for (int q = eb; q < b[1]; ++q) core_block(cw.cv, q, acc);
+                }
+                direct = !(scaled && far * ka <= kCoreReach && sw > 0.03125f * (float)(int)n);
+            }
+            if (act && direct) {
+                sw = 0.0f;
+                swv = 0.0f;
+                const float* x = sm.xv + ca;
+#pragma unroll 8
+                for (int j = 0; j < (int)n; ++j) bisquare_acc(x[j], k, bb, beta, sw, swv);
+            }
+            if (act) {
+                if (sw > 0.0f)
+                    mu = mu_update(mu, swv, sw, k);
+                else
+                    act = false;  // no weight left: keep mu from now on
+            }
+        }
+        if (core) wave_lds_sync();  // the next group's core takes this one's place
+    }
+    if (mine) {
+        const float nanf_ = __builtin_nanf("");
+        trend[cd.off + p] = live ? mu : nanf_;
+        if (median) median[cd.off + p] = live ? m : nanf_;
+        if (detrended)
+            detrended[cd.off + p] =
+                live ? sm.xv[rank1(sm.vbits, sm.vpre, (uint32_t)(p - s0))] / mu : nanf_;
+    }
+}
+
 // kFeat (kFeat* bits) selects the paths an instance carries: the
 // small-window networks, split tiles, and the MAD ablation with time windows.
 // The host launches the smallest instance that covers the batch; fewer paths
 // leave the compiler more registers for the rest, and every instance gives
 // the same results on the batches it serves.
 template <int kFeat>
-__global__ __launch_bounds__(kMainThreads, 8) void umi_main_kernel(
+__global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8) void umi_main_kernel(
     const float* __restrict__ flux, const int32_t* __restrict__ segid,
     const BatchHeader* __restrict__ hdr,
     const CurveDesc* __restrict__ curves, const int2* __restrict__ tiles, int tile_first,
     int tile_count, uint32_t* __restrict__ counter, float* __restrict__ trend,
-    float* __restrict__ median)
+    float* __restrict__ median, int core_floats)
 {
     __shared__ MainSmem sm;
+    // the wavelet build's sequences; in instances with sorted cores the same
+    // space holds the waves' cores once the matrix is built
+    uint16_t* seq;
+    float* cores = nullptr;
+    if constexpr ((kFeat & kFeatCore) != 0) {
+        extern __shared__ __align__(16) float dyn[];
+        seq = reinterpret_cast<uint16_t*>(dyn);
+        cores = dyn;
+    } else {
+        __shared__ uint16_t seq_[2 * kStageMax];  // wavelet-matrix level sequences
+        seq = seq_;
+    }
     const int tid = threadIdx.x;
     const int lane = __lane_id();
     const int wave = tid >> 6;
@@ -1649,7 +2016,7 @@ __global__ __launch_bounds__(kMainThreads, 8) void umi_main_kernel(
 
         if (simple) {
             // every staged sample is valid: values and keys in index order
-            uint32_t* keys = reinterpret_cast<uint32_t*>(sm.seq);
+            uint32_t* keys = reinterpret_cast<uint32_t*>(seq);
             for (int i = tid; i < N; i += kMainThreads) {
                 const float x = f[i];
                 sm.xv[i] = x;
@@ -1716,15 +2083,15 @@ __global__ __launch_bounds__(kMainThreads, 8) void umi_main_kernel(
         if (!scan_tile) {
         for (int r = tid; r < npad; r += kMainThreads) {
             if (r < nv)
-                sm.seq[0][(uint32_t)(sm.sortbuf[r] & 0xffffffffull)] = (uint16_t)r;
+                seq[(uint32_t)(sm.sortbuf[r] & 0xffffffffull)] = (uint16_t)r;
             else
-                sm.seq[0][r] = (uint16_t)(npad - 1);
+                seq[r] = (uint16_t)(npad - 1);
         }
         __syncthreads();
         const int nwl = (npad >> 6) + 1;
         for (int l = 0; l < levels; ++l) {
-            const uint16_t* cur = sm.seq[l & 1];
-            uint16_t* nxt = sm.seq[(l + 1) & 1];
+            const uint16_t* cur = seq + (l & 1) * kStageMax;
+            uint16_t* nxt = seq + ((l + 1) & 1) * kStageMax;
             const int bit = levels - 1 - l;
             for (int i0 = wave * 64; i0 < nwl * 64; i0 += kMainThreads) {
                 const int i = i0 + lane;
@@ -1768,6 +2135,14 @@ __global__ __launch_bounds__(kMainThreads, 8) void umi_main_kernel(
             __syncthreads();
             continue;
         }
+        if ((kFeat & kFeatCore) && cd.core) {
+            const CoreLds cw = core_lds(cores + wave * core_floats, core_cap(cd.W));
+            for (int g0 = (t0 & ~63) + wave * 64; g0 < t1; g0 += kMainThreads)
+                core_group<kFeat>(sm, cw, levels, nv, npad, cd, h, s0, N, t0, t1, g0, segid, alpha,
+                                  c, iters, scale, time, trend, median, detrended);
+            __syncthreads();
+            continue;
+        }
         const int R = (t1 - t0 + kMainThreads - 1) / kMainThreads;  // tile <= kMaxTile -> R <= 3
         // Simple tiles: Phase 1 of this lane's windows from the networks, run
         // here where few registers are live (every window is [p-h, p+h], all
@@ -1775,7 +2150,7 @@ __global__ __launch_bounds__(kMainThreads, 8) void umi_main_kernel(
         float pm[3] = {0.0f, 0.0f, 0.0f};
         uint32_t pn[3] = {0u, 0u, 0u};
         if (simple) {
-            const uint32_t* keys = reinterpret_cast<const uint32_t*>(sm.seq);
+            const uint32_t* keys = reinterpret_cast<const uint32_t*>(seq);
             const int p0 = t0 + tid * R;
             if (p0 < t1) {
                 const int b = p0 - h - s0;
@@ -1885,16 +2260,32 @@ hipError_t launch_main(const float* flux, const int32_t* segid, const BatchHeade
                        int feat, hipStream_t stream)
 {
     if (grid <= 0) return hipSuccess;
-#define UMI_LAUNCH_MAIN(F)                                                                      \
-    hipLaunchKernelGGL(umi_main_kernel<F>, dim3(grid), dim3(kMainThreads), 0, stream, flux, segid, \
-                       hdr, curves, tiles, tile_first, tile_count, counter, trend, median)
-    // the instances built: none, small windows, split tiles, everything
+    // instances with sorted cores size their dynamic LDS for the batch's
+    // largest core; it also holds the wavelet build's sequences
+    const int core_floats = core_floats_for(feat >> kFeatBits);
+    feat &= (1 << kFeatBits) - 1;
+    const size_t dyn = (feat & kFeatCore)
+                           ? std::max((size_t)(kMainThreads / 64) * core_floats * sizeof(float),
+                                      (size_t)2 * kStageMax * sizeof(uint16_t))
+                           : 0;
+#define UMI_LAUNCH_MAIN(F)                                                                       \
+    hipLaunchKernelGGL(umi_main_kernel<F>, dim3(grid), dim3(kMainThreads), dyn, stream, flux, segid, \
+                       hdr, curves, tiles, tile_first, tile_count, counter, trend, median,       \
+                       core_floats)
+    // the instances built: none, small windows, split tiles, everything but
+    // cores; cores, cores and small windows, everything
     if (feat == 0)
         UMI_LAUNCH_MAIN(0);
     else if (feat == kFeatSmall)
         UMI_LAUNCH_MAIN(kFeatSmall);
     else if (feat == kFeatSplit)
         UMI_LAUNCH_MAIN(kFeatSplit);
+    else if (!(feat & kFeatCore))
+        UMI_LAUNCH_MAIN(kFeatSmall | kFeatSplit | kFeatExtra);
+    else if (feat == kFeatCore)
+        UMI_LAUNCH_MAIN(kFeatCore);
+    else if (feat == (kFeatCore | kFeatSmall))
+        UMI_LAUNCH_MAIN(kFeatCore | kFeatSmall);
     else
         UMI_LAUNCH_MAIN(kFeatAll);
 #undef UMI_LAUNCH_MAIN
