@@ -25,26 +25,49 @@ constexpr int kFeatBits = 8;                 // the batch's largest core stands 
 
 // Sorted cores: 64 consecutive windows share all but at most 63 samples of
 // each; the core is that shared run, a whole number of blocks of kCoreBlock.
-constexpr int kCoreMinW = 193;               // narrower windows sum their samples directly
+// Narrower windows sum their samples directly: the edge samples and the blocks
+// at the break points come to about 90 whatever W (1,000 curves of 18,000:
+// W = 129 1.85 ms directly, 1.95 by cores; W = 145 2.00 and 1.83).
+constexpr int kCoreMinW = 137;
 constexpr int kCoreBlock = 8;
-constexpr int kCoreWaves = 6;                // waves per SIMD the core instances are built for
-constexpr int kCoreEdge = 64 + 72;           // edge samples a wave stages (left, right)
+// Waves per SIMD the core instances are built for: LDS (47 KB at W = 361)
+// allows three workgroups per CU, and 80 registers spill little; at 4 waves
+// (128 registers) two workgroups fit and W = 361 took 3.3 ms against 2.5.
+constexpr int kCoreWaves = 6;
+constexpr int kCoreEdge = 64 + kCoreBlock + 64;  // samples a wave sums one by one
 __host__ __device__ constexpr int core_cap(int W)
 {
-    return W > 63 ? (W - 63) & ~(kCoreBlock - 1) : 0;
+    return W > 63 ? W - 63 : 0;
 }
-// the power of two above the core's block count (the search's range)
-__host__ __device__ constexpr int core_search(int cap)
+// the search tree over nb blocks' first values: levels of every 4^k-th value,
+// each a whole number of fours
+__host__ __device__ constexpr int core_levels(int nb)
 {
     int n = 1;
-    while (n <= cap / kCoreBlock) n <<= 1;
+    while ((1 << (2 * n)) < nb) ++n;
     return n;
 }
-// floats of LDS one wave's core takes: values, first value of each block,
-// five moments per block edge, edge samples
+__host__ __device__ constexpr int core_level_len(int nb, int stride)
+{
+    return ((nb + stride - 1) / stride + 3) & ~3;
+}
+__host__ __device__ constexpr int core_tree(int nb)
+{
+    int len = 0;
+    for (int st = 1 << (2 * (core_levels(nb) - 1)); st > 0; st >>= 2) len += core_level_len(nb, st);
+    return len;
+}
+// floats of LDS one wave's core takes: values, edge samples, and the larger
+// of Phase 1's masks and the block table (search tree, five power sums per
+// block edge)
+constexpr int kCoreRanks = 64;               // core ranks around the centre that Phase 1 masks
+constexpr int kCoreMaskWords = 4;            // words of an edge-sample mask (64 + 64 bits)
 __host__ __device__ constexpr int core_floats_for(int cap)
 {
-    return (cap + core_search(cap) + 5 * (cap / kCoreBlock + 1) + kCoreEdge + 3) & ~3;
+    const int nb = cap / kCoreBlock;
+    const int table = core_tree(nb) + 5 * (nb + 1);
+    const int masks = kCoreRanks * kCoreMaskWords;
+    return ((cap + 3) & ~3) + kCoreEdge + (((table > masks ? table : masks) + 3) & ~3);
 }
 
 // Lanes that share one window for a tile of `tile` output positions: 1 above

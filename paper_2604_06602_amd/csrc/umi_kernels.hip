@@ -787,15 +787,26 @@ __device__ __forceinline__ float key_value(uint32_t k)
 struct MainSmem {
     uint64_t sortbuf[kStageMax];          // (key << 32 | compacted index)
     float xv[kStageMax];                  // compacted valid samples
-    uint64_t bits[kStageLog2][kWords];    // wavelet-matrix level bit vectors
-    uint32_t pre[kStageLog2][kWords];     // ones before each word
-    uint32_t zeros[kStageLog2];           // zeros per level
     uint64_t vbits[kWords];               // staged-sample validity
     uint32_t vpre[kWords];
     uint64_t sbits[kWords];               // staged samples that start a segment
     int tile;
     int nvalid;
+    uint32_t kmin, kmax;                  // smallest and largest staged key
+    uint32_t wsum[kMainThreads / 64];     // per wave: bucket counts of its threads
 };
+
+// The wavelet matrix over a tile's sorted ranks.  The same LDS first holds
+// the tile sort's bucket counters, and in instances with sorted cores the
+// waves' cores (tiles take one or the other).
+struct Wavelet {
+    uint16_t seq[2][kStageMax];           // level sequences
+    uint64_t bits[kStageLog2][kWords];    // level bit vectors
+    uint32_t pre[kStageLog2][kWords];     // ones before each word
+    uint32_t zeros[kStageLog2];           // zeros per level
+};
+constexpr int kBuckets = kStageMax;       // counters of the tile sort
+static_assert(sizeof(Wavelet) >= kBuckets * sizeof(uint32_t), "counters fit");
 
 __device__ __forceinline__ uint32_t rank1(const uint64_t* bits, const uint32_t* pre, uint32_t i)
 {
@@ -818,12 +829,12 @@ __device__ __forceinline__ void word_prefix(const uint64_t* bits, uint32_t* pre,
 }
 
 // k-th smallest (0-based) value of the level-0 sequence within [s, e).
-__device__ __forceinline__ uint32_t wavelet_kth(const MainSmem& sm, int levels, uint32_t s, uint32_t e, uint32_t k)
+__device__ __forceinline__ uint32_t wavelet_kth(const Wavelet& wv, int levels, uint32_t s, uint32_t e, uint32_t k)
 {
     uint32_t r = 0;
     for (int l = 0; l < levels; ++l) {
-        const uint32_t os = rank1(sm.bits[l], sm.pre[l], s);
-        const uint32_t oe = rank1(sm.bits[l], sm.pre[l], e);
+        const uint32_t os = rank1(wv.bits[l], wv.pre[l], s);
+        const uint32_t oe = rank1(wv.bits[l], wv.pre[l], e);
         const uint32_t zs = s - os, ze = e - oe;
         const uint32_t nz = ze - zs;
         if (k < nz) {
@@ -831,8 +842,8 @@ __device__ __forceinline__ uint32_t wavelet_kth(const MainSmem& sm, int levels, 
             e = ze;
         } else {
             k -= nz;
-            s = sm.zeros[l] + os;
-            e = sm.zeros[l] + oe;
+            s = wv.zeros[l] + os;
+            e = wv.zeros[l] + oe;
             r |= 1u << (levels - 1 - l);
         }
     }
@@ -840,18 +851,18 @@ __device__ __forceinline__ uint32_t wavelet_kth(const MainSmem& sm, int levels, 
 }
 
 // Number of level-0 values smaller than v within [s, e).
-__device__ __forceinline__ uint32_t wavelet_count_less(const MainSmem& sm, int levels, uint32_t s,
+__device__ __forceinline__ uint32_t wavelet_count_less(const Wavelet& wv, int levels, uint32_t s,
                                                        uint32_t e, uint32_t v)
 {
     if (v >> levels) return e - s;  // v beyond every stored value
     uint32_t cnt = 0;
     for (int l = 0; l < levels; ++l) {
-        const uint32_t os = rank1(sm.bits[l], sm.pre[l], s);
-        const uint32_t oe = rank1(sm.bits[l], sm.pre[l], e);
+        const uint32_t os = rank1(wv.bits[l], wv.pre[l], s);
+        const uint32_t oe = rank1(wv.bits[l], wv.pre[l], e);
         if ((v >> (levels - 1 - l)) & 1u) {
             cnt += (e - oe) - (s - os);
-            s = sm.zeros[l] + os;
-            e = sm.zeros[l] + oe;
+            s = wv.zeros[l] + os;
+            e = wv.zeros[l] + oe;
         } else {
             s -= os;
             e -= oe;
@@ -1023,10 +1034,10 @@ __device__ __forceinline__ void upper_ssq_multi(const float* __restrict__ x, int
 
 // The j-th smallest value (0-based) of the window held at compacted
 // positions [ca, cb), from the wavelet matrix and the sorted tile.
-__device__ __forceinline__ float window_value(const MainSmem& sm, int levels, uint32_t ca,
+__device__ __forceinline__ float window_value(const MainSmem& sm, const Wavelet& wv, int levels, uint32_t ca,
                                               uint32_t cb, uint32_t j)
 {
-    return key_value((uint32_t)(sm.sortbuf[wavelet_kth(sm, levels, ca, cb, j)] >> 32));
+    return key_value((uint32_t)(sm.sortbuf[wavelet_kth(wv, levels, ca, cb, j)] >> 32));
 }
 
 // Scale ablation: the standard MAD, the lower median of |x - m| over a window
@@ -1036,7 +1047,7 @@ __device__ __forceinline__ float window_value(const MainSmem& sm, int levels, ui
 // minimum over lo of max(m - v_lo, v_{lo+q} - m).  The first term falls and
 // the second rises with lo: a binary search finds where they cross.  Float
 // subtraction is monotone, so the result is the exact MAD rounded once.
-__device__ __forceinline__ float window_mad(const MainSmem& sm, int levels, uint32_t ca,
+__device__ __forceinline__ float window_mad(const MainSmem& sm, const Wavelet& wv, int levels, uint32_t ca,
                                          uint32_t n, float m)
 {
     const uint32_t cb = ca + n;
@@ -1044,15 +1055,15 @@ __device__ __forceinline__ float window_mad(const MainSmem& sm, int levels, uint
     uint32_t lo = 0, hi = q;
     while (lo < hi) {
         const uint32_t mid = (lo + hi) >> 1;
-        const float below = m - window_value(sm, levels, ca, cb, mid);
-        const float above = window_value(sm, levels, ca, cb, mid + q) - m;
+        const float below = m - window_value(sm, wv, levels, ca, cb, mid);
+        const float above = window_value(sm, wv, levels, ca, cb, mid + q) - m;
         if (below <= above)
             hi = mid;
         else
             lo = mid + 1;
     }
-    float mad = window_value(sm, levels, ca, cb, lo + q) - m;
-    if (lo > 0) mad = __builtin_fminf(mad, m - window_value(sm, levels, ca, cb, lo - 1));
+    float mad = window_value(sm, wv, levels, ca, cb, lo + q) - m;
+    if (lo > 0) mad = __builtin_fminf(mad, m - window_value(sm, wv, levels, ca, cb, lo - 1));
     return mad;
 }
 
@@ -1189,15 +1200,15 @@ __device__ __forceinline__ bool window_range(const MainSmem& sm, const CurveDesc
 // Phase 1 of the window at compacted [ca, ca + n) from the sorted tile and
 // the wavelet matrix: the median m, and either n+ (the points strictly
 // above m, for Eq. 1) or, with the MAD ablation, the scale itself.
-__device__ __forceinline__ void window_phase1(const MainSmem& sm, int levels, int nv, int scale,
+__device__ __forceinline__ void window_phase1(const MainSmem& sm, const Wavelet& wv, int levels, int nv, int scale,
                                               uint32_t ca, uint32_t n, float& m, float& sc,
                                               uint32_t& nplus)
 {
     const uint32_t cb = ca + n;
-    const uint32_t rk = wavelet_kth(sm, levels, ca, cb, (n - 1) >> 1);
+    const uint32_t rk = wavelet_kth(wv, levels, ca, cb, (n - 1) >> 1);
     m = key_value((uint32_t)(sm.sortbuf[rk] >> 32));
     if (scale == UMI_SCALE_MAD) {
-        sc = window_mad(sm, levels, ca, n, m);
+        sc = window_mad(sm, wv, levels, ca, n, m);
         return;
     }
     // the points strictly above m are the window's elements ranked after
@@ -1227,13 +1238,148 @@ __device__ __forceinline__ void window_phase1(const MainSmem& sm, int levels, in
             tied += ((uint32_t)(sm.sortbuf[j] & 0xffffffffull) - ca < n) ? 1u : 0u;
         nplus = n - k - 1 - tied;
     } else {
-        nplus = n - wavelet_count_less(sm, levels, ca, cb, rh + 1);
+        nplus = n - wavelet_count_less(wv, levels, ca, cb, rh + 1);
     }
+}
+
+// Wave-wide minimum and maximum by DPP, valid in lane 63.
+__device__ __forceinline__ uint32_t wave_min(uint32_t v)
+{
+#define UMI_STEP(CTRL, ROWS)                                                                       \
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROWS, 0xF, false))
+    UMI_STEP(0x111, 0xF);
+    UMI_STEP(0x112, 0xF);
+    UMI_STEP(0x114, 0xF);
+    UMI_STEP(0x118, 0xF);
+    UMI_STEP(0x142, 0xA);
+    UMI_STEP(0x143, 0xC);
+#undef UMI_STEP
+    return v;
+}
+
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) { return ~wave_min(~v); }
+
+// Inclusive sum over the lanes of a wave by DPP.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v)
+{
+#define UMI_STEP(CTRL, ROWS)                                                                       \
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false)
+    UMI_STEP(0x111, 0xF);
+    UMI_STEP(0x112, 0xF);
+    UMI_STEP(0x114, 0xF);
+    UMI_STEP(0x118, 0xF);
+    UMI_STEP(0x142, 0xA);
+    UMI_STEP(0x143, 0xC);
+#undef UMI_STEP
+    return v;
+}
+
+// Sorts the tile's (key, index) pairs: sortbuf[0, npad) ascending, padded
+// with ~0, from xv[0, nv) and the keys' range in sm.kmin, sm.kmax; cnt holds
+// kBuckets cleared counters.  The keys are dealt to kBuckets buckets of equal
+// key range (counted with LDS atomics, placed by a block scan), and each pair
+// then counts the pairs of its own bucket below it: seven barriers, where a
+// bitonic network over 2,048 pairs has 66.  The pairs are distinct, so the
+// order is the network's, whatever order the atomics ran in (the network took
+// a third of an estimate launch at W = 121 and 361 without its sweeps: 200 x
+// 18,000 samples at W = 121 went from 553 to 490 us with the buckets).  A tile with
+// more than kBucketMost pairs in a bucket (long runs of ties, or a few far
+// outliers) would count for longer than the network sorts; it takes the network.
+constexpr uint32_t kBucketMost = 96;
+
+__device__ __forceinline__ void sort_tile(MainSmem& sm, uint32_t* __restrict__ cnt, int nv, int npad)
+{
+    const int tid = (int)threadIdx.x;
+    const int wave = tid >> 6;
+    constexpr int kPer = kStageMax / kMainThreads;
+    const uint32_t kmin = sm.kmin;
+    const uint32_t range = sm.kmax - kmin;
+    const int shift = max(0, 32 - (int)__builtin_clz(range | 1u) - 11);
+    static_assert(kBuckets == 1 << 11, "shift");
+    uint32_t slot[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int i = tid + q * kMainThreads;
+        if (i < nv) slot[q] = atomicAdd(&cnt[(order_key(sm.xv[i]) - kmin) >> shift], 1u);
+    }
+    __syncthreads();
+    const uint4 c = reinterpret_cast<const uint4*>(cnt)[tid];
+    const uint32_t own = c.x + c.y + c.z + c.w;
+    const uint32_t incl = wave_scan(own);
+    if ((tid & 63) == 63) sm.wsum[wave] = incl;
+    if (__syncthreads_or(max(max(c.x, c.y), max(c.z, c.w)) > kBucketMost)) {
+        for (int i = tid; i < npad; i += kMainThreads)
+            sm.sortbuf[i] = i < nv ? ((uint64_t)order_key(sm.xv[i]) << 32) | (uint32_t)i : ~0ull;
+        __syncthreads();
+        for (int kk = 2; kk <= npad; kk <<= 1) {
+            for (int jj = kk >> 1; jj > 0; jj >>= 1) {
+                for (int cix = tid; cix < (npad >> 1); cix += kMainThreads) {
+                    const int i = 2 * cix - (cix & (jj - 1));
+                    const int l = i + jj;
+                    const uint64_t a = sm.sortbuf[i], b = sm.sortbuf[l];
+                    const bool asc = (i & kk) == 0;
+                    if ((a > b) == asc) {
+                        sm.sortbuf[i] = b;
+                        sm.sortbuf[l] = a;
+                    }
+                }
+                __syncthreads();
+            }
+        }
+        return;
+    }
+    uint32_t base = incl - own;
+#pragma unroll
+    for (int w = 0; w < kMainThreads / 64; ++w) base += w < wave ? sm.wsum[w] : 0u;
+    reinterpret_cast<uint4*>(cnt)[tid] = make_uint4(base, base + c.x, base + c.x + c.y,
+                                                    base + c.x + c.y + c.z);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int i = tid + q * kMainThreads;
+        if (i < nv) {
+            const uint32_t key = order_key(sm.xv[i]);
+            sm.sortbuf[cnt[(key - kmin) >> shift] + slot[q]] = ((uint64_t)key << 32) | (uint32_t)i;
+        }
+    }
+    __syncthreads();
+    uint64_t e[kPer];
+    uint32_t rank[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int i = tid + q * kMainThreads;
+        if (i < nv) {
+            e[q] = sm.sortbuf[i];
+            const uint32_t b = ((uint32_t)(e[q] >> 32) - kmin) >> shift;
+            const uint32_t lo = cnt[b];
+            const uint32_t hi = b + 1 < (uint32_t)kBuckets ? cnt[b + 1] : (uint32_t)nv;
+            uint32_t r = lo;
+            for (uint32_t j = lo; j < hi; ++j) r += sm.sortbuf[j] < e[q] ? 1u : 0u;
+            rank[q] = r;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int i = tid + q * kMainThreads;
+        if (i < nv)
+            sm.sortbuf[rank[q]] = e[q];
+        else if (i < npad)
+            sm.sortbuf[i] = ~0ull;
+    }
+    __syncthreads();
+}
+
+// sort_tile as a call, for the instances with every path: inlined there it
+// cost them 18 spilled registers (a replayed step of six curves, 89 us against 83).
+__device__ __noinline__ void sort_tile_call(MainSmem& sm, uint32_t* cnt, int nv, int npad)
+{
+    sort_tile(sm, cnt, nv, npad);
 }
 
 // The windows of one tile: each lane takes R consecutive output positions.
 template <int R, int kFeat>
-__device__ __forceinline__ void tile_windows(const MainSmem& sm, int levels, int nv,
+__device__ __forceinline__ void tile_windows(const MainSmem& sm, const Wavelet& wv, int levels, int nv,
                                              const CurveDesc& cd, int h, int s0, int N, int t0,
                                              int t1,
                                              const int32_t* __restrict__ segid, float alpha,
@@ -1285,7 +1431,7 @@ __device__ __forceinline__ void tile_windows(const MainSmem& sm, int levels, int
             m[r] = pm[r];  // from the small-window networks
             nplus[r] = pn[r];
         } else if (live[r]) {
-            window_phase1(sm, levels, nv, scale, ca[r], n[r], m[r], sc[r], nplus[r]);
+            window_phase1(sm, wv, levels, nv, scale, ca[r], n[r], m[r], sc[r], nplus[r]);
         }
     }
     if (scale != UMI_SCALE_MAD) {
@@ -1486,7 +1632,7 @@ __device__ __forceinline__ void window_phase1_scan(const MainSmem& sm, int nv, u
 }
 
 template <int G, int kFeat>
-__device__ __forceinline__ void tile_windows_split(const MainSmem& sm, int levels, int nv,
+__device__ __forceinline__ void tile_windows_split(const MainSmem& sm, const Wavelet& wv, int levels, int nv,
                                                    const CurveDesc& cd, int h, int s0, int N,
                                                    int t0, int t1,
                                                    const int32_t* __restrict__ segid,
@@ -1508,7 +1654,7 @@ __device__ __forceinline__ void tile_windows_split(const MainSmem& sm, int level
         if (scan)
             window_phase1_scan<G>(sm, nv, ca, n, m, nplus);
         else
-            window_phase1(sm, levels, nv, scale, ca, n, m, sc, nplus);
+            window_phase1(sm, wv, levels, nv, scale, ca, n, m, sc, nplus);
     }
     const float* x = sm.xv + ca;
     if (live && scale != UMI_SCALE_MAD) {
@@ -1575,19 +1721,23 @@ __device__ __forceinline__ void tile_windows_split(const MainSmem& sm, int level
 // result depends only on the group and the window, never on the tile.
 
 struct CoreLds {
-    float* cv;    // core samples in value order
-    float* fst;   // first value of each block, then NaN up to the search range
-    float* g;     // five power sums per block edge
-    float* edge;  // samples before the core (64 slots), samples after it (72)
+    float* cv;      // core samples in value order
+    float* edge;    // samples before the core (64 slots), the core's samples
+                    // beyond its last whole block, samples after the core
+    uint32_t* over; // Phase 1: kCoreRanks edge-sample masks, then (the same
+                    // space) tree and g
+    float* tree;    // first value of each block, by a search tree (core_find)
+    float* g;       // five power sums per block edge
 };
 
 __device__ __forceinline__ CoreLds core_lds(float* base, int cap)
 {
     CoreLds c;
     c.cv = base;
-    c.fst = base + cap;
-    c.g = c.fst + core_search(cap);
-    c.edge = c.g + 5 * (cap / kCoreBlock + 1);
+    c.edge = base + ((cap + 3) & ~3);
+    c.tree = c.edge + kCoreEdge;
+    c.over = reinterpret_cast<uint32_t*>(c.tree);
+    c.g = c.tree + core_tree(cap / kCoreBlock);
     return c;
 }
 
@@ -1621,14 +1771,12 @@ __device__ __forceinline__ float lane_value(float v, int lane)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
-// The wave's core: nc samples (a multiple of kCoreBlock) at compacted
-// positions [cca, cca + nc).  False when the deviations' scale is unusable.
-__device__ __forceinline__ bool core_build(const MainSmem& sm, const CoreLds& cw, int nv, int npad,
-                                           uint32_t cca, int nc, float alpha, float& centre,
-                                           float& unit)
+// The wave's core in value order, nc samples at compacted positions
+// [cca, cca + nc), and the edge samples.
+__device__ __forceinline__ void core_collect(const MainSmem& sm, const CoreLds& cw, int nv, int npad,
+                                             uint32_t cca, int nc)
 {
     const int lane = __lane_id();
-    const int nb = nc / kCoreBlock;
     int base = 0;
     for (int j0 = 0; j0 < nv && base < nc; j0 += 256) {
         uint64_t e[4];
@@ -1646,16 +1794,31 @@ __device__ __forceinline__ bool core_build(const MainSmem& sm, const CoreLds& cw
             base += (int)__popcll(m);
         }
     }
-    // the samples on either side of the core
-    {
-        const int l = (int)cca - 64 + lane, r = (int)cca + nc + lane;
-        cw.edge[lane] = l >= 0 ? sm.xv[l] : 0.0f;
-        cw.edge[64 + lane] = r < nv ? sm.xv[r] : 0.0f;
-        if (lane < 8) cw.edge[128 + lane] = r + 64 < nv ? sm.xv[r + 64] : 0.0f;
-    }
     wave_lds_sync();
-    for (int b = lane; b < core_search(nc); b += 64)
-        cw.fst[b] = b < nb ? cw.cv[kCoreBlock * b] : __builtin_nanf("");
+    const int rem = nc & (kCoreBlock - 1);
+    const int l = (int)cca - 64 + lane, r = (int)cca + nc + lane;
+    cw.edge[lane] = l >= 0 ? sm.xv[l] : 0.0f;
+    if (lane < rem) cw.edge[64 + lane] = cw.cv[nc - rem + lane];
+    cw.edge[64 + rem + lane] = r < nv ? sm.xv[r] : 0.0f;
+    wave_lds_sync();
+}
+
+// The core's block table and power sums.  False when the deviations' scale
+// is unusable.
+__device__ __forceinline__ bool core_build(const CoreLds& cw, int nc, float alpha, float& centre,
+                                           float& unit)
+{
+    const int lane = __lane_id();
+    const int nb = nc / kCoreBlock;
+    {
+        float* t = cw.tree;
+        for (int st = 1 << (2 * (core_levels(nb) - 1)); st > 0; st >>= 2) {
+            const int len = core_level_len(nb, st);
+            for (int i = lane; i < len; i += 64)
+                t[i] = i * st < nb ? cw.cv[kCoreBlock * i * st] : __builtin_nanf("");
+            t += len;
+        }
+    }
     // a centre about half-way from the median to where the iterations end
     // (above it for alpha > 1), and a power of two near the core's spread
     const float qf = alpha > 1.0f ? __builtin_fminf(0.5f + 0.1f * __builtin_log2f(alpha), 0.8f) : 0.5f;
@@ -1702,19 +1865,205 @@ __device__ __forceinline__ bool core_build(const MainSmem& sm, const CoreLds& cw
     return true;
 }
 
-// The last block whose first value is <= each knot (0 where none is).
+// Phase 1 (Section 2.1) of a group's windows.  A window is the core plus at
+// most 63 edge samples, so its median lies at one of the kCoreRanks core
+// samples around the core's middle, or between two of them.  For each of
+// those core ranks the wave forms the set of edge samples below that core sample (a bit
+// mask: the edge samples' ranks by binary search, set in LDS, then a prefix
+// "or" over the lanes); a window counts its own ones with a mask of its edge
+// samples, and a binary search over the ranks finds the core sample at or
+// below the median.  The median is that sample or one of the few edge samples
+// between it and the next.  No tile-wide structure beyond the sorted tile.
+// Values compare as floats; a median of zero takes its sign by counting.
+// Windows without a core walk the sorted tile.  Also n+ of Eq. 1.  Against the
+// wavelet matrix (a build of 44 barriers, then a descent per window): 1,000 x
+// 18,000 samples at W = 361 without iterations 1.50 -> 0.88 ms.
+__device__ __forceinline__ uint32_t wave_or_scan(uint32_t v)
+{
+#define UMI_STEP(CTRL, ROWS)                                                                       \
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false)
+    UMI_STEP(0x111, 0xF);
+    UMI_STEP(0x112, 0xF);
+    UMI_STEP(0x114, 0xF);
+    UMI_STEP(0x118, 0xF);
+    UMI_STEP(0x142, 0xA);
+    UMI_STEP(0x143, 0xC);
+#undef UMI_STEP
+    return v;
+}
+
+// bits [lo, hi) of word w of a bit vector
+__device__ __forceinline__ uint32_t range_word(int lo, int hi, int w)
+{
+    const int a = min(max(lo - 32 * w, 0), 32), b = min(max(hi - 32 * w, 0), 32);
+    const uint32_t up = b >= 32 ? ~0u : (1u << b) - 1u;
+    const uint32_t dn = a >= 32 ? ~0u : (1u << a) - 1u;
+    return up & ~dn;
+}
+
+__device__ __forceinline__ void core_phase1(const MainSmem& sm, const CoreLds& cw, int nv,
+                                            bool core, int nc, int cca, bool live, uint32_t ca,
+                                            uint32_t n, float& m, uint32_t& nplus)
+{
+    const int lane = __lane_id();
+    const int k = (int)((n - 1) >> 1);
+    bool found = false, zero = false;
+    if (core) {
+        const int r0 = (nc >> 1) - kCoreRanks / 2;
+        const float* const mid = cw.cv + r0;
+        // masks: lane r's holds the edge samples below core rank r0 + r
+#pragma unroll
+        for (int w = 0; w < kCoreMaskWords; ++w) cw.over[kCoreMaskWords * lane + w] = 0u;
+        const int rem = nc & (kCoreBlock - 1);
+        const float e[2] = {cw.edge[lane], cw.edge[64 + rem + lane]};
+        int rk[2] = {0, 0};
+#pragma unroll
+        for (int st = kCoreRanks / 2; st > 0; st >>= 1) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) rk[q] += mid[rk[q] + st - 1] < e[q] ? st : 0;
+        }
+        wave_lds_sync();
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            rk[q] += mid[rk[q]] < e[q] ? 1 : 0;
+            if (rk[q] < kCoreRanks)
+                atomicOr(&cw.over[kCoreMaskWords * rk[q] + 2 * q + (lane >> 5)], 1u << (lane & 31));
+        }
+        wave_lds_sync();
+        uint32_t below[kCoreMaskWords], own[kCoreMaskWords];
+        const int nl = cca - (int)ca, ne = (int)n - nc;
+#pragma unroll
+        for (int w = 0; w < kCoreMaskWords; ++w) {
+            below[w] = wave_or_scan(cw.over[kCoreMaskWords * lane + w]);
+            own[w] = live ? range_word(64 - nl, 64 - nl + ne, w) : 0u;
+        }
+        wave_lds_sync();
+#pragma unroll
+        for (int w = 0; w < kCoreMaskWords; ++w) cw.over[kCoreMaskWords * lane + w] = below[w];
+        wave_lds_sync();
+        // the last rank r (from r0) with rank + own edge samples below <= k
+        int r = 0;
+#pragma unroll
+        for (int st = kCoreRanks / 2; st > 0; st >>= 1) {
+            int f = r0 + r + st;
+#pragma unroll
+            for (int w = 0; w < kCoreMaskWords; ++w)
+                f += __popc(cw.over[kCoreMaskWords * (r + st) + w] & own[w]);
+            r += f <= k ? st : 0;
+        }
+        if (live) {
+            // (past the last rank there is no gap: the median is that core
+            // sample, as no edge sample lies below it)
+            int f = r0 + r;
+            const int r1 = min(r + 1, kCoreRanks - 1);
+            uint32_t gap[kCoreMaskWords];
+#pragma unroll
+            for (int w = 0; w < kCoreMaskWords; ++w) {
+                const uint32_t lo = cw.over[kCoreMaskWords * r + w] & own[w];
+                gap[w] = cw.over[kCoreMaskWords * r1 + w] & own[w] & ~lo;
+                f += __popc(lo);
+            }
+            int t = k - f;  // 0: the core sample; else the t-th of the gap
+            m = mid[r];
+            nplus = n - (uint32_t)k - 1u;
+            float last = -__builtin_inff();
+            while (t > 0) {  // the gap's distinct values in turn
+                float least = __builtin_inff();
+                int cnt = 0;
+#pragma unroll
+                for (int w = 0; w < kCoreMaskWords; ++w) {
+                    for (uint32_t b = gap[w]; b != 0; b &= b - 1) {
+                        const float x = cw.edge[32 * w + (w < 2 ? 0 : rem) + (int)__builtin_ctz(b)];
+                        if (x > last) {
+                            cnt = x < least ? 1 : cnt + (x == least ? 1 : 0);
+                            least = __builtin_fminf(least, x);
+                        }
+                    }
+                }
+                m = least;
+                if (cnt <= 0 || t <= cnt) {
+                    nplus -= (uint32_t)(cnt - t);  // equal edge samples after it
+                    break;
+                }
+                t -= cnt;
+                last = least;
+            }
+            found = true;
+            // an edge sample equal to a core sample ranks below it, so what
+            // else ties with the median after it are the next core samples:
+            // the first one above it by a galloping search
+            const float* const c = mid + r + 1;
+            const int left = nc - (r0 + r + 1);
+            if (left > 0 && c[0] == m) {
+                int lo = 0, hi = 1;  // c[lo] == m
+                while (hi < left && c[hi] == m) {
+                    lo = hi;
+                    hi = 2 * hi + 1;
+                }
+                hi = min(hi, left);
+                while (hi - lo > 1) {
+                    const int at = (lo + hi) >> 1;
+                    if (c[at] == m)
+                        lo = at;
+                    else
+                        hi = at;
+                }
+                nplus -= (uint32_t)(lo + 1);
+            }
+            zero = m == 0.0f;
+        }
+        wave_lds_sync();  // the masks give way to the block table
+    }
+    const float* const x = sm.xv + ca;
+    if (live && !found) {
+        // the (k + 1)-th pair of the window in the sorted tile (padded to a
+        // multiple of 64 with pairs of no window)
+        int need = k + 1;
+        for (int j0 = 0; j0 < nv; j0 += 8) {
+            uint64_t p[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) p[u] = sm.sortbuf[j0 + u];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const bool in = (uint32_t)p[u] - ca < n;
+                if (in && need == 1) m = key_value((uint32_t)(p[u] >> 32));
+                need -= in ? 1 : 0;
+            }
+            if (need <= 0) break;
+        }
+        zero = true;
+    }
+    if (zero) {
+        // n+ by counting, and the negative zeros of a zero median
+        int above = 0, negative = 0;
+        for (int j = 0; j < (int)n; ++j) {
+            above += x[j] > m ? 1 : 0;
+            negative += (int)(__float_as_uint(x[j]) >> 31);
+        }
+        nplus = (uint32_t)above;
+        if (m == 0.0f) m = k < negative ? -0.0f : 0.0f;
+    }
+}
+
+// The last block whose first value is <= each knot (0 where none is): four
+// values per level of the tree, the first of which needs no test (a level
+// holds every 4th value of the next; beyond the last value stands NaN).  One
+// 16-byte load per level where a binary search takes two dependent ones.
 template <int K>
-__device__ __forceinline__ void core_find(const float* __restrict__ fst, int top,
+__device__ __forceinline__ void core_find(const float* __restrict__ tree, int nb,
                                           const float (&knot)[K], int (&b)[K])
 {
 #pragma unroll
     for (int i = 0; i < K; ++i) b[i] = 0;
-    for (int s = top; s > 0; s >>= 1) {
+    for (int st = 1 << (2 * (core_levels(nb) - 1)); st > 0; st >>= 2) {
 #pragma unroll
-        for (int i = 0; i < K; ++i) b[i] += fst[b[i] + s - 1] <= knot[i] ? s : 0;
+        for (int i = 0; i < K; ++i) {
+            const float4 v = reinterpret_cast<const float4*>(tree)[b[i]];
+            b[i] = 4 * b[i] + (v.y <= knot[i] ? 1 : 0) + (v.z <= knot[i] ? 1 : 0) +
+                   (v.w <= knot[i] ? 1 : 0);
+        }
+        tree += core_level_len(nb, st);
     }
-#pragma unroll
-    for (int i = 0; i < K; ++i) b[i] = max(b[i] - 1, 0);
 }
 
 // Sums of w and w z over blocks [e0, e1) with z = (d - delta) kappa, |z| < 1:
@@ -1752,8 +2101,7 @@ __device__ __forceinline__ void core_block(const float* __restrict__ cv, int b, 
 constexpr float kCoreReach = 0.5f;
 
 template <int kFeat>
-__device__ __forceinline__ void core_group(const MainSmem& sm, const CoreLds& cw, int levels,
-                                           int nv, int npad, const CurveDesc& cd, int h, int s0,
+__device__ __forceinline__ void core_group(const MainSmem& sm, const CoreLds& cw, int nv, int npad, const CurveDesc& cd, int h, int s0,
                                            int N, int t0, int t1, int g0,
                                            const int32_t* __restrict__ segid, float alpha, float c,
                                            int iters, int scale, const double* __restrict__ time,
@@ -1774,21 +2122,22 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const CoreLds& cw
     if (live_m != 0) {
         uint32_t nplus = 0;
         float sc = 0.0f;
-        if (live) window_phase1(sm, levels, nv, UMI_SCALE_UPPER_RMS, ca, n, m, sc, nplus);
         // the core: from the last window's start to the first window's end
         const int lane_lo = (int)__builtin_ctzll(alive_m), lane_hi = 63 - (int)__builtin_clzll(alive_m);
         const int cca = __builtin_amdgcn_readlane((int)ca, lane_hi);
         const int ccb = __builtin_amdgcn_readlane((int)(ca + n), lane_lo);
-        const int nc = min(ccb - cca, core_cap(cd.W)) & ~(kCoreBlock - 1);
+        const int nc = min(ccb - cca, core_cap(cd.W));
         float centre = 0.0f, unit = 1.0f;
-        const bool core = nc >= 8 * kCoreBlock &&
-                          core_build(sm, cw, nv, npad, (uint32_t)cca, nc, alpha, centre, unit);
-        const int top = core ? core_search(nc) >> 1 : 0;
+        bool core = nc >= kCoreRanks;
+        if (core) core_collect(sm, cw, nv, npad, (uint32_t)cca, nc);
+        core_phase1(sm, cw, nv, core, nc, cca, live, ca, n, m, nplus);
+        core = core && core_build(cw, nc, alpha, centre, unit);
         const int nb = nc / kCoreBlock;
-        // edge samples: nl before the core, then those after it
+        // samples to sum one by one: nl before the core, what the core holds
+        // beyond its last whole block, and those after the core
         const int nl = live ? cca - (int)ca : 0;
         const float* const xe = cw.edge + 64 - nl;
-        const int ne = live ? (int)n - nc : 0;
+        const int ne = live ? (int)n - nb * kCoreBlock : 0;
         const int src = (int)__builtin_ctzll(live_m);
         const int ne_u = __builtin_amdgcn_readlane(ne, src);
         const bool even = __all(!live || ne == ne_u);
@@ -1809,7 +2158,7 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const CoreLds& cw
             }
             const float knot[1] = {m};
             int b[1];
-            core_find<1>(cw.fst, top, knot, b);
+            core_find<1>(cw.tree, nb, knot, b);
             core_block(cw.cv, b[0], up2);
             const int e = b[0] + 1;
             const float d0 = (float)(kCoreBlock * (nb - e));
@@ -1843,6 +2192,7 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const CoreLds& cw
         const float ka = 1.0f / (cs * unit);  // per unit of the power sums
         const float kb = alpha * ka;
         const bool scaled = ka > 1e-4f && ka < 1e4f;
+        const float vmax = core ? cw.cv[kCoreBlock * nb - 1] : 0.0f;
         for (int it = 0; it < iters; ++it) {
             const float bb = -mu * k;
             float sw = 0.0f, swv = 0.0f;
@@ -1855,12 +2205,26 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const CoreLds& cw
                 } else {
                     for (int j = 0; j < ne; ++j) acc(xe[j]);
                 }
-                const float knot[3] = {mu - cl, mu, mu + cs};
+                const float knot[2] = {mu - cl, mu};
                 int b[3];
-                core_find<3>(cw.fst, top, knot, b);
+                {
+                    int b2[2];
+                    core_find<2>(cw.tree, nb, knot, b2);
+                    b[0] = b2[0];
+                    b[1] = b2[1];
+                }
+                // the upper cut-off is rarely inside the core: past its
+                // largest value every block above the location is whole
+                b[2] = nb;
+                if (!(mu + cs >= vmax)) {
+                    const float hi[1] = {mu + cs};
+                    int b1[1];
+                    core_find<1>(cw.tree, nb, hi, b1);
+                    b[2] = b1[0];
+                    if (b[2] != b[1]) core_block(cw.cv, b[2], acc);
+                }
                 core_block(cw.cv, b[0], acc);
                 if (b[1] != b[0]) core_block(cw.cv, b[1], acc);
-                if (b[2] != b[1]) core_block(cw.cv, b[2], acc);
                 const float delta = (mu - centre) * unit;
                 const float far = __builtin_fabsf(delta);
                 const int eb = min(b[0] + 1, b[1]), ea = min(b[1] + 1, b[2]);
@@ -1917,18 +2281,17 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
     float* __restrict__ median, int core_floats)
 {
     __shared__ MainSmem sm;
-    // the wavelet build's sequences; in instances with sorted cores the same
-    // space holds the waves' cores once the matrix is built
-    uint16_t* seq;
+    Wavelet* wvp;
     float* cores = nullptr;
     if constexpr ((kFeat & kFeatCore) != 0) {
         extern __shared__ __align__(16) float dyn[];
-        seq = reinterpret_cast<uint16_t*>(dyn);
+        wvp = reinterpret_cast<Wavelet*>(dyn);
         cores = dyn;
     } else {
-        __shared__ uint16_t seq_[2 * kStageMax];  // wavelet-matrix level sequences
-        seq = seq_;
+        __shared__ __align__(16) Wavelet wv_;
+        wvp = &wv_;
     }
+    Wavelet& wv = *wvp;
     const int tid = threadIdx.x;
     const int lane = __lane_id();
     const int wave = tid >> 6;
@@ -1946,6 +2309,8 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
         // (not touched at all when the first round covers every tile).
         constexpr bool kStaticFirst = (kFeat & kFeatSplit) != 0;
         if (tid == 0) {
+            sm.kmin = ~0u;
+            sm.kmax = 0u;
             if (counter && !(kStaticFirst && round == 0))
                 sm.tile = (kStaticFirst && tile_first + (int)gridDim.x >= tile_end)
                               ? tile_end
@@ -1955,7 +2320,7 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
                 sm.tile = tile_first + (int)blockIdx.x + round * (int)gridDim.x;
         }
         __syncthreads();
-        const int tile = sm.tile;
+        const int tile = __builtin_amdgcn_readfirstlane(sm.tile);
         if (tile >= tile_end) break;
 
         const int2 td = tiles[tile];
@@ -2007,16 +2372,17 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
             __syncthreads();
         word_prefix(sm.vbits, sm.vpre, nwv, reinterpret_cast<uint32_t*>(&sm.nvalid));
         __syncthreads();
-        const int nv = sm.nvalid;
+        const int nv = __builtin_amdgcn_readfirstlane(sm.nvalid);
         int npad = 64;
         while (npad < nv) npad <<= 1;
         int levels = 6;
         while ((1 << levels) < npad) ++levels;
+        const bool core_tile = (kFeat & kFeatCore) && cd.core;
         const bool scan_tile = (kFeat & kFeatSplit) && G > 1 && scale != UMI_SCALE_MAD;
 
         if (simple) {
             // every staged sample is valid: values and keys in index order
-            uint32_t* keys = reinterpret_cast<uint32_t*>(seq);
+            uint32_t* keys = reinterpret_cast<uint32_t*>(wv.seq);
             for (int i = tid; i < N; i += kMainThreads) {
                 const float x = f[i];
                 sm.xv[i] = x;
@@ -2025,19 +2391,35 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
             __syncthreads();
         } else {
         // --- compaction: values in index order, (key, index) for the sort ---
+        const bool counted = (kFeat & kFeatSplit) && npad <= kMainThreads;
+        uint32_t kmin = ~0u, kmax = 0u;
         for (int i0 = wave * 64; i0 < nwv * 64; i0 += kMainThreads) {
             const int i = i0 + lane;
             if (i < N && sg[i] != -1) {
                 const float x = f[i];
                 const uint32_t ci = rank1(sm.vbits, sm.vpre, (uint32_t)i);
                 sm.xv[ci] = x;
-                sm.sortbuf[ci] = ((uint64_t)order_key(x) << 32) | ci;
+                const uint32_t key = order_key(x);
+                if (counted) sm.sortbuf[ci] = ((uint64_t)key << 32) | ci;
+                kmin = min(kmin, key);
+                kmax = max(kmax, key);
             }
         }
-        for (int i = nv + tid; i < npad; i += kMainThreads) sm.sortbuf[i] = ~0ull;
+        if (counted) {
+            for (int i = nv + tid; i < npad; i += kMainThreads) sm.sortbuf[i] = ~0ull;
+        } else {
+            kmin = wave_min(kmin);
+            kmax = wave_max(kmax);
+            if (lane == 63) {
+                atomicMin(&sm.kmin, kmin);
+                atomicMax(&sm.kmax, kmax);
+            }
+            // clear the tile sort's counters
+            reinterpret_cast<uint4*>(&wv)[tid] = make_uint4(0u, 0u, 0u, 0u);
+        }
         __syncthreads();
 
-        if ((kFeat & kFeatSplit) && npad <= kMainThreads) {
+        if (counted) {
             // --- a small tile: every element counts the elements below it ---
             // The (key, index) pairs are distinct, so the counts are the
             // ranks the sorting network would give, without a barrier per
@@ -2060,58 +2442,46 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
             if (tid < nv) sm.sortbuf[rank] = mine;
             __syncthreads();
         } else {
-            // --- bitonic sort of sortbuf[0, npad) ascending ---
-            for (int kk = 2; kk <= npad; kk <<= 1) {
-                for (int jj = kk >> 1; jj > 0; jj >>= 1) {
-                    for (int cix = tid; cix < (npad >> 1); cix += kMainThreads) {
-                        const int i = 2 * cix - (cix & (jj - 1));
-                        const int l = i + jj;
-                        const uint64_t a = sm.sortbuf[i], b = sm.sortbuf[l];
-                        const bool asc = (i & kk) == 0;
-                        if ((a > b) == asc) {
-                            sm.sortbuf[i] = b;
-                            sm.sortbuf[l] = a;
-                        }
-                    }
-                    __syncthreads();
-                }
-            }
+            if (kFeat & kFeatExtra)
+                sort_tile_call(sm, reinterpret_cast<uint32_t*>(&wv), nv, npad);
+            else
+                sort_tile(sm, reinterpret_cast<uint32_t*>(&wv), nv, npad);
         }
 
         // --- wavelet matrix over the sequence rank_of[compacted index]; split
         // tiles take their medians from the sorted tile directly ---
-        if (!scan_tile) {
+        if (!scan_tile && !core_tile) {
         for (int r = tid; r < npad; r += kMainThreads) {
             if (r < nv)
-                seq[(uint32_t)(sm.sortbuf[r] & 0xffffffffull)] = (uint16_t)r;
+                wv.seq[0][(uint32_t)(sm.sortbuf[r] & 0xffffffffull)] = (uint16_t)r;
             else
-                seq[r] = (uint16_t)(npad - 1);
+                wv.seq[0][r] = (uint16_t)(npad - 1);
         }
         __syncthreads();
         const int nwl = (npad >> 6) + 1;
         for (int l = 0; l < levels; ++l) {
-            const uint16_t* cur = seq + (l & 1) * kStageMax;
-            uint16_t* nxt = seq + ((l + 1) & 1) * kStageMax;
+            const uint16_t* cur = wv.seq[l & 1];
+            uint16_t* nxt = wv.seq[(l + 1) & 1];
             const int bit = levels - 1 - l;
             for (int i0 = wave * 64; i0 < nwl * 64; i0 += kMainThreads) {
                 const int i = i0 + lane;
                 const bool one = (i < npad) && (((cur[i < npad ? i : 0] >> bit) & 1) != 0);
                 const uint64_t bal = __ballot(one);
-                if (lane == 0) sm.bits[l][i0 >> 6] = bal;
+                if (lane == 0) wv.bits[l][i0 >> 6] = bal;
             }
             __syncthreads();
             uint32_t ones_total;
-            word_prefix(sm.bits[l], sm.pre[l], nwl, &sm.zeros[l]);
+            word_prefix(wv.bits[l], wv.pre[l], nwl, &wv.zeros[l]);
             __syncthreads();
             if (tid == 0) {
-                ones_total = sm.zeros[l];
-                sm.zeros[l] = (uint32_t)npad - ones_total;
+                ones_total = wv.zeros[l];
+                wv.zeros[l] = (uint32_t)npad - ones_total;
             }
             __syncthreads();
-            const uint32_t z = sm.zeros[l];
+            const uint32_t z = wv.zeros[l];
             for (int i = tid; i < npad; i += kMainThreads) {
                 const uint16_t val = cur[i];
-                const uint32_t o = rank1(sm.bits[l], sm.pre[l], (uint32_t)i);
+                const uint32_t o = rank1(wv.bits[l], wv.pre[l], (uint32_t)i);
                 const bool one = ((val >> bit) & 1) != 0;
                 nxt[one ? z + o : (uint32_t)i - o] = val;
             }
@@ -2124,21 +2494,21 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
         // positions per lane ---
         if ((kFeat & kFeatSplit) && G > 1) {
             if (G == 2)
-                tile_windows_split<2, kFeat>(sm, levels, nv, cd, h, s0, N, t0, t1, segid, alpha, c, iters,
+                tile_windows_split<2, kFeat>(sm, wv, levels, nv, cd, h, s0, N, t0, t1, segid, alpha, c, iters,
                                       scale, time, trend, median, detrended, scan_tile);
             else if (G == 4)
-                tile_windows_split<4, kFeat>(sm, levels, nv, cd, h, s0, N, t0, t1, segid, alpha, c, iters,
+                tile_windows_split<4, kFeat>(sm, wv, levels, nv, cd, h, s0, N, t0, t1, segid, alpha, c, iters,
                                       scale, time, trend, median, detrended, scan_tile);
             else
-                tile_windows_split<8, kFeat>(sm, levels, nv, cd, h, s0, N, t0, t1, segid, alpha, c, iters,
+                tile_windows_split<8, kFeat>(sm, wv, levels, nv, cd, h, s0, N, t0, t1, segid, alpha, c, iters,
                                       scale, time, trend, median, detrended, scan_tile);
             __syncthreads();
             continue;
         }
-        if ((kFeat & kFeatCore) && cd.core) {
+        if (core_tile) {
             const CoreLds cw = core_lds(cores + wave * core_floats, core_cap(cd.W));
             for (int g0 = (t0 & ~63) + wave * 64; g0 < t1; g0 += kMainThreads)
-                core_group<kFeat>(sm, cw, levels, nv, npad, cd, h, s0, N, t0, t1, g0, segid, alpha,
+                core_group<kFeat>(sm, cw, nv, npad, cd, h, s0, N, t0, t1, g0, segid, alpha,
                                   c, iters, scale, time, trend, median, detrended);
             __syncthreads();
             continue;
@@ -2150,7 +2520,7 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
         float pm[3] = {0.0f, 0.0f, 0.0f};
         uint32_t pn[3] = {0u, 0u, 0u};
         if (simple) {
-            const uint32_t* keys = reinterpret_cast<const uint32_t*>(seq);
+            const uint32_t* keys = reinterpret_cast<const uint32_t*>(wv.seq);
             const int p0 = t0 + tid * R;
             if (p0 < t1) {
                 const int b = p0 - h - s0;
@@ -2161,13 +2531,13 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
             }
         }
         if (R == 3)
-            tile_windows<3, kFeat>(sm, levels, nv, cd, h, s0, N, t0, t1, segid, alpha, c, iters, scale,
+            tile_windows<3, kFeat>(sm, wv, levels, nv, cd, h, s0, N, t0, t1, segid, alpha, c, iters, scale,
                             simple, pm, pn, time, trend, median, detrended);
         else if (R == 2)
-            tile_windows<2, kFeat>(sm, levels, nv, cd, h, s0, N, t0, t1, segid, alpha, c, iters, scale,
+            tile_windows<2, kFeat>(sm, wv, levels, nv, cd, h, s0, N, t0, t1, segid, alpha, c, iters, scale,
                             simple, pm, pn, time, trend, median, detrended);
         else
-            tile_windows<1, kFeat>(sm, levels, nv, cd, h, s0, N, t0, t1, segid, alpha, c, iters, scale,
+            tile_windows<1, kFeat>(sm, wv, levels, nv, cd, h, s0, N, t0, t1, segid, alpha, c, iters, scale,
                             simple, pm, pn, time, trend, median, detrended);
         __syncthreads();
     }
@@ -2265,8 +2635,8 @@ hipError_t launch_main(const float* flux, const int32_t* segid, const BatchHeade
     const int core_floats = core_floats_for(feat >> kFeatBits);
     feat &= (1 << kFeatBits) - 1;
     const size_t dyn = (feat & kFeatCore)
-                           ? std::max((size_t)(kMainThreads / 64) * core_floats * sizeof(float),
-                                      (size_t)2 * kStageMax * sizeof(uint16_t))
+                           ? std::max(sizeof(Wavelet),
+                                      (size_t)(kMainThreads / 64) * core_floats * sizeof(float))
                            : 0;
 #define UMI_LAUNCH_MAIN(F)                                                                       \
     hipLaunchKernelGGL(umi_main_kernel<F>, dim3(grid), dim3(kMainThreads), dyn, stream, flux, segid, \

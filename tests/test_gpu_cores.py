@@ -70,7 +70,7 @@ def core_batch(Ws, seed):
                                    for W in Ws for f, t in _shapes(W, rng)])
 
 
-@pytest.mark.parametrize("Ws,tile", [((193, 199, 255), 1536), ((361, 363), 1536), ((721,), 1280),
+@pytest.mark.parametrize("Ws,tile", [((137, 143), 1536), ((193, 199, 255), 1536), ((361, 363), 1536), ((721,), 1280),
                                      ((1081, 1441), 512), ((361,), 300)])
 def test_cores_against_oracle(torch, umi, oracle_lib, Ws, tile):
     b = core_batch(Ws, 7)
