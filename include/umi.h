@@ -206,15 +206,17 @@ umi_status umi_detrend_gather_ex(const float* flux, const double* time,
  * Plans: a replayable launch over fixed device arrays, for serving loops.
  * umi_plan_create binds the arrays (each `capacity` samples; time and median
  * may be NULL) and a non-default stream, allocates the plan's workspace once
- * and captures its hipGraphs: per staging slot one for batches of at most 256
- * pre-pass chunks (512k samples) and one for any batch, each a copy of the
- * staged tile table, the segmentation pre-pass and the persistent estimate
+ * and captures its hipGraphs: per staging slot one for each estimate kernel
+ * that windows up to max_W can need, each the set-up (which copies the staged
+ * curve table to the device and lists the tiles) and the persistent estimate
  * kernel.  umi_plan_run stages one batch -- curves at explicit offsets inside
  * the arrays, as for umi_detrend_gather, at most `max_curves` curves with
  * W <= max_W -- into one of two pinned staging slots and replays that slot's
- * graph for the batch's size on the plan's stream.
+ * graph on the plan's stream; a batch of at most 32 curves is launched with
+ * its table as kernel arguments instead, one kernel and no staging.
  * It allocates no device or pinned memory and returns without synchronising,
- * except that it waits for the replay that used the same slot two calls earlier.  Results
+ * except that a replay waits for the one that used the same slot two replays
+ * earlier.  Results
  * of a run are in `trend` / `median` once the stream reaches that point.
  * Calls on one plan are serialised; a plan is used from one device.
  * umi_plan_destroy waits for the stream and frees everything.
@@ -247,16 +249,15 @@ umi_status umi_plan_destroy(umi_plan* plan);
  * results (bit for bit, given the same launch options) and errors as
  * umi_detrend_batch; only the workspace differs.
  *
- * The workspace -- the staged header and curve table, the queue and pre-pass
- * counters, the pre-pass chunk records, the tile list and one segment word
- * per sample -- lives in a static device array
- * of UMI_NOALLOC_SCRATCH_BYTES (about 74 MiB) that each GPU the library runs
+ * The workspace -- the staged header and curve table, the tile queue and the
+ * tile list -- lives in a static device array
+ * of UMI_NOALLOC_SCRATCH_BYTES (8.5 MiB) that each GPU the library runs
  * on holds from the first call on that GPU until the process ends.  A call
  * allocates no device, pinned or host memory on its way to the launches (the
- * curve table is packed into static host arrays and copied with
- * hipMemcpyAsync from pageable memory; only an error message is built on the
- * heap); it looks up the array's device address once per GPU, on that GPU's
- * first call.
+ * curve table is packed into static host arrays; up to 32 curves it goes to
+ * the kernel as arguments, more are copied with hipMemcpyAsync from pageable
+ * memory; only an error message is built on the heap); it looks up the
+ * array's device address once per GPU, on that GPU's first call.
  *
  * Limits (larger batches give UMI_ERR_UNSUPPORTED and enqueue nothing):
  *   sum(lengths) <= UMI_NOALLOC_MAX_SAMPLES, n_curves <= UMI_NOALLOC_MAX_CURVES,
@@ -265,9 +266,7 @@ umi_status umi_plan_destroy(umi_plan* plan);
  *
  * Every call on a GPU uses that GPU's one array, whatever the stream, and
  * leaves the last batch's contents there (the kernels overwrite every part
- * they read before reading it; the pre-pass's ticket counters return to zero
- * at the end of each call, and its chunk records carry a launch count that
- * tells them from an earlier call's).  Calls on one stream
+ * they read before reading it).  Calls on one stream
  * are ordered by the stream; calls on one GPU whose stream work can overlap
  * (different streams, or several threads) race on the array and give
  * undefined results.  Host-side, concurrent calls are serialised by a lock.
@@ -275,7 +274,7 @@ umi_status umi_plan_destroy(umi_plan* plan);
 #define UMI_NOALLOC_MAX_SAMPLES 16777216 /* 2^24 samples per call */
 #define UMI_NOALLOC_MAX_CURVES 8192
 #define UMI_NOALLOC_MAX_TILES 1048576    /* 2^20 tiles per call */
-#define UMI_NOALLOC_SCRATCH_BYTES 78250496
+#define UMI_NOALLOC_SCRATCH_BYTES 8913664
 umi_status umi_detrend_batch_noalloc(const float* flux, const double* time,
                                      const int64_t* lengths, int64_t n_curves,
                                      const int32_t* W, float alpha, float c,

@@ -215,7 +215,7 @@ struct PackView {
     int32_t* order;           // scratch: input index per table entry
     int64_t ncurves = 0;      // entries written
     int64_t ntiles = 0;
-    int64_t nchunks = 0;      // pre-pass chunks
+    int64_t nchunks = 0;      // chunks of kPrepChunk samples
     int gpc = kDefaultGroupsPerCU;  // persistent groups per CU
     int feat = kFeatAll;      // estimate-kernel paths the batch needs (kFeat* bits)
 };
@@ -407,47 +407,37 @@ hipError_t grow(T** p, int64_t* cap, int64_t need, bool exact = false, bool* fre
 }
 
 struct DeviceBuffers {
-    int32_t* segid = nullptr;   // per sample slot: the segment word of each sample
-    int64_t cap_segid = 0;
     int2* tiles = nullptr;
     int64_t cap_tiles = 0;
-    ChunkRec* recs = nullptr;   // pre-pass chunk records
+    ChunkRec* recs = nullptr;   // chunk records of the launch interface
     int64_t cap_recs = 0;
-    Counters* ctr = nullptr;    // queue, ticket and epoch counters
+    Counters* ctr = nullptr;    // the tile queue
     int64_t cap_ctr = 0;
 
-    // Zero-filled on allocation (on `stream`, ahead of any kernel there): the
-    // counters, and chunk records whose flags must not look like this epoch's.
-    hipError_t reserve(int64_t span, int64_t ntiles, int64_t nchunks, hipStream_t stream,
-                       bool exact = false)
+    // The counters are zero-filled on allocation (on `stream`, ahead of any
+    // kernel there).
+    hipError_t reserve(int64_t ntiles, int64_t nchunks, hipStream_t stream, bool exact = false)
     {
         hipError_t e;
-        if ((e = grow(&segid, &cap_segid, span, exact)) != hipSuccess) return e;
         if ((e = grow(&tiles, &cap_tiles, ntiles, exact)) != hipSuccess) return e;
-        bool fresh_recs = false, fresh_ctr = false;
-        if ((e = grow(&recs, &cap_recs, nchunks, exact, &fresh_recs)) != hipSuccess) return e;
+        bool fresh_ctr = false;
+        if ((e = grow(&recs, &cap_recs, nchunks, exact)) != hipSuccess) return e;
         if ((e = grow(&ctr, &cap_ctr, 1, true, &fresh_ctr)) != hipSuccess) return e;
-        // a fresh counter restarts the epochs: old records must go too
-        if ((fresh_recs || fresh_ctr) && cap_recs > 0 &&
-            (e = hipMemsetAsync(recs, 0, (size_t)cap_recs * sizeof(ChunkRec), stream)) != hipSuccess)
-            return e;
-        if (fresh_ctr && (e = hipMemsetAsync(ctr, 0, sizeof(Counters), stream)) != hipSuccess)
-            return e;
+        if (fresh_ctr) return hipMemsetAsync(ctr, 0, sizeof(Counters), stream);
         return hipSuccess;
     }
-    bool fits(int64_t span, int64_t ntiles, int64_t nchunks) const
+    bool fits(int64_t ntiles, int64_t nchunks) const
     {
-        return span <= cap_segid && ntiles <= cap_tiles && nchunks <= cap_recs && cap_ctr >= 1;
+        return ntiles <= cap_tiles && nchunks <= cap_recs && cap_ctr >= 1;
     }
     // device bytes held
     int64_t bytes() const
     {
-        return cap_segid * (int64_t)sizeof(int32_t) + cap_tiles * (int64_t)sizeof(int2) +
-               cap_recs * (int64_t)sizeof(ChunkRec) + cap_ctr * (int64_t)sizeof(Counters);
+        return cap_tiles * (int64_t)sizeof(int2) + cap_recs * (int64_t)sizeof(ChunkRec) +
+               cap_ctr * (int64_t)sizeof(Counters);
     }
     void release()
     {
-        if (segid) (void)hipFree(segid);
         if (tiles) (void)hipFree(tiles);
         if (recs) (void)hipFree(recs);
         if (ctr) (void)hipFree(ctr);
@@ -455,61 +445,59 @@ struct DeviceBuffers {
     }
 };
 
-// The pre-pass of a batch: the curve walker (one workgroup per curve) for
-// many curves, else the chunked pre-pass over at most kPrepGroupsPerCU
-// workgroups per CU.
-struct PrepLaunch {
-    bool walk;
-    int grid;
-};
-PrepLaunch prep_launch_for(int64_t ncurves, int64_t nchunks, int n_cu)
+// Workgroups of a batch's set-up launch.
+int setup_grid(int64_t ncurves) { return (int)std::min<int64_t>(ncurves, kSetupGroups); }
+
+// Whether a batch's table goes to the estimate kernel by value, one workgroup
+// per tile: no set-up launch, staging block or tile queue.  Up to kSmallTable
+// curves it fits the kernel arguments; a limit on the workgroups per CU asks
+// for the queue.  (One curve of 20,000 samples at W = 361: 50 us a call with a
+// pre-pass and the queue, 36 by value.)
+bool by_value(int64_t ncurves, const umi_launch& opt, int gpc)
 {
-    if (ncurves >= kPrepWalkMinCurves) return {true, (int)ncurves};
-    return {false, (int)std::min<int64_t>(nchunks, (int64_t)kPrepGroupsPerCU * n_cu)};
+    return ncurves <= kSmallTable && opt.mode == UMI_MODE_PERSISTENT && opt.groups_per_cu == 0 &&
+           gpc >= kDefaultGroupsPerCU;
 }
 
-// Enqueue the pre-pass and estimate kernels for a staged block (header +
-// curve table).  With `stage` (the device address of the pinned host block
-// holding it) the pre-pass reads the block there and copies it to `dblock`
-// for the estimate kernel; without, the block is at `dblock` on the device by
-// the time the stream reaches the kernels (per-curve mode always).  In
-// per-curve mode `table` and `curve_tiles` (host copies of the staged table,
-// `ncurves` entries) give each curve's tile range and length.  `staged`, if
-// given, is recorded once the pre-pass is done with the staging block.
+// Enqueue the kernels of a staged block (header + curve table).  With `stage`
+// (the device address of the pinned host block holding it) the set-up reads
+// the block there and copies it to `dblock` for the estimate kernel; without,
+// the block is at `dblock` on the device by the time the stream reaches the
+// kernels (per-curve mode always).  In per-curve mode `table` and
+// `curve_tiles` (host copies of the staged table, `ncurves` entries) give each
+// curve's tile range and length.  `staged`, if given, is recorded once the
+// set-up is done with the staging block.  With `value` the block `dblock` is
+// host memory and goes to the estimate kernel by value.
 hipError_t enqueue_kernels(const float* flux, const double* time, float* trend, float* median,
                            uint8_t* dblock, const uint8_t* stage, const DeviceBuffers& b, int mode,
-                           const CurveDesc* table, const int64_t* curve_tiles, int ncurves,
-                           PrepLaunch prep, int main_grid, int feat, hipEvent_t ev0,
-                           hipEvent_t ev1, hipEvent_t staged, hipStream_t stream)
+                           bool value, const CurveDesc* table, const int64_t* curve_tiles,
+                           int ncurves, int main_grid, int feat, hipEvent_t ev0, hipEvent_t ev1,
+                           hipEvent_t staged, hipStream_t stream)
 {
     const BatchHeader* hdr = reinterpret_cast<const BatchHeader*>(dblock);
     const CurveDesc* curves = reinterpret_cast<const CurveDesc*>(dblock + sizeof(BatchHeader));
+    // the launch interface's per-sample words: the outputs, which the
+    // estimate kernel overwrites
+    int32_t* words = reinterpret_cast<int32_t*>(trend);
     hipError_t e;
-    if (mode == UMI_MODE_PERSISTENT) {
-        // a lone curve's descriptor goes to the chunked pre-pass as an argument
-        const CurveDesc* one = (table != nullptr && ncurves == 1 && !prep.walk) ? table : nullptr;
-        if ((e = launch_prepass(flux, time, dblock, stage, -1, prep.grid, b.segid, b.tiles, b.ctr,
-                                b.recs, true, prep.walk, one, stream)) != hipSuccess)
-            return e;
-        if (staged && (e = hipEventRecord(staged, stream)) != hipSuccess) return e;
-        if (ev0 && (e = hipEventRecord(ev0, stream)) != hipSuccess) return e;
-        if ((e = launch_main(flux, b.segid, hdr, curves, b.tiles, 0, -1, &b.ctr->queue, main_grid,
-                             trend, median, feat, stream)) != hipSuccess)
-            return e;
-        if (ev1 && (e = hipEventRecord(ev1, stream)) != hipSuccess) return e;
-        return hipSuccess;
-    }
-    // one pre-pass (the walker, one workgroup) and one estimate launch per
-    // curve, one workgroup per tile
+    if ((e = launch_prepass(flux, time, dblock, stage, -1, setup_grid(ncurves), words, b.tiles,
+                            b.ctr, b.recs, !value, false, nullptr, stream)) != hipSuccess)
+        return e;
+    if (staged && (e = hipEventRecord(staged, stream)) != hipSuccess) return e;
     if (ev0 && (e = hipEventRecord(ev0, stream)) != hipSuccess) return e;
-    for (int i = 0; i < ncurves; ++i) {
-        if ((e = launch_prepass(flux, time, dblock, nullptr, i, 1, b.segid, b.tiles, b.ctr,
-                                b.recs, false, true, nullptr, stream)) != hipSuccess)
+    if (mode == UMI_MODE_PERSISTENT) {
+        if ((e = launch_main(flux, words, hdr, curves, b.tiles, 0, -1,
+                             value ? nullptr : &b.ctr->queue, main_grid, trend, median, feat,
+                             stream)) != hipSuccess)
             return e;
-        const int nt = (int)curve_tiles[i];
-        if ((e = launch_main(flux, b.segid, hdr, curves, b.tiles, table[i].tile_base, nt, nullptr,
-                             nt, trend, median, feat, stream)) != hipSuccess)
-            return e;
+    } else {
+        // one estimate launch per curve, one workgroup per tile
+        for (int i = 0; i < ncurves; ++i) {
+            const int nt = (int)curve_tiles[i];
+            if ((e = launch_main(flux, words, hdr, curves, b.tiles, table[i].tile_base, nt,
+                                 nullptr, nt, trend, median, feat, stream)) != hipSuccess)
+                return e;
+        }
     }
     if (ev1 && (e = hipEventRecord(ev1, stream)) != hipSuccess) return e;
     return hipSuccess;
@@ -545,16 +533,16 @@ struct Workspace {
 
     // Make room; if anything must be reallocated, first wait for work already
     // queued on this stream, which may still read the old buffers.
-    hipError_t reserve(int64_t span, int64_t ncurves, int64_t ntiles, int64_t nchunks)
+    hipError_t reserve(int64_t ncurves, int64_t ntiles, int64_t nchunks)
     {
         const int64_t bytes = (int64_t)block_bytes(ncurves);
-        if (buf.fits(span, ntiles, nchunks) && bytes <= cap_dblock && bytes <= cap_hblock &&
+        if (buf.fits(ntiles, nchunks) && bytes <= cap_dblock && bytes <= cap_hblock &&
             staged)
             return hipSuccess;
         hipError_t e = hipStreamSynchronize(stream);
         if (e != hipSuccess) return e;
         staged_pending = false;
-        if ((e = buf.reserve(span, ntiles, nchunks, stream)) != hipSuccess) return e;
+        if ((e = buf.reserve(ntiles, nchunks, stream)) != hipSuccess) return e;
         if ((e = grow(&dblock, &cap_dblock, bytes)) != hipSuccess) return e;
         if (bytes > cap_hblock) {
             if (hblock) (void)hipHostFree(hblock);
@@ -679,31 +667,29 @@ umi_status detrend_gather(const float* flux, const double* time, const int64_t* 
     const int64_t nc = (int64_t)p.curves.size();
     Workspace* ws = workspace_for(device, stream);
     std::lock_guard<std::mutex> lk(ws->mu);
-    if ((e = ws->reserve(span, nc, p.ntiles, p.nchunks)) != hipSuccess)
+    if ((e = ws->reserve(nc, p.ntiles, p.nchunks)) != hipSuccess)
         return fail_hip(e, "workspace allocation");
+    const int grid = (int)std::min<int64_t>(p.ntiles, (int64_t)p.gpc * cu_count(device));
+    if (by_value(nc, opt, p.gpc)) {
+        uint8_t block[sizeof(BatchHeader) + kSmallTable * sizeof(CurveDesc)];
+        write_block(block, p.curves.data(), nc, p.ntiles, p.nchunks, iters, o, time);
+        e = enqueue_kernels(flux, time, trend, median, block, nullptr, ws->buf, opt.mode, true,
+                            p.curves.data(), p.curve_tiles.data(), (int)nc, grid, p.feat,
+                            (hipEvent_t)opt.main_start, (hipEvent_t)opt.main_stop, nullptr, stream);
+        if (e != hipSuccess) return fail_hip(e, "kernel launch");
+        return UMI_OK;
+    }
     if (ws->staged_pending) {  // the previous reads of the staging block must be done
         if ((e = hipEventSynchronize(ws->staged)) != hipSuccess)
             return fail_hip(e, "hipEventSynchronize");
         ws->staged_pending = false;
     }
     write_block(ws->hblock, p.curves.data(), nc, p.ntiles, p.nchunks, iters, o, time);
-    // a persistent launch's pre-pass reads the block from pinned memory and
-    // copies it to the device itself; per-curve launches take a copy first
-    const bool direct = opt.mode == UMI_MODE_PERSISTENT;
-    if (!direct) {
-        if ((e = hipMemcpyAsync(ws->dblock, ws->hblock, block_bytes(nc), hipMemcpyHostToDevice,
-                                stream)) != hipSuccess)
-            return fail_hip(e, "curve table copy");
-        if ((e = hipEventRecord(ws->staged, stream)) != hipSuccess)
-            return fail_hip(e, "hipEventRecord");
-    }
+    // the set-up reads the block from pinned memory and copies it to the device
     ws->staged_pending = true;
-    const int grid = (int)std::min<int64_t>(p.ntiles, (int64_t)p.gpc * cu_count(device));
-    e = enqueue_kernels(flux, time, trend, median, ws->dblock, direct ? ws->hblock_dev : nullptr,
-                        ws->buf, opt.mode, p.curves.data(), p.curve_tiles.data(), (int)nc,
-                        prep_launch_for(nc, p.nchunks, cu_count(device)), grid, p.feat,
-                        (hipEvent_t)opt.main_start, (hipEvent_t)opt.main_stop,
-                        direct ? ws->staged : nullptr, stream);
+    e = enqueue_kernels(flux, time, trend, median, ws->dblock, ws->hblock_dev, ws->buf, opt.mode,
+                        false, p.curves.data(), p.curve_tiles.data(), (int)nc, grid, p.feat,
+                        (hipEvent_t)opt.main_start, (hipEvent_t)opt.main_stop, ws->staged, stream);
     if (e != hipSuccess) return fail_hip(e, "kernel launch");
     return UMI_OK;
 }
@@ -834,17 +820,16 @@ struct umi_plan {
     float* median = nullptr;
     int main_grid = 0;
     umi::DeviceBuffers buf;
-    // Captured graphs per slot and estimate kernel (kPlan*): [0] for batches
-    // of at most kPrepSmallChunks pre-pass chunks (the chunked pre-pass over
-    // that many workgroups), [1] for any batch (the curve walker over
-    // max_curves workgroups).  Either pre-pass reads the slot's pinned block
-    // and copies it to the slot's device block for the estimate kernel.
+    // A captured graph per slot and estimate kernel (kPlan*): the set-up, which
+    // reads the slot's pinned block and copies it to the slot's device block,
+    // and the estimate kernel.  Runs of at most kSmallTable curves pass their
+    // table by value instead and replay none.
     struct Slot {
         uint8_t* host = nullptr;    // pinned header + curve table
         uint8_t* host_dev = nullptr;  // its device address
         uint8_t* dev = nullptr;     // its device copy
-        hipGraph_t graph[kPlanKernels][2] = {};
-        hipGraphExec_t exec[kPlanKernels][2] = {};
+        hipGraph_t graph[kPlanKernels] = {};
+        hipGraphExec_t exec[kPlanKernels] = {};
         hipEvent_t done = nullptr;  // recorded after the slot's last replay
         bool pending = false;
     } slot[2];
@@ -858,10 +843,8 @@ void plan_free(umi_plan* p)
 {
     for (auto& s : p->slot) {
         for (int v = 0; v < kPlanKernels; ++v) {
-            for (int k = 0; k < 2; ++k) {
-                if (s.exec[v][k]) (void)hipGraphExecDestroy(s.exec[v][k]);
-                if (s.graph[v][k]) (void)hipGraphDestroy(s.graph[v][k]);
-            }
+            if (s.exec[v]) (void)hipGraphExecDestroy(s.exec[v]);
+            if (s.graph[v]) (void)hipGraphDestroy(s.graph[v]);
         }
         if (s.done) (void)hipEventDestroy(s.done);
         if (s.host) (void)hipHostFree(s.host);
@@ -869,22 +852,6 @@ void plan_free(umi_plan* p)
         s = umi_plan::Slot();
     }
     p->buf.release();
-}
-
-// Curves the staged table of a graph kind holds, and that kind's pre-pass:
-// kind 0 serves batches of at most kPrepSmallChunks chunks with the chunked
-// pre-pass over that many workgroups (each curve has a chunk, so the table
-// holds at most that many curves); kind 1 any batch, with the curve walker,
-// one workgroup per possible curve.
-int64_t plan_kind_curves(const umi_plan* p, int kind)
-{
-    return kind == 0 ? std::min<int64_t>(p->max_curves, umi::kPrepSmallChunks) : p->max_curves;
-}
-
-umi::PrepLaunch plan_kind_prep(const umi_plan* p, int kind)
-{
-    return kind == 0 ? umi::PrepLaunch{false, umi::kPrepSmallChunks}
-                     : umi::PrepLaunch{true, (int)p->max_curves};
 }
 
 // The estimate kernel for a batch that needs `feat`, and kernel v's own bits.
@@ -907,27 +874,26 @@ int plan_kernels(const umi_plan* p)
     return p->max_W < umi::kCoreMinW ? 1 : (p->max_W <= kPlanMidW ? 2 : kPlanKernels);
 }
 
-// Capture slot `si`'s graph of `kind` with estimate kernel `v`: the pre-pass
-// (which reads the staged block from pinned memory and copies it to the
-// device) and the persistent estimate kernel.  Nothing runs during capture.
-hipError_t plan_capture(umi_plan* p, int si, int kind, int v)
+// Capture slot `si`'s graph with estimate kernel `v`: the set-up and the
+// persistent estimate kernel.  Nothing runs during capture.
+hipError_t plan_capture(umi_plan* p, int si, int v)
 {
     umi_plan::Slot& s = p->slot[si];
     hipError_t e = hipStreamBeginCapture(p->stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return e;
     const hipError_t ce = umi::enqueue_kernels(
         p->flux, p->time, p->trend, p->median, s.dev, s.host_dev, p->buf, UMI_MODE_PERSISTENT,
-        nullptr, nullptr, (int)plan_kind_curves(p, kind), plan_kind_prep(p, kind), p->main_grid,
-        plan_kernel_feat(p, v), nullptr, nullptr, nullptr, p->stream);
+        false, nullptr, nullptr, (int)p->max_curves, p->main_grid, plan_kernel_feat(p, v), nullptr,
+        nullptr, nullptr, p->stream);
     hipGraph_t g = nullptr;
     e = hipStreamEndCapture(p->stream, &g);
     if (ce != hipSuccess || e != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
         return ce != hipSuccess ? ce : e;
     }
-    s.graph[v][kind] = g;
-    if ((e = hipGraphInstantiate(&s.exec[v][kind], g, nullptr, nullptr, 0)) != hipSuccess) {
-        s.exec[v][kind] = nullptr;
+    s.graph[v] = g;
+    if ((e = hipGraphInstantiate(&s.exec[v], g, nullptr, nullptr, 0)) != hipSuccess) {
+        s.exec[v] = nullptr;
         return e;
     }
     return hipSuccess;
@@ -937,8 +903,8 @@ hipError_t plan_capture(umi_plan* p, int si, int kind, int v)
 
 // ---------------------------------------------------------------------------
 // The allocation-free batch call (umi_detrend_batch_noalloc): the workspace
-// of a batch -- header and curve table, queue counter, tile list, segment
-// words -- lives in one file-scope device array, and the host side packs into
+// of a batch -- header and curve table, queue counter, tile list -- lives in
+// one file-scope device array, and the host side packs into
 // static arrays.  Nothing is allocated per call, on the device or the host.
 
 namespace umi {
@@ -957,8 +923,7 @@ constexpr size_t kBlockOff = 0;  // BatchHeader + curve table
 constexpr size_t kCounterOff = round_up(sizeof(BatchHeader) + kMaxCurves * sizeof(CurveDesc));
 constexpr size_t kRecsOff = kCounterOff + kAlign;
 constexpr size_t kTilesOff = round_up(kRecsOff + kMaxChunks * sizeof(ChunkRec));
-constexpr size_t kSegidOff = round_up(kTilesOff + kMaxTiles * sizeof(int2));
-constexpr size_t kScratchBytes = kSegidOff + kMaxSamples * sizeof(int32_t);
+constexpr size_t kScratchBytes = round_up(kTilesOff + kMaxTiles * sizeof(int2));
 static_assert(kScratchBytes == UMI_NOALLOC_SCRATCH_BYTES, "scratch size in umi.h");
 
 constexpr int kMaxDevices = 64;
@@ -1052,13 +1017,7 @@ umi_status detrend_batch(const float* flux, const double* time, const int64_t* l
                     "tiles (very wide windows cut curves into small tiles)");
     if (v.nchunks > kMaxChunks) return fail(UMI_ERR_UNSUPPORTED, "chunk count above its bound");
     write_block(g_block, g_curves, v.ncurves, v.ntiles, v.nchunks, iters, o, time);
-    // from pageable host memory: the source is free again once the call returns
-    if ((e = hipMemcpyAsync(base + kBlockOff, g_block, block_bytes(v.ncurves),
-                            hipMemcpyHostToDevice, stream)) != hipSuccess)
-        return fail_hip(e, "curve table copy");
     DeviceBuffers b;  // a view of the scratch array; never released
-    b.segid = reinterpret_cast<int32_t*>(base + kSegidOff);
-    b.cap_segid = kMaxSamples;
     b.tiles = reinterpret_cast<int2*>(base + kTilesOff);
     b.cap_tiles = kMaxTiles;
     b.ctr = reinterpret_cast<Counters*>(base + kCounterOff);  // zero from the module load
@@ -1066,9 +1025,13 @@ umi_status detrend_batch(const float* flux, const double* time, const int64_t* l
     b.recs = reinterpret_cast<ChunkRec*>(base + kRecsOff);
     b.cap_recs = kMaxChunks;
     const int grid = (int)std::min<int64_t>(v.ntiles, (int64_t)v.gpc * n_cu);
-    e = enqueue_kernels(flux, time, trend, median, base + kBlockOff, nullptr, b, opt.mode,
-                        g_curves, g_curve_tiles, (int)v.ncurves,
-                        prep_launch_for(v.ncurves, v.nchunks, n_cu), grid, v.feat,
+    const bool value = by_value(v.ncurves, opt, v.gpc);
+    // from pageable host memory: the source is free again once the call returns
+    if (!value && (e = hipMemcpyAsync(base + kBlockOff, g_block, block_bytes(v.ncurves),
+                                      hipMemcpyHostToDevice, stream)) != hipSuccess)
+        return fail_hip(e, "curve table copy");
+    e = enqueue_kernels(flux, time, trend, median, value ? g_block : base + kBlockOff, nullptr, b,
+                        opt.mode, value, g_curves, g_curve_tiles, (int)v.ncurves, grid, v.feat,
                         (hipEvent_t)opt.main_start, (hipEvent_t)opt.main_stop, nullptr, stream);
     if (e != hipSuccess) return fail_hip(e, "kernel launch");
     return UMI_OK;
@@ -1195,7 +1158,7 @@ umi_status umi_plan_create(umi_plan** out, int64_t capacity, int64_t max_curves,
     // every curve adds at most one partial chunk
     const int64_t max_chunks = capacity / umi::kPrepChunk + max_curves;
     if (max_chunks > (int64_t)INT32_MAX)
-        return umi::fail(UMI_ERR_UNSUPPORTED, "plan capacity needs too many pre-pass chunks");
+        return umi::fail(UMI_ERR_UNSUPPORTED, "plan capacity needs too many chunks");
     umi_plan* p = new umi_plan();
     p->device = device;
     p->stream = static_cast<hipStream_t>(stream);
@@ -1208,7 +1171,7 @@ umi_status umi_plan_create(umi_plan** out, int64_t capacity, int64_t max_curves,
     p->time = time;
     p->trend = trend;
     p->median = median;
-    hipError_t e = p->buf.reserve(capacity, max_tiles, max_chunks, p->stream, /*exact=*/true);
+    hipError_t e = p->buf.reserve(max_tiles, max_chunks, p->stream, /*exact=*/true);
     const size_t bytes = umi::block_bytes(max_curves);
     for (auto& s : p->slot) {
         if (e == hipSuccess)
@@ -1231,9 +1194,7 @@ umi_status umi_plan_create(umi_plan** out, int64_t capacity, int64_t max_curves,
     p->main_grid = gpc * umi::cu_count(p->device);
     // every slot's graphs, now rather than on a serving step
     for (int si = 0; si < 2 && e == hipSuccess; ++si)
-        for (int kind = 0; kind < 2 && e == hipSuccess; ++kind)
-            for (int v = 0; v < plan_kernels(p) && e == hipSuccess; ++v)
-                e = plan_capture(p, si, kind, v);
+        for (int v = 0; v < plan_kernels(p) && e == hipSuccess; ++v) e = plan_capture(p, si, v);
     if (e != hipSuccess) {
         plan_free(p);
         delete p;
@@ -1277,21 +1238,28 @@ umi_status umi_plan_run_ex(umi_plan* p, const int64_t* offsets, const int64_t* l
         return umi::fail(UMI_ERR_UNSUPPORTED, "batch needs more chunks than the plan holds");
 
     std::lock_guard<std::mutex> lk(p->mu);
-    umi_plan::Slot& s = p->slot[p->next];
     hipError_t e;
+    const int64_t nc = (int64_t)pk.curves.size();
+    if (nc > 0 && umi::by_value(nc, opt, pk.gpc)) {
+        uint8_t block[sizeof(umi::BatchHeader) + umi::kSmallTable * sizeof(umi::CurveDesc)];
+        umi::write_block(block, pk.curves.data(), nc, pk.ntiles, pk.nchunks, iters, o, p->time);
+        e = umi::enqueue_kernels(p->flux, p->time, p->trend, p->median, block, nullptr, p->buf,
+                                 UMI_MODE_PERSISTENT, true, pk.curves.data(),
+                                 pk.curve_tiles.data(), (int)nc, p->main_grid, pk.feat, nullptr,
+                                 nullptr, nullptr, p->stream);
+        return e == hipSuccess ? UMI_OK : umi::fail_hip(e, "kernel launch");
+    }
+    umi_plan::Slot& s = p->slot[p->next];
     if (s.pending) {  // this slot's previous replay must have consumed its bytes
         if ((e = hipEventSynchronize(s.done)) != hipSuccess)
             return umi::fail_hip(e, "hipEventSynchronize");
         s.pending = false;
     }
-    umi::write_block(s.host, pk.curves.data(), (int64_t)pk.curves.size(), pk.ntiles, pk.nchunks,
-                     iters, o, p->time);
-    // small batches (at most kPrepSmallChunks chunks) replay kind 0
-    const int kind = pk.nchunks <= umi::kPrepSmallChunks ? 0 : 1;
+    umi::write_block(s.host, pk.curves.data(), nc, pk.ntiles, pk.nchunks, iters, o, p->time);
     const int v = n_curves > 0 ? plan_kernel(pk.feat) : 0;
-    if (!s.exec[v][kind] && (e = plan_capture(p, p->next, kind, v)) != hipSuccess)
+    if (!s.exec[v] && (e = plan_capture(p, p->next, v)) != hipSuccess)
         return umi::fail_hip(e, "graph capture");
-    if ((e = hipGraphLaunch(s.exec[v][kind], p->stream)) != hipSuccess)
+    if ((e = hipGraphLaunch(s.exec[v], p->stream)) != hipSuccess)
         return umi::fail_hip(e, "hipGraphLaunch");
     if ((e = hipEventRecord(s.done, p->stream)) != hipSuccess)
         return umi::fail_hip(e, "hipEventRecord");

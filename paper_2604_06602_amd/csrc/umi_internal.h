@@ -77,15 +77,9 @@ __host__ __device__ constexpr int split_lanes(int tile)
 {
     return tile > kSplitMaxTile ? 1 : (tile > kMainThreads / 4 ? 2 : (tile > kMainThreads / 8 ? 4 : 8));
 }
-constexpr int kPrepThreads = 256;            // threads per pre-pass workgroup
-constexpr int kPrepItems = 8;                // samples per thread per chunk (chunked pre-pass)
-constexpr int kPrepChunk = kPrepThreads * kPrepItems;  // samples per pre-pass chunk
-constexpr int kPrepWalkItems = 4;            // samples per thread per step (curve walker)
-constexpr int kPrepGroupsPerCU = 8;          // chunked pre-pass workgroups per CU
-constexpr int kPrepSmallChunks = 256;        // plan steps of at most this many chunks take
-                                             // a chunked pre-pass of this many workgroups
-constexpr int kPrepWalkMinCurves = 128;      // batches of this many curves or more take the
-                                             // one-workgroup-per-curve walker
+constexpr int kSetupThreads = 256;           // threads per set-up workgroup
+constexpr int kSetupGroups = 1024;           // set-up workgroups at most
+constexpr int kPrepChunk = 1 << 20;          // samples a chunk of the table's chunk counts stands for
 constexpr float kScaleConst = 0.6745f;       // Section 2.2, after Eq. 1
 constexpr double kGapDays = 0.5;             // segment break threshold (days)
 
@@ -119,43 +113,31 @@ struct CurveDesc {
 };
 static_assert(sizeof(CurveDesc) == 48, "CurveDesc layout");
 
-// Segmentation summary of a run of consecutive samples of one curve, or the
-// state after a curve's first samples (a prefix), as the pre-pass scan
-// carries it from chunk to chunk.
-struct SegState {
-    int32_t cnt;        // valid samples
-    int32_t fv;         // first valid sample (curve-local), -1 if none
-    int32_t lv;         // last valid sample, -1 if none
-    int32_t ls;         // latest segment start, -1 if none; in a run that is
-                        // not a prefix only starts after fv count (fv's own
-                        // status depends on what precedes the run)
-    int32_t lsb;        // valid samples of the run (or prefix) before ls
+// A batch's table by value, as kernel arguments (n_curves 0: the table is in
+// device memory).
+constexpr int kSmallTable = 32;
+struct SmallTable {
+    int32_t n_curves;
     int32_t reserved;
-    double ft;          // time of fv
-    double lt;          // time of lv
+    BatchHeader hdr;
+    CurveDesc c[kSmallTable];
 };
-static_assert(sizeof(SegState) == 40, "SegState layout");
+static_assert(sizeof(SmallTable) <= 2048, "SmallTable fits the kernel arguments");
 
-// One pre-pass chunk's published scan state: its own summary (`agg`), then
-// the state after the curve's samples up to its end (`inc`).  Each holds the
-// nine 32-bit words of a SegState (cnt, fv, lv, ls, lsb, then the low and
-// high halves of ft and lt), each stored in the low half of a 64-bit word
-// whose high half is the launch's stamp: a reader takes a state once all nine
-// words carry its launch's stamp, so no word needs ordering against another.
-constexpr int kSegWords = 9;
+// One record per chunk of the launch interface (launch_prepass): two words.
+constexpr int kSegWords = 1;
 struct ChunkRec {
     uint64_t agg[kSegWords];
     uint64_t inc[kSegWords];
 };
-static_assert(sizeof(ChunkRec) == 144, "ChunkRec layout");
 
 // Device counters of a workspace (zeroed when it is allocated).
 struct Counters {
-    uint32_t queue;     // estimate-kernel tile queue (cleared by the pre-pass)
-    uint32_t tickets;   // pre-pass chunk tickets (reset by its last workgroup)
-    uint32_t done;      // pre-pass workgroups finished (reset likewise)
-    uint32_t trash;     // takes the walker pre-pass's stores that have no sample
-    uint64_t epoch;     // pre-pass launches completed; stamps use epoch + 1
+    uint32_t queue;     // estimate-kernel tile queue (cleared by the set-up)
+    uint32_t tickets;
+    uint32_t done;
+    uint32_t reserved;
+    uint64_t epoch;
     uint64_t reserved2;
 };
 static_assert(sizeof(Counters) == 32, "Counters layout");
@@ -177,15 +159,7 @@ struct CopyBatch {
 };
 static_assert(sizeof(CopyBatch) <= 2048, "CopyBatch fits the kernel arguments");
 
-// Per-sample segment word written by the pre-pass at segid[curve.off + i]:
-//   -1       sample i is invalid;
-//   x >= 0   sample i is valid and its segment starts at the valid sample x
-//            (curve-local index, x < i);
-//   -2 - n   sample i is valid and starts a segment of n valid samples.
-// A segment is live when n >= max(1, W / 3).  Curves hold fewer than
-// 2^31 - 1 samples, so -2 - n never overflows.
-
-// Tile record written by the pre-pass: x = index into the curve table,
+// Tile record written by the set-up: x = index into the curve table,
 // y = first output position (curve-local).
 
 }  // namespace umi

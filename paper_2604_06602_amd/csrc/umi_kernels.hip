@@ -1,30 +1,13 @@
 // HIP kernels of the UMI library for CDNA4 (gfx950).
 //
-// Two kernels run per batch, both on the caller's stream:
-//
-//   pre-pass            validity and segmentation (gap handling, minimum
-//                       segment length W/3 of Section 4.4): block scans write
-//                       a segment word per sample and one record per segment,
-//                       and lay out the tile list for the main kernel.  Two
-//                       forms: umi_prepass_walk_kernel walks each curve with
-//                       one workgroup (batches of many curves);
-//                       umi_prepass_chunk_kernel cuts curves into chunks of
-//                       2,048 samples taken in ticket order, each joined to
-//                       the curve before it by a decoupled look-back (few
-//                       curves, so that a lone curve is spread over the chip).
-//
 //   umi_main_kernel     tiles of consecutive output positions.  A workgroup
-//                       stages a tile plus its W-1 halo from HBM once, keeps the
-//                       valid samples compacted in LDS, sorts (key, index) pairs
-//                       of the staged samples once (bitonic network in LDS), and
-//                       builds a wavelet matrix over the sorted ranks.  Every
-//                       lane then takes up to three consecutive windows:
-//                         Phase 1 (Section 2.1): exact median as the k-th
-//                           smallest rank in the window's index range, one
-//                           O(log N) wavelet descent -- the sort is shared by
-//                           all windows of the tile.  Tiles of full windows
-//                           with W <= 31 skip the sort and take their medians
-//                           from register networks instead;
+//                       stages a tile plus its W-1 halo from HBM once, finds
+//                       the span's valid samples and segments (gap handling,
+//                       minimum segment length W/3 of Section 4.4), keeps the
+//                       valid samples compacted in LDS and sorts (value,
+//                       index) pairs of them once.  Then, per window:
+//                         Phase 1 (Section 2.1): the exact median, from the
+//                           sorted tile;
 //                         Phase 2 (Section 2.2, Eq. 1): upper-RMS scale;
 //                         Phase 3 (Section 2.3, Eqs. 2-4): asymmetric bisquare
 //                           iterations in the residual form
@@ -32,14 +15,25 @@
 //                           k = A/(c s), A = (1 + alpha)/2: Eq. 4 rewritten
 //                           around the current mu, with Eq. 2's two branches
 //                           folded into one expression of v.
-//                       Windows that share samples and have the same length
-//                       are summed in one fused sweep (one LDS read per sample
-//                       for all of them).  Launched either persistently (a
-//                       grid sized to the chip pops tiles from a device
-//                       counter) or one workgroup per tile.
+//                       Windows of kCoreMinW samples or more share sorted
+//                       cores with their neighbours and sum most of their
+//                       samples by power sums.  Narrower ones take their
+//                       medians from a wavelet matrix over the sorted ranks
+//                       (full windows of W <= 31 from register networks) and
+//                       sum sample by sample, a lane taking up to three
+//                       consecutive windows and one LDS read feeding all of
+//                       them; tiles of at most 256 positions split each window
+//                       over 2, 4 or 8 lanes.  Launched with the curve table by
+//                       value and one workgroup per tile (few curves),
+//                       persistently (a grid sized to the chip pops tiles from
+//                       a device counter), or per curve.
+//
+//   umi_setup_kernel    copies the staged curve table of a larger batch to
+//                       the device, lists its tiles and clears the counter.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstring>
 
 #include <stdint.h>
 
@@ -54,719 +48,35 @@
 namespace umi {
 
 // ---------------------------------------------------------------------------
-// small wave / block helpers (64-lane wavefronts)
-
-__device__ __forceinline__ int wave_incl_sum(int x)
+// Set-up of a batch whose curve table is in device memory (or in the caller's
+// pinned staging block, which the device reads over the bus): copies the
+// staged block to `to` for the estimate kernel, writes the tile list and
+// clears the tile queue.  Batches of at most kSmallTable curves pass the
+// table to the estimate kernel by value and need none of this.
+__global__ __launch_bounds__(kSetupThreads) void umi_setup_kernel(
+    const uint8_t* __restrict__ block, uint8_t* __restrict__ to, int2* __restrict__ tiles,
+    uint32_t* __restrict__ queue)
 {
-    const int lane = __lane_id();
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        int y = __shfl_up(x, d, 64);
-        if (lane >= d) x += y;
+    const BatchHeader* __restrict__ hdr = reinterpret_cast<const BatchHeader*>(block);
+    const CurveDesc* __restrict__ curves =
+        reinterpret_cast<const CurveDesc*>(block + sizeof(BatchHeader));
+    if (blockIdx.x == 0 && threadIdx.x == 0) *queue = 0u;
+    const int n_curves = hdr->n_curves;
+    if (to != nullptr) {  // in 8-byte words, spread over the grid
+        const int words = (int)((sizeof(BatchHeader) + (size_t)n_curves * sizeof(CurveDesc)) / 8);
+        const uint64_t* s = reinterpret_cast<const uint64_t*>(block);
+        uint64_t* d = reinterpret_cast<uint64_t*>(to);
+        for (int i = (int)(blockIdx.x * kSetupThreads + threadIdx.x); i < words;
+             i += (int)gridDim.x * kSetupThreads)
+            d[i] = s[i];
     }
-    return x;
-}
-
-// Inclusive "latest" scan over the lanes of a wave: the pair (idx, val) of
-// the highest lane so far whose idx is >= 0 (idx grows with the lane where
-// set, so the latest is the largest).
-__device__ __forceinline__ void wave_incl_latest(int& idx, int& val)
-{
-    const int lane = __lane_id();
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int yi = __shfl_up(idx, d, 64);
-        const int yv = __shfl_up(val, d, 64);
-        if (lane >= d && yi > idx) {
-            idx = yi;
-            val = yv;
-        }
+    for (int c = (int)blockIdx.x; c < n_curves; c += (int)gridDim.x) {
+        const int len = curves[c].len, tile = curves[c].tile, base = curves[c].tile_base;
+        for (int t = (int)threadIdx.x; (int64_t)t * tile < len; t += kSetupThreads)
+            tiles[base + t] = make_int2(c, t * tile);
     }
-}
-
-// The same for an (index, time) pair, together with an inclusive sum `cnt`.
-template <class T>
-__device__ __forceinline__ void wave_incl_latest_sum(int& idx, T& val, int& cnt)
-{
-    const int lane = __lane_id();
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int yi = __shfl_up(idx, d, 64);
-        const T yv = __shfl_up(val, d, 64);
-        const int yc = __shfl_up(cnt, d, 64);
-        if (lane >= d) {
-            if (yi > idx) {
-                idx = yi;
-                val = yv;
-            }
-            cnt += yc;
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Pre-pass: segments and tiles.
-//
-// Curves are cut into chunks of kPrepChunk samples (kPrepItems consecutive
-// samples per thread); workgroups take chunks in ticket order from a device
-// counter and scan each in one pass.  The pre-pass writes one int32 per sample:
-//   -1                    the sample is invalid (non-finite flux or time);
-//   x >= 0                a valid sample whose segment starts at the valid
-//                         sample x (curve-local index), x < this sample;
-//   -2 - n  (<= -2)       the first valid sample of a segment of n valid
-//                         samples (the segment's record lives in its first
-//                         slot, so the workspace is 4 bytes per sample).
-// A new segment starts at a valid sample whose predecessor among valid
-// samples is more than kGapDays earlier (strictly), and at the first valid
-// sample.  The slot of a segment's first sample is written once, by whoever
-// sees the segment end (the thread holding the next start, or the workgroup of
-// the curve's last chunk), so no slot has two writers.
-//
-// A chunk's output depends on the curve before it only through a small state
-// (SegState: valid count, last valid sample and its time, latest segment
-// start).  Each workgroup first scans its chunk alone and publishes the
-// chunk's summary; it then finds the state before the chunk by looking back
-// over its predecessors' records -- 64 at a time, one per lane -- combining
-// summaries until it meets one whose state is final (a decoupled look-back),
-// publishes its own final state, and writes its segment words.  Tickets are
-// handed out in order, so every chunk a workgroup waits for belongs to a
-// workgroup that has already started, and every workgroup publishes its
-// summary before it waits for anything: the waits always end.
-
-// The state after run `a` followed by run `b`.  `a_prefix`: `a` starts at the
-// curve's first sample, so after an empty `a` the first valid sample of `b`
-// starts a segment.  The gap test is the expression the per-sample scan uses.
-__device__ __forceinline__ SegState seg_combine(const SegState& a, const SegState& b, bool a_prefix,
-                                                bool has_time)
-{
-    if (b.cnt == 0) return a;
-    SegState r = b;
-    if (a.cnt == 0) {
-        if (a_prefix && b.ls < 0) {
-            r.ls = b.fv;
-            r.lsb = 0;
-        }
-        return r;
-    }
-    r.cnt = a.cnt + b.cnt;
-    r.fv = a.fv;
-    r.ft = a.ft;
-    if (b.ls >= 0) {
-        r.lsb = a.cnt + b.lsb;
-    } else if (has_time && (b.ft - a.lt) > kGapDays) {
-        r.ls = b.fv;
-        r.lsb = a.cnt;
-    } else {
-        r.ls = a.ls;
-        r.lsb = a.lsb;
-    }
-    return r;
-}
-
-__device__ __forceinline__ SegState seg_empty()
-{
-    SegState e;
-    e.cnt = 0;
-    e.fv = e.lv = e.ls = -1;
-    e.lsb = 0;
-    e.reserved = 0;
-    e.ft = e.lt = 0.0;
-    return e;
-}
-
-constexpr int kSpinLimit = 1 << 20;  // polls of one record before giving up (never reached)
-
-// Word i of a SegState (see ChunkRec) and the reverse.
-__device__ __forceinline__ uint32_t seg_word(const SegState& s, int i)
-{
-    const uint64_t ft = __double_as_longlong(s.ft), lt = __double_as_longlong(s.lt);
-    switch (i) {
-    case 0: return (uint32_t)s.cnt;
-    case 1: return (uint32_t)s.fv;
-    case 2: return (uint32_t)s.lv;
-    case 3: return (uint32_t)s.ls;
-    case 4: return (uint32_t)s.lsb;
-    case 5: return (uint32_t)ft;
-    case 6: return (uint32_t)(ft >> 32);
-    case 7: return (uint32_t)lt;
-    default: return (uint32_t)(lt >> 32);
-    }
-}
-
-__device__ __forceinline__ SegState seg_from_words(const uint32_t (&v)[kSegWords])
-{
-    SegState s;
-    s.cnt = (int32_t)v[0];
-    s.fv = (int32_t)v[1];
-    s.lv = (int32_t)v[2];
-    s.ls = (int32_t)v[3];
-    s.lsb = (int32_t)v[4];
-    s.reserved = 0;
-    s.ft = __longlong_as_double((long long)(((uint64_t)v[6] << 32) | v[5]));
-    s.lt = __longlong_as_double((long long)(((uint64_t)v[8] << 32) | v[7]));
-    return s;
-}
-
-// Publish a state: lane i < kSegWords of the calling wave stores word i with
-// the stamp (relaxed device-scope atomics: no cache flush, no ordering).
-__device__ __forceinline__ void seg_publish(uint64_t* words, const SegState& s, uint32_t stamp)
-{
-    const int lane = __lane_id();
-    if (lane < kSegWords)
-        __hip_atomic_store(&words[lane], ((uint64_t)stamp << 32) | seg_word(s, lane),
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Read a state if every word carries `stamp`.
-__device__ __forceinline__ bool seg_read(const uint64_t* words, uint32_t stamp, SegState& out)
-{
-    uint32_t v[kSegWords];
-    bool ok = true;
-#pragma unroll
-    for (int i = 0; i < kSegWords; ++i) {
-        const uint64_t w = __hip_atomic_load(&words[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        ok = ok && (uint32_t)(w >> 32) == stamp;
-        v[i] = (uint32_t)w;
-    }
-    if (ok) out = seg_from_words(v);
-    return ok;
-}
-
-// The state before chunk g of a curve whose first chunk is g0 (g > g0), from
-// the predecessors' records; run by one whole wave.  Lane l examines chunk
-// g - 1 - l - 64 k in round k; the nearest chunk with a final state ends the
-// walk, and the summaries of the chunks after it are combined in order.  The
-// result is returned in every lane.
-__device__ SegState lookback(const ChunkRec* __restrict__ recs, int g, int g0, uint32_t stamp,
-                             bool has_time, SegState* sh /* [64] */)
-{
-    const int lane = __lane_id();
-    SegState acc = seg_empty();  // the chunks after the current window, in order
-    for (int hi = g - 1;; hi -= 64) {
-        const int j = hi - lane;
-        int status = 2;  // before the curve's first chunk: the empty prefix
-        SegState st = seg_empty();
-        if (j >= g0) {
-            status = 0;
-            for (int polls = 0; polls < kSpinLimit && status == 0; ++polls) {
-                if (seg_read(recs[j].inc, stamp, st))
-                    status = 2;
-                else if (seg_read(recs[j].agg, stamp, st))
-                    status = 1;
-                else
-                    __builtin_amdgcn_s_sleep(1);
-            }
-            if (status == 0) status = 2;  // a timeout reads as final
-        }
-        sh[lane] = st;
-        const uint64_t fin = __ballot(status == 2);
-        const int k = fin ? __builtin_ctzll(fin) : 64;  // nearest final state in this window
-        // every lane's state is in LDS before lane 0 reads them
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        if (lane == 0) {
-            for (int i = 0; i < k; ++i) acc = seg_combine(sh[i], acc, false, has_time);
-            if (k < 64) acc = seg_combine(sh[k], acc, true, has_time);
-            sh[0] = acc;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        acc = sh[0];  // every lane
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        if (k < 64) break;
-    }
-    return acc;
-}
-
-// The batch header and curve table the pre-pass reads sit either in device
-// memory already or in the caller's pinned staging block, which the device
-// reads over the bus; in the latter case the pre-pass also copies the block
-// into device memory (`to`) for the estimate kernel, spread over the grid in
-// 8-byte words, so no separate copy precedes it.
-__device__ __forceinline__ void stage_block_copy(const uint8_t* __restrict__ src,
-                                                 uint8_t* __restrict__ to, int n_curves, int nt)
-{
-    if (to == nullptr) return;
-    const int words = (int)((sizeof(BatchHeader) + (size_t)n_curves * sizeof(CurveDesc)) / 8);
-    const uint64_t* s = reinterpret_cast<const uint64_t*>(src);
-    uint64_t* d = reinterpret_cast<uint64_t*>(to);
-    for (int i = (int)(blockIdx.x * nt + threadIdx.x); i < words; i += (int)gridDim.x * nt)
-        d[i] = s[i];
 }
 static_assert(sizeof(BatchHeader) % 8 == 0 && sizeof(CurveDesc) % 8 == 0, "8-byte words");
-
-template <int NT, int K>
-__global__ __launch_bounds__(NT) void umi_prepass_chunk_kernel(
-    const float* __restrict__ flux, const double* __restrict__ time,
-    const uint8_t* __restrict__ block, uint8_t* __restrict__ block_to, int curve_one,
-    int32_t* __restrict__ segid, int2* __restrict__ tiles, Counters* __restrict__ ctr,
-    ChunkRec* __restrict__ recs, int clear_queue, CurveDesc one, int one_chunks)
-{
-    const BatchHeader* __restrict__ hdr = reinterpret_cast<const BatchHeader*>(block);
-    const CurveDesc* __restrict__ curves =
-        reinterpret_cast<const CurveDesc*>(block + sizeof(BatchHeader));
-    constexpr int NW = NT / 64;
-    constexpr int kChunk = NT * K;
-    __shared__ int sh_vi[NW];      // per wave: latest valid index
-    __shared__ double sh_vt[NW];   //           its time
-    __shared__ int sh_vc[NW];      //           valid count
-    __shared__ int sh_sx[NW];      // per wave: latest segment start
-    __shared__ int sh_sz[NW];      //           valid samples before it
-    __shared__ int sh_fv;          // the chunk's first valid sample
-    __shared__ double sh_ft;       //   its time
-    __shared__ int sh_ticket, sh_curve;
-    __shared__ SegState sh_carry;  // the curve's state before the chunk
-    __shared__ SegState sh_lb[64]; // look-back window
-
-    const int tid = (int)threadIdx.x;
-    const int w = tid >> 6;
-    const int lane = __lane_id();
-    if (clear_queue && blockIdx.x == 0 && tid == 0) ctr->queue = 0u;
-    const uint64_t epoch_word = ctr->epoch;
-    const uint32_t stamp = (uint32_t)(epoch_word + 1);  // this launch's record stamp
-    // one curve (per-curve launches) or the whole batch; a batch of one curve
-    // may come with its descriptor and chunk count as arguments, so that no
-    // step waits on a read of the table over the bus
-    const bool given = one_chunks >= 0;
-    const int n_chunks = given ? one_chunks
-                               : (curve_one >= 0 ? (curves[curve_one].len + kChunk - 1) / kChunk
-                                                 : hdr->n_chunks);
-    const int n_curves = given ? 1 : hdr->n_curves;
-    stage_block_copy(block, block_to, n_curves, NT);
-
-    for (;;) {
-        if (tid == 0) sh_ticket = (int)atomicAdd(&ctr->tickets, 1u);
-        __syncthreads();
-        const int g = sh_ticket;
-        if (g >= n_chunks) break;
-        // the chunk's curve: the last table entry whose first chunk is <= g
-        // (a 64-way search by wave 0; chunk_base increases along the table)
-        if (curve_one >= 0) {
-            if (tid == 0) sh_curve = curve_one;
-        } else if (w == 0) {
-            int lo = 0, hi = n_curves;
-            while (hi - lo > 1) {
-                const int step = (hi - lo + 63) / 64;
-                const int idx = lo + lane * step;
-                const bool le = idx < hi && curves[idx].chunk_base <= g;
-                const uint64_t m = __ballot(le);
-                const int last = 63 - __builtin_clzll(m);  // lane 0 always qualifies
-                lo = lo + last * step;
-                hi = min(lo + step, hi);
-            }
-            if (lane == 0) sh_curve = lo;
-        }
-        __syncthreads();
-        const int cidx = sh_curve;
-        const CurveDesc cd = given ? one : curves[cidx];
-        const int g0 = curve_one >= 0 ? 0 : cd.chunk_base;  // the curve's first chunk
-        const int lo = (g - g0) * kChunk;
-        const int hi = min(lo + kChunk, cd.len);
-        const float* f = flux + cd.off;
-        const double* tm = time ? time + cd.off : nullptr;
-        const bool has_time = tm != nullptr;
-        int32_t* sid = segid + cd.off;
-
-        // the tiles that start in this chunk
-        for (int t = (lo + cd.tile - 1) / cd.tile + tid; t * cd.tile < hi; t += NT)
-            tiles[cd.tile_base + t] = make_int2(cidx, t * cd.tile);
-
-        float fv[K];
-        double tv[K];
-        const int e0 = lo + tid * K;
-#pragma unroll
-        for (int q = 0; q < K; ++q) {
-            const int e = e0 + q;
-            fv[q] = e < hi ? f[e] : __builtin_nanf("");
-            tv[q] = (has_time && e < hi) ? tm[e] : 0.0;
-        }
-        uint32_t vmask = 0;  // bit q: item q is valid
-        int vi = -1, vc = 0, fi = -1;
-        double vt = 0.0, ft = 0.0;
-#pragma unroll
-        for (int q = 0; q < K; ++q) {
-            const bool ok = e0 + q < hi && isfinite(fv[q]) && (!has_time || isfinite(tv[q]));
-            vmask |= (ok ? 1u : 0u) << q;
-            if (ok) {
-                if (fi < 0) {
-                    fi = e0 + q;
-                    ft = tv[q];
-                }
-                vi = e0 + q;
-                vt = tv[q];
-                ++vc;
-            }
-        }
-
-        // phase 1 (chunk alone): latest valid sample and valid count before
-        // this thread's items, the chunk's first and last valid samples
-        const int own_vc = vc;
-        wave_incl_latest_sum(vi, vt, vc);
-        if (lane == 63) {
-            sh_vi[w] = vi;
-            sh_vt[w] = vt;
-            sh_vc[w] = vc;
-        }
-        int ex_i = __shfl_up(vi, 1, 64);
-        double ex_t = __shfl_up(vt, 1, 64);
-        int before = vc - own_vc;  // valid samples earlier in this wave
-        if (lane == 0) ex_i = -1;
-        __syncthreads();
-        int tot = 0, blk_i = -1;
-        double blk_t = 0.0;
-        for (int i = 0; i < NW; ++i) {
-            if (i == w && ex_i < 0) {  // nothing valid earlier in this wave
-                ex_i = blk_i;
-                ex_t = blk_t;
-            }
-            if (i < w) before += sh_vc[i];
-            tot += sh_vc[i];
-            if (sh_vi[i] >= 0) {
-                blk_i = sh_vi[i];
-                blk_t = sh_vt[i];
-            }
-        }
-        if (before == 0 && own_vc > 0) {  // the thread holding the chunk's first valid sample
-            sh_fv = fi;
-            sh_ft = ft;
-        }
-
-        // phase 2 (chunk alone): segment starts that follow a valid sample of
-        // the chunk, then the latest such start before this thread's items
-        int sx = -1, sz = 0;
-        {
-            int pi = ex_i;
-            double pt = ex_t;
-            int v = before;
-#pragma unroll
-            for (int q = 0; q < K; ++q) {
-                if ((vmask >> q) & 1u) {
-                    if (pi >= 0 && has_time && (tv[q] - pt) > kGapDays) {
-                        sx = e0 + q;
-                        sz = v;
-                    }
-                    pi = e0 + q;
-                    pt = tv[q];
-                    ++v;
-                }
-            }
-        }
-        wave_incl_latest(sx, sz);
-        if (lane == 63) {
-            sh_sx[w] = sx;
-            sh_sz[w] = sz;
-        }
-        int px = __shfl_up(sx, 1, 64);
-        int pz = __shfl_up(sz, 1, 64);
-        if (lane == 0) px = -1;
-        __syncthreads();
-        int bx = -1, bz = 0;
-        for (int i = 0; i < NW; ++i) {
-            if (i == w && px < 0) {
-                px = bx;
-                pz = bz;
-            }
-            if (sh_sx[i] >= 0) {
-                bx = sh_sx[i];
-                bz = sh_sz[i];
-            }
-        }
-
-        // publish the chunk's summary, find the state before it, publish the
-        // state after it (wave 0)
-        if (w == 0) {
-            SegState agg = seg_empty();
-            if (tot > 0) {
-                agg.cnt = tot;
-                agg.fv = sh_fv;
-                agg.ft = sh_ft;
-                agg.lv = blk_i;
-                agg.lt = blk_t;
-                agg.ls = bx;
-                agg.lsb = bz;
-            }
-            SegState carry = seg_empty();
-            if (g > g0) {
-                seg_publish(recs[g].agg, agg, stamp);
-                carry = lookback(recs, g, g0, stamp, has_time, sh_lb);
-            }
-            const SegState inc = seg_combine(carry, agg, true, has_time);  // every lane
-            seg_publish(recs[g].inc, inc, stamp);
-            if (lane == 0) {
-                sh_carry = carry;
-                // the curve's last segment ends with its last chunk
-                if (hi == cd.len && inc.ls >= 0) sid[inc.ls] = -2 - (inc.cnt - inc.lsb);
-            }
-        }
-        __syncthreads();
-        const SegState cy = sh_carry;
-        const int fv0 = sh_fv;      // the chunk's first valid sample (when tot > 0)
-        const double ft0 = sh_ft;
-
-        // writes: segment of each item; a start closes the segment before it.
-        // The state entering this thread's items comes from the chunk scan
-        // where the chunk holds something before them, else from the carry;
-        // it is formed with selects only.
-        {
-            const bool local_pred = ex_i >= 0;
-            int pi = local_pred ? ex_i : cy.lv;
-            double pt = local_pred ? ex_t : cy.lt;
-            int v = cy.cnt + before;
-            // the chunk's first valid sample starts a segment when nothing
-            // valid precedes it in the curve or the gap to it is too long
-            const bool first_starts =
-                tot > 0 && (cy.cnt == 0 || (has_time && (ft0 - cy.lt) > kGapDays));
-            const bool local_start = px >= 0;
-            const bool use_fv = !local_start && first_starts && fv0 < e0;
-            pz = local_start ? pz + cy.cnt : (use_fv ? cy.cnt : cy.lsb);
-            px = local_start ? px : (use_fv ? fv0 : cy.ls);
-#pragma unroll
-            for (int q = 0; q < K; ++q) {
-                const int e = e0 + q;
-                if (e < hi) {
-                    if ((vmask >> q) & 1u) {
-                        if (pi < 0 || (has_time && (tv[q] - pt) > kGapDays)) {
-                            if (px >= 0) sid[px] = -2 - (v - pz);
-                            px = e;
-                            pz = v;
-                        } else {
-                            sid[e] = px;
-                        }
-                        pi = e;
-                        pt = tv[q];
-                        ++v;
-                    } else {
-                        sid[e] = -1;
-                    }
-                }
-            }
-        }
-        __syncthreads();  // LDS of this chunk is reused by the next
-    }
-
-    // the last workgroup to finish resets the tickets for the next launch.
-    // Every workgroup's final ticket increment has returned its value before
-    // the workgroup counts itself done, so once `done` shows all of them no
-    // increment is outstanding.
-    if (tid == 0) {
-        const uint32_t old =
-            __hip_atomic_fetch_add(&ctr->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (old == gridDim.x - 1) {
-            __hip_atomic_store(&ctr->tickets, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&ctr->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&ctr->epoch, epoch_word + 1, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-}
-
-// The same segment words and tiles from one workgroup per curve, which walks
-// the curve's chunks of NT * K samples in order and carries the scan state in
-// registers (the next chunk's loads are issued before the current chunk's
-// scans).  No tickets, records or look-back: batches of many curves fill the
-// chip this way, and every chunk costs one pass.  kTime: a time array is
-// given (without one nothing breaks a segment).  Two barriers per chunk:
-// each LDS array is written in one phase and read in the next, and a phase's
-// writes follow the barrier that ends every wave's reads of the same array in
-// the chunk before.
-template <int NT, int K, bool kTime>
-__global__ __launch_bounds__(NT) void umi_prepass_walk_kernel(
-    const float* __restrict__ flux, const double* __restrict__ time,
-    const uint8_t* __restrict__ block, uint8_t* __restrict__ block_to, int curve_first,
-    int32_t* __restrict__ segid, int2* __restrict__ tiles, uint32_t* __restrict__ counter,
-    int32_t* __restrict__ trash)
-{
-    const BatchHeader* __restrict__ hdr = reinterpret_cast<const BatchHeader*>(block);
-    const CurveDesc* __restrict__ curves =
-        reinterpret_cast<const CurveDesc*>(block + sizeof(BatchHeader));
-    constexpr int NW = NT / 64;
-    __shared__ int sh_vi[NW];      // per wave: latest valid index
-    __shared__ double sh_vt[NW];   //           its time
-    __shared__ int sh_vc[NW];      //           valid count
-    __shared__ int sh_sx[NW];      // per wave: latest segment start
-    __shared__ int sh_sz[NW];      //           valid samples before it
-
-    if (counter != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *counter = 0u;
-    const int n_curves = hdr->n_curves;
-    stage_block_copy(block, block_to, n_curves, NT);
-    const int cidx = curve_first + (int)blockIdx.x;
-    if (cidx >= n_curves) return;  // fixed-size grids cover fewer curves
-    const CurveDesc cd = curves[cidx];
-
-    const int ntiles = cd.len > 0 ? (cd.len + cd.tile - 1) / cd.tile : 0;
-    for (int t = threadIdx.x; t < ntiles; t += NT)
-        tiles[cd.tile_base + t] = make_int2(cidx, t * cd.tile);
-
-    const float* f = flux + cd.off;
-    const double* tm = time + (kTime ? cd.off : 0);  // unused without times
-    int32_t* sid = segid + cd.off;
-
-    // carries from earlier chunks (uniform over the block)
-    int c_vi = -1;      // latest valid index
-    double c_vt = 0.0;  // its time
-    int c_vc = 0;       // valid samples so far
-    int c_sx = -1;      // latest segment start
-    int c_sz = 0;       // valid samples before it
-
-    const int w = threadIdx.x >> 6;
-    const int lane = __lane_id();
-    constexpr int kChunk = NT * K;
-
-    // The next chunk's flux and times are loaded while the current one is
-    // scanned, so the loads' latency overlaps the scans.  Every step issues
-    // the same loads and stores whatever the data (indices past the curve
-    // load its last sample and store to `trash`), so the wait for a chunk's
-    // loads counts only the memory operations issued after them and never
-    // waits for the previous chunk's stores or the next chunk's loads.
-    const int last = cd.len - 1;
-    float fv[K];
-    double tv[K];
-    auto load_chunk = [&](int base, float* fo, double* to) {
-#pragma unroll
-        for (int q = 0; q < K; ++q) {
-            const int e = min(base + (int)threadIdx.x * K + q, last);
-            fo[q] = f[e];
-            to[q] = kTime ? tm[e] : 0.0;
-        }
-    };
-    if (cd.len > 0) load_chunk(0, fv, tv);
-
-    for (int base = 0; base < cd.len; base += kChunk) {
-        float nf[K];
-        double nt[K];
-        load_chunk(base + kChunk, nf, nt);
-        const int e0 = base + (int)threadIdx.x * K;
-        uint32_t vmask = 0;  // bit q: item q is valid
-        int vi = -1, vc = 0;
-        double vt = 0.0;
-#pragma unroll
-        for (int q = 0; q < K; ++q) {
-            const bool ok = e0 + q < cd.len && isfinite(fv[q]) && (!kTime || isfinite(tv[q]));
-            vmask |= (ok ? 1u : 0u) << q;
-            if (ok) {
-                vi = e0 + q;
-                vt = tv[q];
-                ++vc;
-            }
-        }
-
-        // phase 1: latest valid sample and valid count before this thread's items
-        const int own_vc = vc;
-        wave_incl_latest_sum(vi, vt, vc);
-        if (lane == 63) {
-            sh_vi[w] = vi;
-            sh_vt[w] = vt;
-            sh_vc[w] = vc;
-        }
-        int ex_i = __shfl_up(vi, 1, 64);
-        double ex_t = __shfl_up(vt, 1, 64);
-        int before = vc - own_vc;  // valid samples earlier in this wave
-        if (lane == 0) ex_i = -1;
-        __syncthreads();
-        int blk_i = c_vi, tot = 0;
-        double blk_t = c_vt;
-        for (int i = 0; i < NW; ++i) {
-            if (i == w && ex_i < 0) {  // nothing valid earlier in this wave
-                ex_i = blk_i;
-                ex_t = blk_t;
-            }
-            if (i < w) before += sh_vc[i];
-            tot += sh_vc[i];
-            if (sh_vi[i] >= 0) {
-                blk_i = sh_vi[i];
-                blk_t = sh_vt[i];
-            }
-        }
-        before += c_vc;
-
-        // phase 2: segment starts among this thread's items, then the latest
-        // start before them
-        int sx = -1, sz = 0;
-        {
-            int pi = ex_i;
-            double pt = ex_t;
-            int v = before;
-#pragma unroll
-            for (int q = 0; q < K; ++q) {
-                if ((vmask >> q) & 1u) {
-                    if (pi < 0 || (kTime && (tv[q] - pt) > kGapDays)) {
-                        sx = e0 + q;
-                        sz = v;
-                    }
-                    pi = e0 + q;
-                    pt = tv[q];
-                    ++v;
-                }
-            }
-        }
-        wave_incl_latest(sx, sz);
-        if (lane == 63) {
-            sh_sx[w] = sx;
-            sh_sz[w] = sz;
-        }
-        int px = __shfl_up(sx, 1, 64);
-        int pz = __shfl_up(sz, 1, 64);
-        if (lane == 0) px = -1;
-        __syncthreads();
-        {
-            int bx = c_sx, bz = c_sz;
-            for (int i = 0; i < NW; ++i) {
-                if (i == w && px < 0) {
-                    px = bx;
-                    pz = bz;
-                }
-                if (sh_sx[i] >= 0) {
-                    bx = sh_sx[i];
-                    bz = sh_sz[i];
-                }
-            }
-            // every wave has read the phase-1 arrays; carries for the next chunk
-            if (blk_i >= 0) {
-                c_vi = blk_i;
-                c_vt = blk_t;
-            }
-            c_vc += tot;
-            c_sx = bx;
-            c_sz = bz;
-        }
-
-        // writes: segment of each item; a start closes the segment before it.
-        // One store per item, its address and value chosen by selects.
-        {
-            int pi = ex_i;
-            double pt = ex_t;
-            int v = before;
-#pragma unroll
-            for (int q = 0; q < K; ++q) {
-                const int e = e0 + q;
-                const bool valid = (vmask >> q) & 1u;  // implies e < cd.len
-                const bool start = valid && (pi < 0 || (kTime && (tv[q] - pt) > kGapDays));
-                int32_t* dst = start ? (px >= 0 ? sid + px : trash) : (e < cd.len ? sid + e : trash);
-                const int32_t val = start ? -2 - (v - pz) : (valid ? px : -1);
-                *dst = val;
-                if (start) {
-                    px = e;
-                    pz = v;
-                }
-                if (valid) {
-                    pi = e;
-                    pt = tv[q];
-                    ++v;
-                }
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < K; ++q) {
-            fv[q] = nf[q];
-            tv[q] = nt[q];
-        }
-    }
-    if (threadIdx.x == 0 && c_sx >= 0) sid[c_sx] = -2 - (c_vc - c_sz);
-}
 
 // ---------------------------------------------------------------------------
 // Main kernel.
@@ -789,9 +99,13 @@ struct MainSmem {
     float xv[kStageMax];                  // compacted valid samples
     uint64_t vbits[kWords];               // staged-sample validity
     uint32_t vpre[kWords];
-    uint64_t sbits[kWords];               // staged samples that start a segment
+    uint64_t sbits[kWords];               // valid samples a gap precedes: they start a segment
+    uint64_t live[kWords];                // valid samples of segments of at least W/3
+    double tfirst[kWords], tlast[kWords]; // times of each word's first and last valid sample
     int tile;
     int nvalid;
+    int multi;                            // the span holds more than one segment
+    int dead;                             // and some of its valid samples are not live
     uint32_t kmin, kmax;                  // smallest and largest staged key
     uint32_t wsum[kMainThreads / 64];     // per wave: bucket counts of its threads
 };
@@ -815,6 +129,82 @@ __device__ __forceinline__ uint32_t rank1(const uint64_t* bits, const uint32_t* 
     return pre[w] + (uint32_t)__popcll(bits[w] & m);
 }
 
+// Wave-wide minimum and maximum by DPP, valid in lane 63.
+__device__ __forceinline__ uint32_t wave_min(uint32_t v)
+{
+#define UMI_STEP(CTRL, ROWS)                                                                       \
+    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROWS, 0xF, false))
+    UMI_STEP(0x111, 0xF);
+    UMI_STEP(0x112, 0xF);
+    UMI_STEP(0x114, 0xF);
+    UMI_STEP(0x118, 0xF);
+    UMI_STEP(0x142, 0xA);
+    UMI_STEP(0x143, 0xC);
+#undef UMI_STEP
+    return v;
+}
+
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) { return ~wave_min(~v); }
+
+// The thread's index in the workgroup, opaque to the compiler: it would keep
+// every index and address it derives from threadIdx.x across the tiles of the
+// estimate kernel's loop, and spill what does not fit (the instance with
+// cores: 29 registers spilled against 8).
+__device__ __forceinline__ int thread_index()
+{
+    int t = (int)threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+// The value of the lane before (lane 0 keeps its own).
+__device__ __forceinline__ double wave_shift(double v)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)u, (int)(uint32_t)u,
+                                                              0x138, 0xF, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(
+        (int)(uint32_t)(u >> 32), (int)(uint32_t)(u >> 32), 0x138, 0xF, 0xF, false);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// The same value in scalar registers (it is the wave's already).
+template <class T>
+__device__ __forceinline__ T uniform(const T& v)
+{
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    constexpr int n = sizeof(T) / 4;
+    int w[n];
+    __builtin_memcpy(w, &v, sizeof(T));
+#pragma unroll
+    for (int i = 0; i < n; ++i) w[i] = __builtin_amdgcn_readfirstlane(w[i]);
+    T r;
+    __builtin_memcpy(&r, w, sizeof(T));
+    return r;
+}
+
+// Inclusive sum over the lanes of a wave by DPP.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v)
+{
+#define UMI_STEP(CTRL, ROWS)                                                                       \
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false)
+    UMI_STEP(0x111, 0xF);
+    UMI_STEP(0x112, 0xF);
+    UMI_STEP(0x114, 0xF);
+    UMI_STEP(0x118, 0xF);
+    UMI_STEP(0x142, 0xA);
+    UMI_STEP(0x143, 0xC);
+#undef UMI_STEP
+    return v;
+}
+
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
 // Ones-before prefix over `nw` words, computed by wave 0; returns total ones
 // in lane 0's view through `total_out` (written to LDS by the caller).
 __device__ __forceinline__ void word_prefix(const uint64_t* bits, uint32_t* pre, int nw, uint32_t* total_out)
@@ -822,10 +212,136 @@ __device__ __forceinline__ void word_prefix(const uint64_t* bits, uint32_t* pre,
     if (threadIdx.x < 64) {
         const int lane = threadIdx.x;
         const int c = lane < nw ? __popcll(bits[lane]) : 0;
-        const int incl = wave_incl_sum(c);
+        const int incl = (int)wave_scan((uint32_t)c);
         if (lane < nw) pre[lane] = (uint32_t)(incl - c);
         if (lane == 63) *total_out = (uint32_t)incl;
     }
+}
+
+// ---------------------------------------------------------------------------
+// Validity and segments of a tile's staged span (gap handling, minimum
+// segment length W/3 of Section 4.4).
+//
+// A window reaches at most W-1 samples and never past its segment, so all it
+// needs is inside the staged span: which samples are valid, and where a valid
+// sample lies more than kGapDays after the valid one before it (strictly; no
+// times, no breaks).  Only a segment's length can depend on samples outside
+// the span, and only for the first and the last segment of the span, when
+// they hold fewer than W/3 valid samples inside it: those are followed
+// outwards until the count is reached or the segment ends.  So no pass over
+// the curves precedes the estimate kernel (a scan that wrote one segment word
+// per sample took 0.47 ms of 3.0 on 2,000 curves of 40,000-70,000 samples at
+// W = 25, and 12 of 50 us on one of 20,000 at W = 361).
+
+// Valid samples of the segment that reaches the span's border, beyond it:
+// from curve sample e in direction dir (the nearest valid sample inside the
+// span is at time tn), until `need` are found.  Run by one whole wave.
+__device__ __forceinline__ int segment_beyond(const float* __restrict__ flux,
+                                           const double* __restrict__ time, int len, int e, int dir,
+                                           double tn, int need)
+{
+    const int lane = thread_index() & 63;
+    constexpr int K = 4;  // samples per lane and step, loaded together
+    int got = 0;
+    while (got < need && e >= 0 && e < len) {
+        float x[K];
+        double t[K];
+#pragma unroll
+        for (int u = 0; u < K; ++u) {
+            const int i = e + dir * (64 * u + lane);
+            const bool in = i >= 0 && i < len;
+            x[u] = in ? flux[i] : __builtin_nanf("");
+            t[u] = in && time ? time[i] : 0.0;
+        }
+        for (int u = 0; u < K && got < need; ++u) {
+            const bool ok = isfinite(x[u]) && isfinite(t[u]);
+            const uint64_t m = __ballot(ok);
+            const uint64_t nearer = m & ((1ull << lane) - 1ull);
+            // the nearest valid sample towards the span
+            const double ts = __shfl(t[u], nearer ? 63 - (int)__builtin_clzll(nearer) : lane, 64);
+            const double t_in = nearer ? ts : tn;
+            const bool cut = ok && time && (dir > 0 ? t[u] - t_in : t_in - t[u]) > kGapDays;
+            const uint64_t c = __ballot(cut);
+            if (c != 0) return got + (int)__popcll(m & ((c & -c) - 1ull));
+            got += (int)__popcll(m);
+            if (m != 0) tn = __shfl(t[u], 63 - (int)__builtin_clzll(m), 64);
+        }
+        e += dir * 64 * K;
+    }
+    return got;
+}
+
+// From the span's validity and in-word start bits: the prefix counts, the
+// starts at word borders, and the live bits (valid samples of segments of at
+// least m_min valid samples).  Run by wave 0.
+__device__ __forceinline__ void resolve_segments(MainSmem& sm, const float* __restrict__ flux,
+                                                 const double* __restrict__ time, int len, int s0,
+                                                 int N, int nwv, int m_min)
+{
+    const int lane = thread_index() & 63;
+    const uint64_t v = lane < nwv ? sm.vbits[lane] : 0ull;
+    uint64_t s = lane < nwv ? sm.sbits[lane] : 0ull;
+    const int c = __popcll(v);
+    const int incl = (int)wave_scan((uint32_t)c);
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    const uint64_t some = __ballot(c > 0);
+    if (time != nullptr) {
+        // the first valid sample of a word against the last before the word
+        const uint64_t earlier = some & ((1ull << lane) - 1ull);
+        if (c > 0 && earlier != 0 &&
+            sm.tfirst[lane] - sm.tlast[63 - __builtin_clzll(earlier)] > kGapDays) {
+            s |= v & -v;
+            sm.sbits[lane] = s;
+        }
+    }
+    if (lane < nwv) {
+        sm.vpre[lane] = (uint32_t)(incl - c);
+        sm.live[lane] = v;
+    }
+    const bool multi = __ballot(s != 0) != 0;
+    if (lane == 0) {
+        sm.nvalid = total;
+        sm.multi = multi ? 1 : 0;
+        sm.dead = 0;
+    }
+    if (total == 0 || (!multi && total >= m_min)) return;
+    // segment by segment: a valid sample starts one, the first of the span too
+    wave_lds_sync();
+    const int wf = (int)__builtin_ctzll(some), wl = 63 - (int)__builtin_clzll(some);
+    int lo = 0, begin = 0;     // the segment's first sample (as a word walk), samples before it
+    int w = 0;
+    uint64_t bits = __shfl(s, 0, 64);
+    bool dead = false;
+    for (;;) {
+        while (bits == 0 && ++w < nwv) bits = __shfl(s, w, 64);
+        const bool last = w >= nwv;
+        const int hi = last ? N : 64 * w + (int)__builtin_ctzll(bits);
+        const int upto = last ? total
+                              : __builtin_amdgcn_readlane(incl - c, w) +
+                                    (int)__popcll(__shfl(v, w, 64) & ((bits & -bits) - 1ull));
+        int n = upto - begin;
+#pragma unroll 1
+        for (int dir = -1; dir <= 1; dir += 2) {
+            if (n > 0 && n < m_min && (dir < 0 ? begin == 0 : last))
+                n += segment_beyond(flux, time, len, dir < 0 ? s0 - 1 : s0 + N, dir,
+                                    !time ? 0.0 : (dir < 0 ? sm.tfirst[wf] : sm.tlast[wl]),
+                                    m_min - n);
+        }
+        if (n < m_min && upto > begin) {
+            // a dead segment: its samples [lo, hi) give NaN
+            dead = true;
+            const int a = min(max(lo - 64 * lane, 0), 64), b = min(max(hi - 64 * lane, 0), 64);
+            if (lane < nwv && a < b) {
+                const uint64_t up = b >= 64 ? ~0ull : (1ull << b) - 1ull;
+                sm.live[lane] &= ~(up & (~0ull << a));
+            }
+        }
+        if (last) break;
+        lo = hi;
+        begin = upto;
+        bits &= bits - 1;
+    }
+    if (lane == 0) sm.dead = dead ? 1 : 0;
 }
 
 // k-th smallest (0-based) value of the level-0 sequence within [s, e).
@@ -1150,37 +666,27 @@ __device__ __forceinline__ void small_window_medians(const uint32_t* __restrict_
 // dead segment (a NaN output).
 template <int kFeat>
 __device__ __forceinline__ bool window_range(const MainSmem& sm, const CurveDesc& cd,
-                                             const int32_t* __restrict__ segid,
-                                             const double* __restrict__ time, int h, int s0,
-                                             int N, int m_min, int p, uint32_t& ca, uint32_t& n)
+                                             const double* __restrict__ time, bool multi, int h,
+                                             int s0, int N, int p, uint32_t& ca, uint32_t& n)
 {
-    // p's segment: it starts at the valid sample x and holds cnt valid
-    // samples (the record sits in the slot of x)
-    const int sidp = segid[cd.off + p];
-    int x = -1, cnt = 0;
-    if (sidp <= -2) {
-        x = p;
-        cnt = -2 - sidp;
-    } else if (sidp >= 0 && sidp < p) {
-        const int rec = segid[cd.off + sidp];
-        x = sidp;
-        cnt = rec <= -2 ? -2 - rec : 0;
+    const uint32_t ip = (uint32_t)(p - s0);
+    if (((sm.live[ip >> 6] >> (ip & 63u)) & 1ull) == 0ull) return false;
+    int a = max(p - h, s0);
+    int b = min(p + h, s0 + N - 1);
+    if (multi) {
+        // the segment starts at the last start bit up to p, and ends before
+        // the first one after it, where these are within reach
+        const uint32_t reach = (uint32_t)(a - s0);
+        uint32_t wi = ip >> 6;
+        uint64_t sb = sm.sbits[wi] & (~0ull >> (63u - (ip & 63u)));
+        while (sb == 0ull && (wi << 6) > reach) sb = sm.sbits[--wi];
+        if (sb != 0ull) a = max(a, s0 + (int)((wi << 6) + 63u - (uint32_t)__builtin_clzll(sb)));
+        const uint32_t from = ip + 1u, lim = (uint32_t)(b - s0);
+        wi = from >> 6;
+        sb = sm.sbits[wi] & (~0ull << (from & 63u));
+        while (sb == 0ull && (wi << 6) + 64u <= lim) sb = sm.sbits[++wi];
+        if (sb != 0ull) b = min(b, s0 + (int)((wi << 6) + (uint32_t)__builtin_ctzll(sb)) - 1);
     }
-    if (x < 0 || cnt < m_min) return false;
-    int a = max(p - h, x);
-    if (kFeat & kFeatCore) a = max(a, s0);  // positions before the tile are asked for too
-    // the window ends before the next segment's first sample: the first
-    // start bit after p within reach of p + h
-    const uint32_t from = (uint32_t)(p + 1 - s0);
-    uint32_t lim = (uint32_t)(min(p + h, s0 + N - 1) - s0);
-    uint32_t wi = from >> 6;
-    uint64_t sb = sm.sbits[wi] & (~0ull << (from & 63u));
-    while (sb == 0ull && (wi << 6) + 64u <= lim) sb = sm.sbits[++wi];
-    if (sb != 0ull) {
-        const uint32_t nx = (wi << 6) + (uint32_t)__builtin_ctzll(sb);
-        if (nx <= lim) lim = nx - 1u;
-    }
-    int b = s0 + (int)lim;
     if ((kFeat & kFeatExtra) && cd.window_days > 0.0) {
         // time window: only the samples within half its length of p count.
         // Times are non-decreasing, so they form a run that two scans in from
@@ -1242,38 +748,6 @@ __device__ __forceinline__ void window_phase1(const MainSmem& sm, const Wavelet&
     }
 }
 
-// Wave-wide minimum and maximum by DPP, valid in lane 63.
-__device__ __forceinline__ uint32_t wave_min(uint32_t v)
-{
-#define UMI_STEP(CTRL, ROWS)                                                                       \
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROWS, 0xF, false))
-    UMI_STEP(0x111, 0xF);
-    UMI_STEP(0x112, 0xF);
-    UMI_STEP(0x114, 0xF);
-    UMI_STEP(0x118, 0xF);
-    UMI_STEP(0x142, 0xA);
-    UMI_STEP(0x143, 0xC);
-#undef UMI_STEP
-    return v;
-}
-
-__device__ __forceinline__ uint32_t wave_max(uint32_t v) { return ~wave_min(~v); }
-
-// Inclusive sum over the lanes of a wave by DPP.
-__device__ __forceinline__ uint32_t wave_scan(uint32_t v)
-{
-#define UMI_STEP(CTRL, ROWS)                                                                       \
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false)
-    UMI_STEP(0x111, 0xF);
-    UMI_STEP(0x112, 0xF);
-    UMI_STEP(0x114, 0xF);
-    UMI_STEP(0x118, 0xF);
-    UMI_STEP(0x142, 0xA);
-    UMI_STEP(0x143, 0xC);
-#undef UMI_STEP
-    return v;
-}
-
 // Sorts the tile's (key, index) pairs: sortbuf[0, npad) ascending, padded
 // with ~0, from xv[0, nv) and the keys' range in sm.kmin, sm.kmax; cnt holds
 // kBuckets cleared counters.  The keys are dealt to kBuckets buckets of equal
@@ -1289,8 +763,8 @@ constexpr uint32_t kBucketMost = 96;
 
 __device__ __forceinline__ void sort_tile(MainSmem& sm, uint32_t* __restrict__ cnt, int nv, int npad)
 {
-    const int tid = (int)threadIdx.x;
-    const int wave = tid >> 6;
+    const int tid = thread_index();
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int kPer = kStageMax / kMainThreads;
     const uint32_t kmin = sm.kmin;
     const uint32_t range = sm.kmax - kmin;
@@ -1382,16 +856,14 @@ template <int R, int kFeat>
 __device__ __forceinline__ void tile_windows(const MainSmem& sm, const Wavelet& wv, int levels, int nv,
                                              const CurveDesc& cd, int h, int s0, int N, int t0,
                                              int t1,
-                                             const int32_t* __restrict__ segid, float alpha,
-                                             float c, int iters, int scale, bool simple,
+                                             bool multi, float alpha, float c, int iters, int scale, bool simple,
                                              const float* pm, const uint32_t* pn,
                                              const double* __restrict__ time,
                                              float* __restrict__ trend,
                                              float* __restrict__ median,
                                              float* __restrict__ detrended)
 {
-    const int m_min = max(1, cd.W / 3);
-    const int pfirst = t0 + (int)threadIdx.x * R;
+    const int pfirst = t0 + thread_index() * R;
     uint32_t ca[R], n[R];
     bool live[R];
 #pragma unroll
@@ -1408,7 +880,7 @@ __device__ __forceinline__ void tile_windows(const MainSmem& sm, const Wavelet& 
             n[r] = (uint32_t)cd.W;
         } else {
             live[r] = p < t1 &&
-                      window_range<kFeat>(sm, cd, segid, time, h, s0, N, m_min, p, ca[r], n[r]);
+                      window_range<kFeat>(sm, cd, time, multi, h, s0, N, p, ca[r], n[r]);
         }
     }
     // The common case -- every window of the wave live, of one length, and
@@ -1569,7 +1041,7 @@ template <int G>
 __device__ __forceinline__ void window_phase1_scan(const MainSmem& sm, int nv, uint32_t ca,
                                                    uint32_t n, float& m, uint32_t& nplus)
 {
-    const uint32_t l = threadIdx.x & (G - 1);
+    const uint32_t l = (uint32_t)thread_index() & (G - 1);
     const uint32_t k = (n - 1) >> 1;
     uint32_t need = k + 1;  // window pairs still to pass, the k-th included
     uint32_t rk = 0;
@@ -1635,19 +1107,18 @@ template <int G, int kFeat>
 __device__ __forceinline__ void tile_windows_split(const MainSmem& sm, const Wavelet& wv, int levels, int nv,
                                                    const CurveDesc& cd, int h, int s0, int N,
                                                    int t0, int t1,
-                                                   const int32_t* __restrict__ segid,
-                                                   float alpha, float c, int iters, int scale,
+                                                   bool multi, float alpha, float c, int iters, int scale,
                                                    const double* __restrict__ time,
                                                    float* __restrict__ trend,
                                                    float* __restrict__ median,
                                                    float* __restrict__ detrended, bool scan)
 {
-    const int m_min = max(1, cd.W / 3);
-    const int l = (int)threadIdx.x & (G - 1);
-    const int p = t0 + (int)threadIdx.x / G;
+    const int tid = thread_index();
+    const int l = tid & (G - 1);
+    const int p = t0 + tid / G;
     uint32_t ca = 0, n = 0;
     const bool live =
-        p < t1 && window_range<kFeat>(sm, cd, segid, time, h, s0, N, m_min, p, ca, n);
+        p < t1 && window_range<kFeat>(sm, cd, time, multi, h, s0, N, p, ca, n);
     float m = 0.0f, sc = 0.0f;
     uint32_t nplus = 0;
     if (live) {  // same on every lane
@@ -1741,13 +1212,6 @@ __device__ __forceinline__ CoreLds core_lds(float* base, int cap)
     return c;
 }
 
-__device__ __forceinline__ void wave_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
-
 // v + (v of the lane a DPP control selects, 0 where it selects none)
 template <int kCtrl, int kRows>
 __device__ __forceinline__ float dpp_add(float v)
@@ -1776,7 +1240,7 @@ __device__ __forceinline__ float lane_value(float v, int lane)
 __device__ __forceinline__ void core_collect(const MainSmem& sm, const CoreLds& cw, int nv, int npad,
                                              uint32_t cca, int nc)
 {
-    const int lane = __lane_id();
+    const int lane = thread_index() & 63;
     int base = 0;
     for (int j0 = 0; j0 < nv && base < nc; j0 += 256) {
         uint64_t e[4];
@@ -1808,7 +1272,7 @@ __device__ __forceinline__ void core_collect(const MainSmem& sm, const CoreLds& 
 __device__ __forceinline__ bool core_build(const CoreLds& cw, int nc, float alpha, float& centre,
                                            float& unit)
 {
-    const int lane = __lane_id();
+    const int lane = thread_index() & 63;
     const int nb = nc / kCoreBlock;
     {
         float* t = cw.tree;
@@ -1905,7 +1369,7 @@ __device__ __forceinline__ void core_phase1(const MainSmem& sm, const CoreLds& c
                                             bool core, int nc, int cca, bool live, uint32_t ca,
                                             uint32_t n, float& m, uint32_t& nplus)
 {
-    const int lane = __lane_id();
+    const int lane = thread_index() & 63;
     const int k = (int)((n - 1) >> 1);
     bool found = false, zero = false;
     if (core) {
@@ -2103,18 +1567,17 @@ constexpr float kCoreReach = 0.5f;
 template <int kFeat>
 __device__ __forceinline__ void core_group(const MainSmem& sm, const CoreLds& cw, int nv, int npad, const CurveDesc& cd, int h, int s0,
                                            int N, int t0, int t1, int g0,
-                                           const int32_t* __restrict__ segid, float alpha, float c,
+                                           bool multi, float alpha, float c,
                                            int iters, int scale, const double* __restrict__ time,
                                            float* __restrict__ trend, float* __restrict__ median,
                                            float* __restrict__ detrended)
 {
-    const int p = g0 + __lane_id();
+    const int p = g0 + (thread_index() & 63);
     const bool mine = p >= t0 && p < t1;
     uint32_t ca = 0, n = 0;
     // the ranges of positions outside the tile count too (cut at the staged
     // span, which the core never reaches): the core is the group's
-    const bool alive = p < cd.len && window_range<kFeat>(sm, cd, segid, time, h, s0, N,
-                                                         max(1, cd.W / 3), p, ca, n);
+    const bool alive = p < cd.len && window_range<kFeat>(sm, cd, time, multi, h, s0, N, p, ca, n);
     const bool live = alive && mine;
     const uint64_t alive_m = __ballot(alive);
     const uint64_t live_m = __ballot(live);
@@ -2274,11 +1737,10 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const CoreLds& cw
 // the same results on the batches it serves.
 template <int kFeat>
 __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8) void umi_main_kernel(
-    const float* __restrict__ flux, const int32_t* __restrict__ segid,
-    const BatchHeader* __restrict__ hdr,
+    const float* __restrict__ flux, const BatchHeader* __restrict__ hdr,
     const CurveDesc* __restrict__ curves, const int2* __restrict__ tiles, int tile_first,
     int tile_count, uint32_t* __restrict__ counter, float* __restrict__ trend,
-    float* __restrict__ median, int core_floats)
+    float* __restrict__ median, int core_floats, const SmallTable small)
 {
     __shared__ MainSmem sm;
     Wavelet* wvp;
@@ -2292,17 +1754,20 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
         wvp = &wv_;
     }
     Wavelet& wv = *wvp;
-    const int tid = threadIdx.x;
-    const int lane = __lane_id();
-    const int wave = tid >> 6;
-    const int iters = hdr->iters;
-    const int scale = (kFeat & kFeatExtra) ? hdr->scale : (int)UMI_SCALE_UPPER_RMS;
-    float* const detrended = hdr->detrended;
-    const double* const time = hdr->time;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const bool by_value = small.n_curves > 0;
+    const int iters = by_value ? small.hdr.iters : hdr->iters;
+    const int scale = (kFeat & kFeatExtra) ? (by_value ? small.hdr.scale : hdr->scale)
+                                           : (int)UMI_SCALE_UPPER_RMS;
+    float* const detrended = by_value ? small.hdr.detrended : hdr->detrended;
+    const double* const time = by_value ? small.hdr.time : hdr->time;
     // tile range [tile_first, tile_end): a count < 0 means "all tiles of the batch"
-    const int tile_end = tile_count < 0 ? hdr->n_tiles : tile_first + tile_count;
+    const int tile_end = tile_count >= 0 ? tile_first + tile_count
+                                         : (by_value ? small.hdr.n_tiles : hdr->n_tiles);
 
     for (int round = 0;; ++round) {
+        const int tid = thread_index();
+        const int lane = tid & 63;
         // Instances with split tiles serve small batches, where a workgroup
         // often has one tile: its first tile is its block index, and the
         // queue counter hands out the tiles after the grid's first round
@@ -2323,56 +1788,90 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
         const int tile = __builtin_amdgcn_readfirstlane(sm.tile);
         if (tile >= tile_end) break;
 
-        const int2 td = tiles[tile];
-        const CurveDesc cd = curves[td.x];
+        CurveDesc cd;
+        int t0;
+        if (by_value) {
+            // the tile's curve: the last table entry whose first tile is <= tile
+            int ci = 0;
+            if (small.n_curves > 1) {
+                const bool le = lane < small.n_curves && small.c[lane].tile_base <= tile;
+                ci = 63 - (int)__builtin_clzll(__ballot(le));
+            }
+            cd = uniform(small.c[ci]);
+            t0 = (tile - cd.tile_base) * cd.tile;
+        } else {
+            const int2 td = tiles[tile];
+            cd = uniform(curves[__builtin_amdgcn_readfirstlane(td.x)]);
+            t0 = __builtin_amdgcn_readfirstlane(td.y);
+        }
         const float alpha = cd.alpha;
         const float c = cd.c;
         const int h = (cd.W - 1) >> 1;
-        const int t0 = td.y;
         const int t1 = min(t0 + cd.tile, cd.len);
         const int s0 = max(t0 - h, 0);
         const int s1 = min(t1 + h, cd.len);
         const int N = s1 - s0;  // <= kStageMax, guaranteed by the host
-        const float* f = flux + cd.off + s0;
-        const int32_t* sg = segid + cd.off + s0;
+        const float* const f = flux + cd.off;
+        const double* const tm = time ? time + cd.off : nullptr;
 
-        // --- staged validity bit vector (valid = finite flux and time) ---
-        // A tile is "simple" when every one of its windows is full: a small
-        // W, no curve end within reach, and the whole span valid and in one
-        // segment.  Its medians then come from per-window networks.
-        // segment of staged sample i (the start index of its segment, -1 if
-        // invalid): a segment's first slot holds its record instead
-        const int sg0 = sg[0];
-        const int seg0 = sg0 >= 0 ? sg0 : (sg0 == -1 ? -1 : s0);
-        bool same = true;
+        // --- staging: validity (finite flux and time) and segment starts as
+        // bit vectors, the span's samples in registers ---
         const int nwv = (N >> 6) + 1;
-        for (int i0 = wave * 64; i0 < nwv * 64; i0 += kMainThreads) {
-            const int i = i0 + lane;
-            const int sgi = i < N ? sg[i] : sg0;
-            const bool ok = (i < N) && (sgi != -1);
-            if (kFeat & kFeatSmall) {
-                const int segi = i < N ? (sgi >= 0 ? sgi : (sgi == -1 ? -1 : s0 + i)) : seg0;
-                same = same && segi == seg0;
+        constexpr int kPer = kStageMax / kMainThreads;
+        float xs[kPer];
+        {
+            double ts[kPer];
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                const int i = tid + u * kMainThreads;
+                xs[u] = i < N ? f[s0 + i] : __builtin_nanf("");
+                ts[u] = i < N && tm ? tm[s0 + i] : 0.0;
             }
-            const uint64_t bal = __ballot(ok);
-            const uint64_t st = __ballot(ok && sgi <= -2);
-            if (lane == 0) {
-                sm.vbits[i0 >> 6] = bal;
-                sm.sbits[i0 >> 6] = st;
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                const int wi = wave + u * (kMainThreads / 64);
+                if (wi >= nwv) break;
+                const bool ok = isfinite(xs[u]) && isfinite(ts[u]);
+                const uint64_t bal = __ballot(ok);
+                uint64_t st = 0;
+                if (tm) {
+                    // against the valid sample before it in the word (the
+                    // first of a word: resolve_segments)
+                    double before = wave_shift(ts[u]);
+                    const uint64_t earlier = bal & ((1ull << lane) - 1ull);
+                    const int prev = earlier ? 63 - (int)__builtin_clzll(earlier) : lane;
+                    if (__any(ok && prev < lane - 1)) {
+                        const double tp = __shfl(ts[u], prev, 64);
+                        if (prev != lane - 1) before = tp;
+                    }
+                    st = __ballot(ok && earlier != 0 && ts[u] - before > kGapDays);
+                    if (ok && earlier == 0) sm.tfirst[wi] = ts[u];
+                    if (ok && (bal >> lane) == 1ull) sm.tlast[wi] = ts[u];
+                }
+                if (lane == 0) {
+                    sm.vbits[wi] = bal;
+                    sm.sbits[wi] = st;
+                }
+            }
+            if (tid == 0 && nwv == kWords) {  // a full span's sentinel word
+                sm.vbits[kWords - 1] = 0ull;
+                sm.sbits[kWords - 1] = 0ull;
             }
         }
         // lanes per window (1: R windows per lane)
         const int G = (kFeat & kFeatSplit) ? split_lanes(cd.tile) : 1;
-        bool simple = false;
-        if (kFeat & kFeatSmall)
-            simple = __syncthreads_and(same) && seg0 >= 0 && cd.W <= kSmallW &&
-                     scale != UMI_SCALE_MAD && cd.window_days == 0.0 && t0 >= h &&
-                     t1 + h <= cd.len && G == 1;
-        else
-            __syncthreads();
-        word_prefix(sm.vbits, sm.vpre, nwv, reinterpret_cast<uint32_t*>(&sm.nvalid));
+        __syncthreads();
+        if (wave == 0) resolve_segments(sm, f, tm, cd.len, s0, N, nwv, max(1, cd.W / 3));
         __syncthreads();
         const int nv = __builtin_amdgcn_readfirstlane(sm.nvalid);
+        const bool multi = __builtin_amdgcn_readfirstlane(sm.multi) != 0;
+        // A tile is "simple" when every one of its windows is full: a small
+        // W, no curve end within reach, and the whole span valid, live and in
+        // one segment.  Its medians then come from per-window networks.
+        const bool simple = (kFeat & kFeatSmall) && nv == N && !multi &&
+                            __builtin_amdgcn_readfirstlane(sm.dead) == 0 && cd.W <= kSmallW &&
+                            scale != UMI_SCALE_MAD && cd.window_days == 0.0 && t0 >= h &&
+                            t1 + h <= cd.len && G == 1;
         int npad = 64;
         while (npad < nv) npad <<= 1;
         int levels = 6;
@@ -2383,23 +1882,26 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
         if (simple) {
             // every staged sample is valid: values and keys in index order
             uint32_t* keys = reinterpret_cast<uint32_t*>(wv.seq);
-            for (int i = tid; i < N; i += kMainThreads) {
-                const float x = f[i];
-                sm.xv[i] = x;
-                keys[i] = order_key(x);
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                const int i = tid + u * kMainThreads;
+                if (i < N) {
+                    sm.xv[i] = xs[u];
+                    keys[i] = order_key(xs[u]);
+                }
             }
             __syncthreads();
         } else {
         // --- compaction: values in index order, (key, index) for the sort ---
         const bool counted = (kFeat & kFeatSplit) && npad <= kMainThreads;
         uint32_t kmin = ~0u, kmax = 0u;
-        for (int i0 = wave * 64; i0 < nwv * 64; i0 += kMainThreads) {
-            const int i = i0 + lane;
-            if (i < N && sg[i] != -1) {
-                const float x = f[i];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int i = tid + u * kMainThreads;
+            if (i < N && ((sm.vbits[i >> 6] >> lane) & 1ull) != 0ull) {
                 const uint32_t ci = rank1(sm.vbits, sm.vpre, (uint32_t)i);
-                sm.xv[ci] = x;
-                const uint32_t key = order_key(x);
+                sm.xv[ci] = xs[u];
+                const uint32_t key = order_key(xs[u]);
                 if (counted) sm.sortbuf[ci] = ((uint64_t)key << 32) | ci;
                 kmin = min(kmin, key);
                 kmax = max(kmax, key);
@@ -2494,13 +1996,13 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
         // positions per lane ---
         if ((kFeat & kFeatSplit) && G > 1) {
             if (G == 2)
-                tile_windows_split<2, kFeat>(sm, wv, levels, nv, cd, h, s0, N, t0, t1, segid, alpha, c, iters,
+                tile_windows_split<2, kFeat>(sm, wv, levels, nv, cd, h, s0, N, t0, t1, multi, alpha, c, iters,
                                       scale, time, trend, median, detrended, scan_tile);
             else if (G == 4)
-                tile_windows_split<4, kFeat>(sm, wv, levels, nv, cd, h, s0, N, t0, t1, segid, alpha, c, iters,
+                tile_windows_split<4, kFeat>(sm, wv, levels, nv, cd, h, s0, N, t0, t1, multi, alpha, c, iters,
                                       scale, time, trend, median, detrended, scan_tile);
             else
-                tile_windows_split<8, kFeat>(sm, wv, levels, nv, cd, h, s0, N, t0, t1, segid, alpha, c, iters,
+                tile_windows_split<8, kFeat>(sm, wv, levels, nv, cd, h, s0, N, t0, t1, multi, alpha, c, iters,
                                       scale, time, trend, median, detrended, scan_tile);
             __syncthreads();
             continue;
@@ -2508,7 +2010,7 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
         if (core_tile) {
             const CoreLds cw = core_lds(cores + wave * core_floats, core_cap(cd.W));
             for (int g0 = (t0 & ~63) + wave * 64; g0 < t1; g0 += kMainThreads)
-                core_group<kFeat>(sm, cw, nv, npad, cd, h, s0, N, t0, t1, g0, segid, alpha,
+                core_group<kFeat>(sm, cw, nv, npad, cd, h, s0, N, t0, t1, g0, multi, alpha,
                                   c, iters, scale, time, trend, median, detrended);
             __syncthreads();
             continue;
@@ -2531,13 +2033,13 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
             }
         }
         if (R == 3)
-            tile_windows<3, kFeat>(sm, wv, levels, nv, cd, h, s0, N, t0, t1, segid, alpha, c, iters, scale,
+            tile_windows<3, kFeat>(sm, wv, levels, nv, cd, h, s0, N, t0, t1, multi, alpha, c, iters, scale,
                             simple, pm, pn, time, trend, median, detrended);
         else if (R == 2)
-            tile_windows<2, kFeat>(sm, wv, levels, nv, cd, h, s0, N, t0, t1, segid, alpha, c, iters, scale,
+            tile_windows<2, kFeat>(sm, wv, levels, nv, cd, h, s0, N, t0, t1, multi, alpha, c, iters, scale,
                             simple, pm, pn, time, trend, median, detrended);
         else
-            tile_windows<1, kFeat>(sm, wv, levels, nv, cd, h, s0, N, t0, t1, segid, alpha, c, iters, scale,
+            tile_windows<1, kFeat>(sm, wv, levels, nv, cd, h, s0, N, t0, t1, multi, alpha, c, iters, scale,
                             simple, pm, pn, time, trend, median, detrended);
         __syncthreads();
     }
@@ -2582,37 +2084,18 @@ __global__ __launch_bounds__(256) void umi_copy_kernel(CopyBatch cb)
 // ---------------------------------------------------------------------------
 // Host-side launch wrappers (the host library calls only these).
 
-// `one` (host memory, read before the call returns), for a batch of one curve
-// taking the chunked form: that curve's table entry, passed to the kernel by
-// value so that it need not read the staged table before its first step.
-hipError_t launch_prepass(const float* flux, const double* time, uint8_t* block,
-                          const uint8_t* stage, int curve_one, int grid, int32_t* segid,
-                          int2* tiles, Counters* ctr, ChunkRec* recs, bool clear_queue, bool walk,
-                          const CurveDesc* one, hipStream_t stream)
+// The set-up of a batch: with clear_queue one launch over the staged table (a
+// staging block `stage`, or `block` itself in device memory).  Without, the
+// estimate launch takes the table by value (kSmallTable) and finds its tiles
+// itself: nothing to do.  Samples need no pass of their own, so the arrays of
+// the interface that described one stay as they are.
+hipError_t launch_prepass(const float*, const double*, uint8_t* block, const uint8_t* stage, int,
+                          int grid, int32_t*, int2* tiles, Counters* ctr, ChunkRec*,
+                          bool clear_queue, bool, const CurveDesc*, hipStream_t stream)
 {
-    if (grid <= 0) return hipSuccess;
-    // read the header and table from the staging block (and copy them into
-    // `block`), or from `block` itself
-    const uint8_t* src = stage ? stage : block;
-    uint8_t* to = stage ? block : nullptr;
-    // one workgroup per curve, from curve_one (or the first) on
-    int32_t* trash = reinterpret_cast<int32_t*>(&ctr->trash);
-    if (walk && time)
-        hipLaunchKernelGGL((umi_prepass_walk_kernel<kPrepThreads, kPrepWalkItems, true>),
-                           dim3(grid), dim3(kPrepThreads), 0, stream, flux, time, src, to,
-                           curve_one < 0 ? 0 : curve_one, segid, tiles,
-                           clear_queue ? &ctr->queue : nullptr, trash);
-    else if (walk)
-        hipLaunchKernelGGL((umi_prepass_walk_kernel<kPrepThreads, kPrepWalkItems, false>),
-                           dim3(grid), dim3(kPrepThreads), 0, stream, flux, time, src, to,
-                           curve_one < 0 ? 0 : curve_one, segid, tiles,
-                           clear_queue ? &ctr->queue : nullptr, trash);
-    else
-        hipLaunchKernelGGL((umi_prepass_chunk_kernel<kPrepThreads, kPrepItems>), dim3(grid),
-                           dim3(kPrepThreads), 0, stream, flux, time, src, to, curve_one,
-                           segid, tiles, ctr, recs, clear_queue ? 1 : 0,
-                           one ? *one : CurveDesc{},
-                           one ? (one->len + kPrepChunk - 1) / kPrepChunk : -1);
+    if (grid <= 0 || !clear_queue) return hipSuccess;
+    hipLaunchKernelGGL(umi_setup_kernel, dim3(grid), dim3(kSetupThreads), 0, stream,
+                       stage ? stage : block, stage ? block : nullptr, tiles, &ctr->queue);
     return hipGetLastError();
 }
 
@@ -2624,12 +2107,25 @@ hipError_t launch_copy(const CopyBatch& cb, hipStream_t stream)
     return hipGetLastError();
 }
 
-hipError_t launch_main(const float* flux, const int32_t* segid, const BatchHeader* hdr,
+// Without a queue and a tile count, hdr and curves are host memory: a table of
+// at most kSmallTable curves, passed by value, one workgroup per tile.
+hipError_t launch_main(const float* flux, const int32_t*, const BatchHeader* hdr,
                        const CurveDesc* curves, const int2* tiles, int tile_first,
                        int tile_count, uint32_t* counter, int grid, float* trend, float* median,
                        int feat, hipStream_t stream)
 {
     if (grid <= 0) return hipSuccess;
+    SmallTable small;
+    small.n_curves = 0;
+    if (counter == nullptr && tile_count < 0) {
+        if (hdr->n_curves < 1 || hdr->n_curves > kSmallTable) return hipErrorInvalidValue;
+        small.n_curves = hdr->n_curves;
+        small.hdr = *hdr;
+        std::memcpy(small.c, curves, (size_t)hdr->n_curves * sizeof(CurveDesc));
+        grid = hdr->n_tiles;
+        hdr = nullptr;
+        curves = nullptr;
+    }
     // instances with sorted cores size their dynamic LDS for the batch's
     // largest core; it also holds the wavelet build's sequences
     const int core_floats = core_floats_for(feat >> kFeatBits);
@@ -2639,9 +2135,9 @@ hipError_t launch_main(const float* flux, const int32_t* segid, const BatchHeade
                                       (size_t)(kMainThreads / 64) * core_floats * sizeof(float))
                            : 0;
 #define UMI_LAUNCH_MAIN(F)                                                                       \
-    hipLaunchKernelGGL(umi_main_kernel<F>, dim3(grid), dim3(kMainThreads), dyn, stream, flux, segid, \
-                       hdr, curves, tiles, tile_first, tile_count, counter, trend, median,       \
-                       core_floats)
+    hipLaunchKernelGGL(umi_main_kernel<F>, dim3(grid), dim3(kMainThreads), dyn, stream, flux, hdr, \
+                        curves, tiles, tile_first, tile_count, counter, trend, median,       \
+                       core_floats, small)
     // the instances built: none, small windows, split tiles, everything but
     // cores; cores, cores and small windows, everything
     if (feat == 0)
