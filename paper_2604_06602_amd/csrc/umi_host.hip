@@ -91,20 +91,33 @@ int default_tile(int W)
     if (fill >= kMainThreads && rem < kMainThreads / 2) return fill - rem;
     return fill;
 }
+// The same with sorted cores, whose passes are a group of windows per wave:
+// always whole passes (200 curves of 19,440 at W = 1081: 728 us with tiles of
+// 968, 692 with 768).
+int core_tile(int tile)
+{
+    constexpr int kPass = kCoreGroup * kMainThreads / 64;
+    return tile >= kPass ? tile - tile % kPass : tile;
+}
 constexpr int kDefaultGroupsPerCU = 4;  // LDS (37.6 KB) allows four 512-thread groups per CU
 
 // The tile and groups per CU for window W in a batch of `samples` samples
 // (< 0: any size).  `sized` tells whether a batch-size row chose them.
-void tuned(int W, int64_t samples, int* tile, int* gpc, bool* sized = nullptr)
+void tuned(int W, int64_t samples, int* tile, int* gpc, bool* sized = nullptr,
+           bool* built_in = nullptr)
 {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     *tile = default_tile(W);
     *gpc = kDefaultGroupsPerCU;
     if (sized) *sized = false;
+    if (built_in) *built_in = true;
     for (const TuneRow& r : g_tune) {
         if (W > r.w_max) continue;
         if (r.samples_max > 0 && (samples < 0 || samples > r.samples_max)) continue;
-        if (r.tile > 0) *tile = std::min(r.tile, max_tile(W));
+        if (r.tile > 0) {
+            *tile = std::min(r.tile, max_tile(W));
+            if (built_in) *built_in = false;
+        }
         if (r.groups_per_cu > 0) *gpc = r.groups_per_cu;
         if (sized) *sized = r.samples_max > 0;
         break;
@@ -220,18 +233,29 @@ struct PackView {
     int feat = kFeatAll;      // estimate-kernel paths the batch needs (kFeat* bits)
 };
 
-// Tile sizes a batch too small to give every CU a tile falls back to, largest
-// first: at 512 each lane of a workgroup takes one window, at 256, 128 and 64
-// two, four and eight lanes share one.
-constexpr int kSmallBatchTiles[] = {1024, 512, 256, 128, 64};
+// Tile sizes a batch that does not fill the GPU falls back to, largest first.
+// Above 256 positions each lane takes a window (cores: a pair of lanes, 256
+// positions of a tile at a time), at 256, 128 and 64 two, four and eight lanes
+// share one.
+constexpr int kSmallBatchTiles[] = {1280, 1024, 768, 512, 320, 256, 128, 64};
 
-// Whether a curve's tiles take sorted cores: wide index windows with the
-// upper-RMS scale, one lane per window, and asymmetries whose two sides' cut-offs
-// are not far apart.
-bool takes_core(const CurveDesc& d, int32_t scale)
+// Workgroups per CU the GPU holds at once (LDS: four, with cores three), and
+// what a small batch may be cut into: as many tiles as run together, since a
+// tile's time hardly depends on how many others do; a second round of them
+// would.  Tiles below 256 positions only while every CU has at most one: they
+// halve a workgroup's windows, not what it does for the tile.  (16 curves of
+// 20,000, us a call: W = 361 640 tiles of 512 52, 320 of 1024 74, 848 of 384 64,
+// 1250 of 256 51; W = 25 1000 tiles of 320 30, 640 of 512 32, 320 of 1024 43.
+// One curve of 20,000 at W = 361: 157 tiles of 128 22.3, 63 of 320 33.)
+constexpr int kSmallBatchSlots = 4;
+constexpr int kSmallBatchCoreSlots = 3;
+
+// Whether a curve's tiles take sorted cores: wide windows with the upper-RMS scale, tiles that hold a group of windows (all but those of the
+// very widest), and asymmetries whose two sides' cut-offs are not far apart.
+bool core_window(int W, float alpha, int32_t scale)
 {
-    return d.W >= kCoreMinW && d.tile > kSplitMaxTile && scale == UMI_SCALE_UPPER_RMS &&
-           !(d.window_days > 0.0) && d.alpha >= 0.25f && d.alpha <= 16.0f;
+    return W >= kCoreMinW && max_tile(W) >= kCoreGroup && scale == UMI_SCALE_UPPER_RMS &&
+           alpha >= 0.25f && alpha <= 16.0f;
 }
 
 umi_status pack_into(const int64_t* offsets, const int64_t* lengths, int64_t n, const int32_t* W,
@@ -243,22 +267,23 @@ umi_status pack_into(const int64_t* offsets, const int64_t* lengths, int64_t n, 
     int64_t nord = 0, samples = 0;
     for (int64_t b = 0; b < n; ++b) samples += std::max<int64_t>(lengths[b], 0);
     bool any_sized = false;
+    auto is_core = [&](int64_t b) {
+        return core_window(W[b], o.alpha ? o.alpha[b] : alpha, o.scale);
+    };
     for (int64_t b = 0; b < n; ++b) {
         int t, g;
-        bool sized;
-        tuned(W[b], samples, &t, &g, &sized);
+        bool sized, built_in;
+        tuned(W[b], samples, &t, &g, &sized, &built_in);
+        if (built_in && is_core(b)) t = core_tile(t);
         any_sized = any_sized || sized;
         if (opt.tile > 0) t = std::min(opt.tile, max_tile(W[b]));
         tile_of[b] = t;
         if (lengths[b] > 0) order[nord++] = (int32_t)b;
     }
-    // A batch that the tuned tiles cut into fewer tiles than there are CUs
-    // (one curve, a quiet serving step) would leave most of the chip idle:
-    // smaller tiles spread its windows over more CUs, down to tiles that
-    // split each window over 2, 4 or 8 lanes.  Tiles above kSplitMaxTile
-    // give identical results whatever their size; split tiles agree with them
-    // to rounding.  An explicit launch tile, or a tuning row for this batch
-    // size, is kept as given.
+    // A batch that the tuned tiles cut into fewer tiles than the GPU runs at
+    // once (one curve, a quiet serving step) takes smaller ones
+    // (kSmallBatchTiles).  An explicit launch tile, or a tuning row for this
+    // batch size, is kept as given.
     auto count_tiles = [&](int cap) {
         int64_t t = 0;
         for (int64_t i = 0; i < nord; ++i) {
@@ -268,11 +293,16 @@ umi_status pack_into(const int64_t* offsets, const int64_t* lengths, int64_t n, 
         }
         return t;
     };
-    if (opt.tile == 0 && !any_sized && count_tiles(0) < n_cu) {
+    if (opt.tile == 0 && !any_sized) {
+        bool cores = false;
+        for (int64_t i = 0; i < nord; ++i) cores = cores || is_core(order[i]);
+        const int64_t slots = (int64_t)n_cu * (cores ? kSmallBatchCoreSlots : kSmallBatchSlots);
         for (int cap : kSmallBatchTiles) {
-            if (count_tiles(cap) > max_tiles) break;
+            if (cores && cap % (kCoreGroup * kMainThreads / 64) != 0 && cap > kSplitMaxTile)
+                continue;  // a round of groups nearly empty
+            const int64_t t = count_tiles(cap);
+            if (t > max_tiles || t > (cap < kSplitMaxTile ? n_cu : slots)) break;
             for (int64_t i = 0; i < nord; ++i) tile_of[order[i]] = std::min(tile_of[order[i]], cap);
-            if (count_tiles(0) >= n_cu) break;
         }
     }
     // costliest tiles first; ties by length, then by input position (a total
@@ -305,7 +335,7 @@ umi_status pack_into(const int64_t* offsets, const int64_t* lengths, int64_t n, 
         d.c = o.c ? o.c[b] : c;
         d.window_days = o.window_days ? o.window_days[b] : 0.0;
         d.chunk_base = (int32_t)out->nchunks;
-        d.core = takes_core(d, o.scale) ? 1 : 0;
+        d.core = is_core(b) ? 1 : 0;
         out->curve_tiles[i] = nt;
         out->ntiles += nt;
         out->nchunks += nch;
@@ -313,16 +343,21 @@ umi_status pack_into(const int64_t* offsets, const int64_t* lengths, int64_t n, 
     // the estimate-kernel paths this batch needs
     out->feat = o.scale == UMI_SCALE_MAD ? kFeatExtra : 0;
     int cap = 0;  // the batch's largest sorted core
+    bool split = false;
     for (int64_t i = 0; i < nord; ++i) {
         const CurveDesc& d = out->curves[i];
         if (d.W <= kSmallW) out->feat |= kFeatSmall;
-        if (d.tile <= kSplitMaxTile) out->feat |= kFeatSplit;
         if (d.window_days > 0.0) out->feat |= kFeatExtra;
+        if (d.tile <= kSplitMaxTile) {
+            out->feat |= kFeatSplit;
+            split = split || !d.core;
+        }
         if (d.core) {
             out->feat |= kFeatCore;
             cap = std::max(cap, core_cap(d.W));
         }
     }
+    if (!split) out->feat |= kFeatNoSplit;
     out->feat |= cap << kFeatBits;
     out->gpc = kDefaultGroupsPerCU;
     if (nord > 0) {
@@ -1135,10 +1170,9 @@ umi_status umi_plan_create(umi_plan** out, int64_t capacity, int64_t max_curves,
     // Tiles the plan must hold: the whole capacity at the smallest tile any
     // W <= max_W takes for batches of any size; batches at most samples_max
     // long at their batch-size rows' tiles; and the small-batch rule, which
-    // only halves tiles while a batch has fewer tiles than CUs, so it never
-    // needs more than 2 n_cu + max_curves.  With room for all of these, a run
-    // is cut exactly as the direct calls cut the same batch.
-    int64_t min_tile = std::min(umi::max_tile(max_W), umi::default_tile(max_W));
+    // cuts a batch into at most kSmallBatchSlots tiles per CU.  With room for
+    // all of these, a run is cut exactly as the direct calls cut the same batch.
+    int64_t min_tile = std::min(umi::max_tile(max_W), umi::core_tile(umi::default_tile(max_W)));
     int64_t sized_tiles = 0;
     {
         std::lock_guard<std::mutex> lk(umi::g_tune_mu);
@@ -1152,7 +1186,8 @@ umi_status umi_plan_create(umi_plan** out, int64_t capacity, int64_t max_curves,
         }
     }
     const int64_t max_tiles = std::max(capacity / std::max<int64_t>(1, min_tile),
-                                       std::max(sized_tiles, 2 * n_cu)) + max_curves;
+                                       std::max(sized_tiles, umi::kSmallBatchSlots * n_cu)) +
+                              max_curves;
     if (max_tiles > (int64_t)INT32_MAX)
         return umi::fail(UMI_ERR_UNSUPPORTED, "plan capacity needs too many tiles");
     // every curve adds at most one partial chunk

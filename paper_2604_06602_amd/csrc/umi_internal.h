@@ -21,26 +21,30 @@ constexpr int kFeatSplit = 2;                // split tiles (tile <= kSplitMaxTi
 constexpr int kFeatExtra = 4;                // MAD ablation, time windows
 constexpr int kFeatCore = 8;                 // sorted cores (wide windows)
 constexpr int kFeatAll = kFeatSmall | kFeatSplit | kFeatExtra | kFeatCore;
+constexpr int kFeatNoSplit = 16;             // with kFeatSplit: the small tiles all take cores,
+                                             // so no instance with split windows is needed
 constexpr int kFeatBits = 8;                 // the batch's largest core stands above these
 
-// Sorted cores: 64 consecutive windows share all but at most 63 samples of
+// Sorted cores: 32 consecutive windows share all but at most 31 samples of
 // each; the core is that shared run, a whole number of blocks of kCoreBlock.
-// Narrower windows sum their samples directly: the edge samples and the blocks
-// at the break points come to about 90 whatever W (1,000 curves of 18,000:
-// W = 129 1.85 ms directly, 1.95 by cores; W = 145 2.00 and 1.83).
-constexpr int kCoreMinW = 137;
+// Narrower windows sum their samples directly: what a wave does for a group,
+// and the 33 edge and 16 block samples of a window's iteration, cost the same
+// whatever W (1,000 curves of 18,000: W = 109 1.51 ms directly, 1.57 by cores;
+// W = 121 1.64 and 1.51).
+constexpr int kCoreMinW = 117;
 constexpr int kCoreBlock = 8;
 // Waves per SIMD the core instances are built for: LDS (47 KB at W = 361)
 // allows three workgroups per CU, and 80 registers spill little; at 4 waves
 // (128 registers) two workgroups fit and W = 361 took 3.3 ms against 2.5.
 constexpr int kCoreWaves = 6;
-constexpr int kCoreEdge = 64 + kCoreBlock + 64;  // samples a wave sums one by one
+constexpr int kCoreGroup = 32;               // windows that share a core
+constexpr int kCoreEdge = 32 + kCoreBlock + 32;  // samples a wave sums one by one
 __host__ __device__ constexpr int core_cap(int W)
 {
-    return W > 63 ? W - 63 : 0;
+    return W >= kCoreGroup ? W - (kCoreGroup - 1) : 0;
 }
 // the search tree over nb blocks' first values: levels of every 4^k-th value,
-// each a whole number of fours
+// each a whole number of fours (the level of every value is the blocks' own)
 __host__ __device__ constexpr int core_levels(int nb)
 {
     int n = 1;
@@ -54,19 +58,21 @@ __host__ __device__ constexpr int core_level_len(int nb, int stride)
 __host__ __device__ constexpr int core_tree(int nb)
 {
     int len = 0;
-    for (int st = 1 << (2 * (core_levels(nb) - 1)); st > 0; st >>= 2) len += core_level_len(nb, st);
+    for (int st = 1 << (2 * (core_levels(nb) - 1)); st > 1; st >>= 2) len += core_level_len(nb, st);
     return len;
 }
 // floats of LDS one wave's core takes: values, edge samples, and the larger
-// of Phase 1's masks and the block table (search tree, five power sums per
+// of the rank marks and the block table (search tree, five power sums per
 // block edge)
-constexpr int kCoreRanks = 64;               // core ranks around the centre that Phase 1 masks
-constexpr int kCoreMaskWords = 4;            // words of an edge-sample mask (64 + 64 bits)
+constexpr int kCoreMin = 32;                 // samples of the smallest core (Phase 1's ranks lie inside)
+constexpr int kCoreMarks = kStageMax / 16;   // words of the rank marks (and of Phase 1's masks)
+static_assert(kCoreMarks >= 2 * 64, "masks fit");
+constexpr int kRankBytes = 2 * kStageMax;    // the tile's ranks, ahead of the waves' cores
 __host__ __device__ constexpr int core_floats_for(int cap)
 {
     const int nb = cap / kCoreBlock;
     const int table = core_tree(nb) + 5 * (nb + 1);
-    const int masks = kCoreRanks * kCoreMaskWords;
+    const int masks = kCoreMarks;
     return ((cap + 3) & ~3) + kCoreEdge + (((table > masks ? table : masks) + 3) & ~3);
 }
 

@@ -94,8 +94,19 @@ __device__ __forceinline__ float key_value(uint32_t k)
     return __uint_as_float(b);
 }
 
+// A pair of the tile sort, and of the sorted tile: the sample's totalOrder
+// key, in the sorted tile the sample itself, above its compacted index.
+__device__ __forceinline__ uint64_t sorted_pair(uint64_t keyed)
+{
+    return ((uint64_t)__float_as_uint(key_value((uint32_t)(keyed >> 32))) << 32) | (uint32_t)keyed;
+}
+
+__device__ __forceinline__ float sorted_value(uint64_t pair)
+{
+    return __uint_as_float((uint32_t)(pair >> 32));
+}
+
 struct MainSmem {
-    uint64_t sortbuf[kStageMax];          // (key << 32 | compacted index)
     float xv[kStageMax];                  // compacted valid samples
     uint64_t vbits[kWords];               // staged-sample validity
     uint32_t vpre[kWords];
@@ -110,17 +121,19 @@ struct MainSmem {
     uint32_t wsum[kMainThreads / 64];     // per wave: bucket counts of its threads
 };
 
-// The wavelet matrix over a tile's sorted ranks.  The same LDS first holds
-// the tile sort's bucket counters, and in instances with sorted cores the
-// waves' cores (tiles take one or the other).
+// The sorted tile and the wavelet matrix over its ranks.  The sequences' space
+// first holds the tile sort's bucket counters; tiles with sorted cores need
+// only the ranks, and the waves' cores take all the space behind those.
 struct Wavelet {
-    uint16_t seq[2][kStageMax];           // level sequences
+    uint16_t seq[2][kStageMax];           // level sequences; [0]: rank of each sample
     uint64_t bits[kStageLog2][kWords];    // level bit vectors
     uint32_t pre[kStageLog2][kWords];     // ones before each word
     uint32_t zeros[kStageLog2];           // zeros per level
+    uint64_t sortbuf[kStageMax];          // pairs, (key or value << 32 | compacted index)
 };
 constexpr int kBuckets = kStageMax;       // counters of the tile sort
-static_assert(sizeof(Wavelet) >= kBuckets * sizeof(uint32_t), "counters fit");
+static_assert(sizeof(Wavelet::seq) >= kBuckets * sizeof(uint32_t), "counters fit");
+static_assert(sizeof(Wavelet::seq[0]) == kRankBytes, "cores start behind the ranks");
 
 __device__ __forceinline__ uint32_t rank1(const uint64_t* bits, const uint32_t* pre, uint32_t i)
 {
@@ -407,14 +420,16 @@ __device__ __forceinline__ void bisquare_acc(float x, float k, float b, float be
     swv = __builtin_fmaf(w, v, swv);
 }
 
-// Eq. 4 in residual form: mu + sum(w v) / (k sum(w)), with a correctly
-// rounded division.  Every path uses this same expression, so paths that sum
-// in the same order agree bit for bit.  (The hardware reciprocal would do
-// here too -- the quotient is a correction of the order of the scale -- but
-// it changed the register assignment of the estimate loops for the worse.)
+// Eq. 4 in residual form: mu + sum(w v) / (k sum(w)), with the hardware
+// reciprocal (1 ulp): the quotient is a correction of the order of the scale,
+// so its last bit is far below the location's, and the errors against 64 bits
+// do not change (3.73e-8 at W = 25).  A correctly rounded division took ten
+// instructions more per window and iteration (2,000 x 40,000-70,000 samples at
+// W = 25: 2.56 ms against 2.46).  Every path uses this same expression, so
+// paths that sum in the same order agree bit for bit.
 __device__ __forceinline__ float mu_update(float mu, float swv, float sw, float k)
 {
-    return mu + swv / (sw * k);
+    return __builtin_fmaf(swv, __builtin_amdgcn_rcpf(sw * k), mu);
 }
 
 // Eq. 1: s = 0.6745 sqrt(ssq / n+), with the hardware square root and
@@ -553,7 +568,7 @@ __device__ __forceinline__ void upper_ssq_multi(const float* __restrict__ x, int
 __device__ __forceinline__ float window_value(const MainSmem& sm, const Wavelet& wv, int levels, uint32_t ca,
                                               uint32_t cb, uint32_t j)
 {
-    return key_value((uint32_t)(sm.sortbuf[wavelet_kth(wv, levels, ca, cb, j)] >> 32));
+    return sorted_value(wv.sortbuf[wavelet_kth(wv, levels, ca, cb, j)]);
 }
 
 // Scale ablation: the standard MAD, the lower median of |x - m| over a window
@@ -712,7 +727,7 @@ __device__ __forceinline__ void window_phase1(const MainSmem& sm, const Wavelet&
 {
     const uint32_t cb = ca + n;
     const uint32_t rk = wavelet_kth(wv, levels, ca, cb, (n - 1) >> 1);
-    m = key_value((uint32_t)(sm.sortbuf[rk] >> 32));
+    m = sorted_value(wv.sortbuf[rk]);
     if (scale == UMI_SCALE_MAD) {
         sc = window_mad(sm, wv, levels, ca, n, m);
         return;
@@ -722,14 +737,14 @@ __device__ __forceinline__ void window_phase1(const MainSmem& sm, const Wavelet&
     // to m in the sorted order); a galloping search: one probe without ties,
     // O(log) with many
     uint32_t rh = rk, hi = rk + 1, step = 1;
-    while (hi < (uint32_t)nv && key_value((uint32_t)(sm.sortbuf[hi] >> 32)) == m) {
+    while (hi < (uint32_t)nv && sorted_value(wv.sortbuf[hi]) == m) {
         rh = hi;
         hi = rh + (step <<= 1);
     }
     if (hi > (uint32_t)nv) hi = (uint32_t)nv;
     while (hi - rh > 1u) {  // last equal in [rh, hi)
         const uint32_t mid = (rh + hi) >> 1;
-        if (key_value((uint32_t)(sm.sortbuf[mid] >> 32)) == m)
+        if (sorted_value(wv.sortbuf[mid]) == m)
             rh = mid;
         else
             hi = mid;
@@ -741,15 +756,16 @@ __device__ __forceinline__ void window_phase1(const MainSmem& sm, const Wavelet&
     if (rh - rk <= 16u) {
         uint32_t tied = 0;
         for (uint32_t j = rk + 1; j <= rh; ++j)
-            tied += ((uint32_t)(sm.sortbuf[j] & 0xffffffffull) - ca < n) ? 1u : 0u;
+            tied += ((uint32_t)(wv.sortbuf[j] & 0xffffffffull) - ca < n) ? 1u : 0u;
         nplus = n - k - 1 - tied;
     } else {
         nplus = n - wavelet_count_less(wv, levels, ca, cb, rh + 1);
     }
 }
 
-// Sorts the tile's (key, index) pairs: sortbuf[0, npad) ascending, padded
-// with ~0, from xv[0, nv) and the keys' range in sm.kmin, sm.kmax; cnt holds
+// Sorts the tile's (key, index) pairs: sortbuf[0, npad) ascending, as (value,
+// index) pairs padded with ~0, and seq[0], the rank of each sample (with
+// `ranks` only that), from xv[0, nv) and the keys' range in sm.kmin, sm.kmax; cnt holds
 // kBuckets cleared counters.  The keys are dealt to kBuckets buckets of equal
 // key range (counted with LDS atomics, placed by a block scan), and each pair
 // then counts the pairs of its own bucket below it: seven barriers, where a
@@ -761,8 +777,9 @@ __device__ __forceinline__ void window_phase1(const MainSmem& sm, const Wavelet&
 // outliers) would count for longer than the network sorts; it takes the network.
 constexpr uint32_t kBucketMost = 96;
 
-__device__ __forceinline__ void sort_tile(MainSmem& sm, uint32_t* __restrict__ cnt, int nv, int npad)
+__device__ __forceinline__ void sort_tile(MainSmem& sm, Wavelet& wv, int nv, int npad, bool ranks)
 {
+    uint32_t* const cnt = reinterpret_cast<uint32_t*>(wv.seq);
     const int tid = thread_index();
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int kPer = kStageMax / kMainThreads;
@@ -783,23 +800,29 @@ __device__ __forceinline__ void sort_tile(MainSmem& sm, uint32_t* __restrict__ c
     if ((tid & 63) == 63) sm.wsum[wave] = incl;
     if (__syncthreads_or(max(max(c.x, c.y), max(c.z, c.w)) > kBucketMost)) {
         for (int i = tid; i < npad; i += kMainThreads)
-            sm.sortbuf[i] = i < nv ? ((uint64_t)order_key(sm.xv[i]) << 32) | (uint32_t)i : ~0ull;
+            wv.sortbuf[i] = i < nv ? ((uint64_t)order_key(sm.xv[i]) << 32) | (uint32_t)i : ~0ull;
         __syncthreads();
         for (int kk = 2; kk <= npad; kk <<= 1) {
             for (int jj = kk >> 1; jj > 0; jj >>= 1) {
                 for (int cix = tid; cix < (npad >> 1); cix += kMainThreads) {
                     const int i = 2 * cix - (cix & (jj - 1));
                     const int l = i + jj;
-                    const uint64_t a = sm.sortbuf[i], b = sm.sortbuf[l];
+                    const uint64_t a = wv.sortbuf[i], b = wv.sortbuf[l];
                     const bool asc = (i & kk) == 0;
                     if ((a > b) == asc) {
-                        sm.sortbuf[i] = b;
-                        sm.sortbuf[l] = a;
+                        wv.sortbuf[i] = b;
+                        wv.sortbuf[l] = a;
                     }
                 }
                 __syncthreads();
             }
         }
+        for (int i = tid; i < npad; i += kMainThreads) {
+            const uint64_t p = wv.sortbuf[i];
+            wv.seq[0][i < nv ? (uint32_t)p : (uint32_t)i] = (uint16_t)(i < nv ? i : npad - 1);
+            if (i < nv) wv.sortbuf[i] = sorted_pair(p);
+        }
+        __syncthreads();
         return;
     }
     uint32_t base = incl - own;
@@ -813,7 +836,7 @@ __device__ __forceinline__ void sort_tile(MainSmem& sm, uint32_t* __restrict__ c
         const int i = tid + q * kMainThreads;
         if (i < nv) {
             const uint32_t key = order_key(sm.xv[i]);
-            sm.sortbuf[cnt[(key - kmin) >> shift] + slot[q]] = ((uint64_t)key << 32) | (uint32_t)i;
+            wv.sortbuf[cnt[(key - kmin) >> shift] + slot[q]] = ((uint64_t)key << 32) | (uint32_t)i;
         }
     }
     __syncthreads();
@@ -823,12 +846,12 @@ __device__ __forceinline__ void sort_tile(MainSmem& sm, uint32_t* __restrict__ c
     for (int q = 0; q < kPer; ++q) {
         const int i = tid + q * kMainThreads;
         if (i < nv) {
-            e[q] = sm.sortbuf[i];
+            e[q] = wv.sortbuf[i];
             const uint32_t b = ((uint32_t)(e[q] >> 32) - kmin) >> shift;
             const uint32_t lo = cnt[b];
             const uint32_t hi = b + 1 < (uint32_t)kBuckets ? cnt[b + 1] : (uint32_t)nv;
             uint32_t r = lo;
-            for (uint32_t j = lo; j < hi; ++j) r += sm.sortbuf[j] < e[q] ? 1u : 0u;
+            for (uint32_t j = lo; j < hi; ++j) r += wv.sortbuf[j] < e[q] ? 1u : 0u;
             rank[q] = r;
         }
     }
@@ -836,19 +859,22 @@ __device__ __forceinline__ void sort_tile(MainSmem& sm, uint32_t* __restrict__ c
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
         const int i = tid + q * kMainThreads;
-        if (i < nv)
-            sm.sortbuf[rank[q]] = e[q];
-        else if (i < npad)
-            sm.sortbuf[i] = ~0ull;
+        if (i < nv) {
+            wv.seq[0][(uint32_t)e[q]] = (uint16_t)rank[q];
+            if (!ranks) wv.sortbuf[rank[q]] = sorted_pair(e[q]);
+        } else if (i < npad) {
+            wv.seq[0][i] = (uint16_t)(npad - 1);
+            wv.sortbuf[i] = ~0ull;
+        }
     }
     __syncthreads();
 }
 
 // sort_tile as a call, for the instances with every path: inlined there it
 // cost them 18 spilled registers (a replayed step of six curves, 89 us against 83).
-__device__ __noinline__ void sort_tile_call(MainSmem& sm, uint32_t* cnt, int nv, int npad)
+__device__ __noinline__ void sort_tile_call(MainSmem& sm, Wavelet& wv, int nv, int npad, bool ranks)
 {
-    sort_tile(sm, cnt, nv, npad);
+    sort_tile(sm, wv, nv, npad, ranks);
 }
 
 // The windows of one tile: each lane takes R consecutive output positions.
@@ -1038,7 +1064,7 @@ __device__ __forceinline__ uint32_t group_sum_u32(uint32_t v)
 // of log2(npad) levels of four barriers each for the whole tile.  The median
 // and n+ are the same integers as window_phase1's.
 template <int G>
-__device__ __forceinline__ void window_phase1_scan(const MainSmem& sm, int nv, uint32_t ca,
+__device__ __forceinline__ void window_phase1_scan(const Wavelet& wv, int nv, uint32_t ca,
                                                    uint32_t n, float& m, uint32_t& nplus)
 {
     const uint32_t l = (uint32_t)thread_index() & (G - 1);
@@ -1049,7 +1075,7 @@ __device__ __forceinline__ void window_phase1_scan(const MainSmem& sm, int nv, u
         const int q0 = j0 + 8 * (int)l;
         uint64_t v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = sm.sortbuf[q0 + u];
+        for (int u = 0; u < 8; ++u) v[u] = wv.sortbuf[q0 + u];
         uint32_t bits = 0;
 #pragma unroll
         for (int u = 0; u < 8; ++u)
@@ -1080,25 +1106,25 @@ __device__ __forceinline__ void window_phase1_scan(const MainSmem& sm, int nv, u
         rk = group_sum_u32<G>(pos);
         break;
     }
-    m = key_value((uint32_t)(sm.sortbuf[rk] >> 32));
+    m = sorted_value(wv.sortbuf[rk]);
     // the points strictly above m: the window pairs after the last tile pair
     // numerically equal to m (ties sit next to m in the sorted order)
     uint32_t rh = rk, hi = rk + 1, step = 1;
-    while (hi < (uint32_t)nv && key_value((uint32_t)(sm.sortbuf[hi] >> 32)) == m) {
+    while (hi < (uint32_t)nv && sorted_value(wv.sortbuf[hi]) == m) {
         rh = hi;
         hi = rh + (step <<= 1);
     }
     if (hi > (uint32_t)nv) hi = (uint32_t)nv;
     while (hi - rh > 1u) {  // last equal in [rh, hi)
         const uint32_t mid = (rh + hi) >> 1;
-        if (key_value((uint32_t)(sm.sortbuf[mid] >> 32)) == m)
+        if (sorted_value(wv.sortbuf[mid]) == m)
             rh = mid;
         else
             hi = mid;
     }
     uint32_t tied = 0;
     for (uint32_t j = rk + 1 + l; j <= rh; j += G)
-        tied += ((uint32_t)(sm.sortbuf[j] & 0xffffffffull) - ca < n) ? 1u : 0u;
+        tied += ((uint32_t)(wv.sortbuf[j] & 0xffffffffull) - ca < n) ? 1u : 0u;
     tied = group_sum_u32<G>(tied);
     nplus = n - k - 1 - tied;
 }
@@ -1123,7 +1149,7 @@ __device__ __forceinline__ void tile_windows_split(const MainSmem& sm, const Wav
     uint32_t nplus = 0;
     if (live) {  // same on every lane
         if (scan)
-            window_phase1_scan<G>(sm, nv, ca, n, m, nplus);
+            window_phase1_scan<G>(wv, nv, ca, n, m, nplus);
         else
             window_phase1(sm, wv, levels, nv, scale, ca, n, m, sc, nplus);
     }
@@ -1170,33 +1196,41 @@ __device__ __forceinline__ void tile_windows_split(const MainSmem& sm, const Wav
 // ---------------------------------------------------------------------------
 // Wide windows by sorted cores.
 //
-// The 64 windows of an aligned group of consecutive positions share all but
-// at most 63 samples of each.  One wave takes a group, a window per lane: it
-// compacts the shared samples (the core) in value order out of the sorted
-// tile, in blocks of kCoreBlock, and keeps at every block edge the first five
-// power sums of the core's deviations from a value near its centre, counted
-// from the centre outwards.  Eq. 3's weight is a polynomial of degree four in
-// the sample on either side of the location and zero beyond the cut-offs, so
-// the sums of Eq. 4 over the blocks strictly between two of the three
-// break points (lower cut-off, location, upper cut-off) follow from two block
-// edges' power sums, shifted to the location; the block that holds a break
-// point and the window's own samples outside the core (its edge samples) are
-// summed one by one as in the direct sweep.  Eq. 1's sum follows likewise.
-// An iteration of a 361-sample window takes some 65 + 24 samples instead of
-// 361.
+// The 32 windows of an aligned group of consecutive positions share all but
+// at most 31 samples of each.  One wave takes a group, a pair of lanes per
+// window: it compacts the shared samples (the core) in value order out of the
+// sorted tile, in blocks of kCoreBlock, and keeps at every block edge the
+// first five power sums of the core's deviations from a value near its
+// centre, counted from the centre outwards.  Eq. 3's weight is a polynomial of
+// degree four in the sample on either side of the location and zero beyond
+// the cut-offs, so the sums of Eq. 4 over the blocks strictly between two of
+// the three break points (lower cut-off, location, upper cut-off) follow from
+// two block edges' power sums, shifted to the location; the block that holds
+// a break point and the window's own samples outside the core (its edge
+// samples) are summed one by one as in the direct sweep.  Eq. 1's sum follows
+// likewise.  An iteration of a 361-sample window takes some 33 + 16 samples
+// instead of 361.
 //
 // The polynomial is exact; what it costs is rounding where the location lies
-// far from the centre in units of the cut-off, so a lane sums its window (or
-// the part below the location) directly when it does, and when the scales
-// leave the range in which the powers neither overflow nor vanish.  A lane's
+// far from the centre in units of the cut-off, so a window (or the part below
+// its location) is summed directly when it does, and when the scales leave
+// the range in which the powers neither overflow nor vanish.  A window's
 // result depends only on the group and the window, never on the tile.
+//
+// What bounds it: VALU issue.  1,000 x 18,000 samples at W = 361: 14.0k lane
+// instructions per window and 4.2 ms with every sample summed directly, 5.0k
+// and 1.85 ms with groups of 64 windows (a lane each, twice the edge samples),
+// 4.6k and 1.75 ms with pairs of lanes, which also keep twice the waves busy
+// in a small batch (16 x 20,000: 98 us against 84).  The waves' cores take the
+// LDS that the tile sort is done with, so three workgroups fit a CU up to
+// W = 750 (W = 721: 1.42 ms with two, 1.11 with three for 500 x 18,000).
 
 struct CoreLds {
     float* cv;      // core samples in value order
-    float* edge;    // samples before the core (64 slots), the core's samples
-                    // beyond its last whole block, samples after the core
-    uint32_t* over; // Phase 1: kCoreRanks edge-sample masks, then (the same
-                    // space) tree and g
+    float* edge;    // samples before the core (32 slots), the core's samples
+                    // beyond its last whole block, samples after the core (32)
+    uint32_t* over; // the core's rank marks, then Phase 1's kCoreRanks masks,
+                    // then (the same space) tree and g
     float* tree;    // first value of each block, by a search tree (core_find)
     float* g;       // five power sums per block edge
 };
@@ -1236,57 +1270,78 @@ __device__ __forceinline__ float lane_value(float v, int lane)
 }
 
 // The wave's core in value order, nc samples at compacted positions
-// [cca, cca + nc), and the edge samples.
-__device__ __forceinline__ void core_collect(const MainSmem& sm, const CoreLds& cw, int nv, int npad,
-                                             uint32_t cca, int nc)
+// [cca, cca + nc), and the edge samples.  The core's samples mark their ranks
+// in a bit vector; the marks before a sample's own are its place.
+__device__ __forceinline__ void core_collect(const MainSmem& sm, const Wavelet& wv,
+                                             const CoreLds& cw, int nv, int cca, int nc)
 {
     const int lane = thread_index() & 63;
-    int base = 0;
-    for (int j0 = 0; j0 < nv && base < nc; j0 += 256) {
-        uint64_t e[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            e[u] = j0 + 64 * u < npad ? sm.sortbuf[j0 + 64 * u + lane] : ~0ull;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const bool in = (uint32_t)e[u] - cca < (uint32_t)nc;
-            const uint64_t m = __ballot(in);
-            const int at = base + (int)__builtin_amdgcn_mbcnt_hi(
-                                      (uint32_t)(m >> 32),
-                                      __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-            if (in) cw.cv[at] = key_value((uint32_t)(e[u] >> 32));
-            base += (int)__popcll(m);
-        }
+    const uint16_t* const rank = wv.seq[0] + cca;
+    const float* const x = sm.xv + cca;
+    uint2* const marks = reinterpret_cast<uint2*>(cw.over);  // (32 ranks, marks before them)
+    marks[lane] = make_uint2(0u, 0u);
+    wave_lds_sync();
+#pragma unroll 4
+    for (int j = lane; j < nc; j += 64) {
+        const uint32_t r = rank[j];
+        atomicOr(&marks[r >> 5].x, 1u << (r & 31u));
+    }
+    wave_lds_sync();
+    const uint32_t c = (uint32_t)__popc(marks[lane].x);
+    marks[lane].y = wave_scan(c) - c;
+    wave_lds_sync();
+#pragma unroll 4
+    for (int j = lane; j < nc; j += 64) {
+        const uint32_t r = rank[j];
+        const uint2 b = marks[r >> 5];
+        cw.cv[b.y + (uint32_t)__popc(b.x & ((1u << (r & 31u)) - 1u))] = x[j];
     }
     wave_lds_sync();
     const int rem = nc & (kCoreBlock - 1);
-    const int l = (int)cca - 64 + lane, r = (int)cca + nc + lane;
-    cw.edge[lane] = l >= 0 ? sm.xv[l] : 0.0f;
-    if (lane < rem) cw.edge[64 + lane] = cw.cv[nc - rem + lane];
-    cw.edge[64 + rem + lane] = r < nv ? sm.xv[r] : 0.0f;
+    const int i = cca - 32 + lane + (lane < 32 ? 0 : nc);
+    cw.edge[lane + (lane < 32 ? 0 : rem)] = i >= 0 && i < nv ? sm.xv[i] : 0.0f;
+    if (lane < rem) cw.edge[32 + lane] = cw.cv[nc - rem + lane];
     wave_lds_sync();
+}
+static_assert(kStageMax == 64 * 32, "a word of marks per lane");
+
+// What a curve's alpha fixes for its groups, formed once per tile.
+struct CoreParams {
+    float kA, beta;   // A = (1 + alpha)/2 and B/A of the folded residual
+    float inv_alpha;  // the lower cut-off in units of the upper one
+    float quantile;   // of the core, where its centre is taken: about half-way
+                      // from the median to where the iterations end
+};
+
+__device__ __forceinline__ CoreParams core_params(float alpha)
+{
+    CoreParams q;
+    q.kA = 0.5f * (1.0f + alpha);
+    q.beta = (1.0f - alpha) / (1.0f + alpha);
+    q.inv_alpha = 1.0f / alpha;
+    q.quantile =
+        alpha > 1.0f ? __builtin_fminf(0.5f + 0.1f * __builtin_log2f(alpha), 0.8f) : 0.5f;
+    return q;
 }
 
 // The core's block table and power sums.  False when the deviations' scale
 // is unusable.
-__device__ __forceinline__ bool core_build(const CoreLds& cw, int nc, float alpha, float& centre,
+__device__ __forceinline__ bool core_build(const CoreLds& cw, int nc, float quantile, float& centre,
                                            float& unit)
 {
     const int lane = thread_index() & 63;
     const int nb = nc / kCoreBlock;
     {
         float* t = cw.tree;
-        for (int st = 1 << (2 * (core_levels(nb) - 1)); st > 0; st >>= 2) {
+        for (int st = 1 << (2 * (core_levels(nb) - 1)); st > 1; st >>= 2) {
             const int len = core_level_len(nb, st);
             for (int i = lane; i < len; i += 64)
                 t[i] = i * st < nb ? cw.cv[kCoreBlock * i * st] : __builtin_nanf("");
             t += len;
         }
     }
-    // a centre about half-way from the median to where the iterations end
-    // (above it for alpha > 1), and a power of two near the core's spread
-    const float qf = alpha > 1.0f ? __builtin_fminf(0.5f + 0.1f * __builtin_log2f(alpha), 0.8f) : 0.5f;
-    const int cq = (int)(qf * (float)nc);
+    // the centre, and a power of two near the core's spread
+    const int cq = (int)(quantile * (float)nc);
     centre = cw.cv[cq];
     const float spread = cw.cv[(27 * nc) >> 5] - cw.cv[(5 * nc) >> 5];
     const int ex = __builtin_amdgcn_frexp_expf(spread);
@@ -1316,11 +1371,14 @@ __device__ __forceinline__ bool core_build(const CoreLds& cw, int nc, float alph
                 s[4] = __builtin_fmaf(d4, d, s[4]);
             }
         }
+        const bool more = r0 + 32 < max(nb - bc, bc);
 #pragma unroll
         for (int k = 0; k < 5; ++k) {
             const float t = half_scan(s[k]) + carry[k];
-            const float lo = lane_value(t, 31), hi = lane_value(t, 63);
-            carry[k] = up ? lo : hi;
+            if (more) {
+                const float lo = lane_value(t, 31), hi = lane_value(t, 63);
+                carry[k] = up ? lo : hi;
+            }
             if (act) cw.g[5 * (up ? b + 1 : b) + k] = up ? t : -t;
         }
     }
@@ -1329,20 +1387,8 @@ __device__ __forceinline__ bool core_build(const CoreLds& cw, int nc, float alph
     return true;
 }
 
-// Phase 1 (Section 2.1) of a group's windows.  A window is the core plus at
-// most 63 edge samples, so its median lies at one of the kCoreRanks core
-// samples around the core's middle, or between two of them.  For each of
-// those core ranks the wave forms the set of edge samples below that core sample (a bit
-// mask: the edge samples' ranks by binary search, set in LDS, then a prefix
-// "or" over the lanes); a window counts its own ones with a mask of its edge
-// samples, and a binary search over the ranks finds the core sample at or
-// below the median.  The median is that sample or one of the few edge samples
-// between it and the next.  No tile-wide structure beyond the sorted tile.
-// Values compare as floats; a median of zero takes its sign by counting.
-// Windows without a core walk the sorted tile.  Also n+ of Eq. 1.  Against the
-// wavelet matrix (a build of 44 barriers, then a descent per window): 1,000 x
-// 18,000 samples at W = 361 without iterations 1.50 -> 0.88 ms.
-__device__ __forceinline__ uint32_t wave_or_scan(uint32_t v)
+// Inclusive "or" over each half of the wave, and over the wave.
+__device__ __forceinline__ uint32_t half_or_scan(uint32_t v)
 {
 #define UMI_STEP(CTRL, ROWS)                                                                       \
     v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false)
@@ -1351,83 +1397,88 @@ __device__ __forceinline__ uint32_t wave_or_scan(uint32_t v)
     UMI_STEP(0x114, 0xF);
     UMI_STEP(0x118, 0xF);
     UMI_STEP(0x142, 0xA);
-    UMI_STEP(0x143, 0xC);
 #undef UMI_STEP
     return v;
 }
 
-// bits [lo, hi) of word w of a bit vector
-__device__ __forceinline__ uint32_t range_word(int lo, int hi, int w)
+__device__ __forceinline__ uint32_t wave_or_scan(uint32_t v)
 {
-    const int a = min(max(lo - 32 * w, 0), 32), b = min(max(hi - 32 * w, 0), 32);
-    const uint32_t up = b >= 32 ? ~0u : (1u << b) - 1u;
-    const uint32_t dn = a >= 32 ? ~0u : (1u << a) - 1u;
-    return up & ~dn;
+    v = half_or_scan(v);
+    return v | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);
 }
 
-__device__ __forceinline__ void core_phase1(const MainSmem& sm, const CoreLds& cw, int nv,
-                                            bool core, int nc, int cca, bool live, uint32_t ca,
-                                            uint32_t n, float& m, uint32_t& nplus)
+// Phase 1 (Section 2.1) of a group's windows.  A window is the core plus at
+// most 31 edge samples (63 with time windows, which differ in length), so its
+// median lies at one of the kRanks core samples around the core's middle, or
+// between two of them.  For each of
+// those core ranks the wave forms the set of edge samples below that core
+// sample (a bit mask: the edge samples' ranks by binary search, set in LDS,
+// then a prefix "or" over the lanes); a window counts its own ones with a mask
+// of its edge samples, and a binary search over the ranks finds the core
+// sample at or below the median.  The median is that sample or one of the few
+// edge samples between it and the next.  No tile-wide structure beyond the
+// sorted tile.  Values compare as floats; a median of zero takes its sign by
+// counting.  Windows without a core bisect the ranks.  Also n+ of Eq. 1.
+// Against the wavelet matrix (a build of 44 barriers, then a descent per
+// window): 1,000 x 18,000 samples at W = 361 without iterations 1.50 -> 0.88 ms.
+template <int kRanks>
+__device__ __forceinline__ void core_phase1(const MainSmem& sm, const Wavelet& wv,
+                                            const CoreLds& cw, int nv,
+                                            bool core, bool fits, int nc, int cca, bool live,
+                                            uint32_t ca, uint32_t n, float& m, uint32_t& nplus)
 {
+    static_assert(kRanks == 32 || kRanks == 64, "a rank per lane of a wave or of its half");
     const int lane = thread_index() & 63;
     const int k = (int)((n - 1) >> 1);
     bool found = false, zero = false;
     if (core) {
-        const int r0 = (nc >> 1) - kCoreRanks / 2;
+        const int r0 = (nc >> 1) - kRanks / 2;
         const float* const mid = cw.cv + r0;
-        // masks: lane r's holds the edge samples below core rank r0 + r
-#pragma unroll
-        for (int w = 0; w < kCoreMaskWords; ++w) cw.over[kCoreMaskWords * lane + w] = 0u;
         const int rem = nc & (kCoreBlock - 1);
-        const float e[2] = {cw.edge[lane], cw.edge[64 + rem + lane]};
-        int rk[2] = {0, 0};
+        // masks of core rank r0 + r: words 2r (samples before the core) and
+        // 2r + 1 (after it)
+        cw.over[lane] = 0u;
+        if (kRanks == 64) cw.over[64 + lane] = 0u;
+        const int word = lane >> 5, slot = lane & 31;
+        const float e = cw.edge[lane + (word ? rem : 0)];
+        int rk = 0;
 #pragma unroll
-        for (int st = kCoreRanks / 2; st > 0; st >>= 1) {
-#pragma unroll
-            for (int q = 0; q < 2; ++q) rk[q] += mid[rk[q] + st - 1] < e[q] ? st : 0;
+        for (int st = kRanks / 2; st > 0; st >>= 1) rk += mid[rk + st - 1] < e ? st : 0;
+        rk += mid[rk] < e ? 1 : 0;
+        wave_lds_sync();
+        if (rk < kRanks) atomicOr(&cw.over[2 * rk + word], 1u << slot);
+        wave_lds_sync();
+        if (kRanks == 32) {
+            const uint32_t below = half_or_scan(cw.over[2 * slot + word]);
+            wave_lds_sync();
+            cw.over[2 * slot + word] = below;
+        } else {
+            const uint32_t b0 = wave_or_scan(cw.over[2 * lane]);
+            const uint32_t b1 = wave_or_scan(cw.over[2 * lane + 1]);
+            wave_lds_sync();
+            cw.over[2 * lane] = b0;
+            cw.over[2 * lane + 1] = b1;
         }
         wave_lds_sync();
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            rk[q] += mid[rk[q]] < e[q] ? 1 : 0;
-            if (rk[q] < kCoreRanks)
-                atomicOr(&cw.over[kCoreMaskWords * rk[q] + 2 * q + (lane >> 5)], 1u << (lane & 31));
-        }
-        wave_lds_sync();
-        uint32_t below[kCoreMaskWords], own[kCoreMaskWords];
-        const int nl = cca - (int)ca, ne = (int)n - nc;
-#pragma unroll
-        for (int w = 0; w < kCoreMaskWords; ++w) {
-            below[w] = wave_or_scan(cw.over[kCoreMaskWords * lane + w]);
-            own[w] = live ? range_word(64 - nl, 64 - nl + ne, w) : 0u;
-        }
-        wave_lds_sync();
-#pragma unroll
-        for (int w = 0; w < kCoreMaskWords; ++w) cw.over[kCoreMaskWords * lane + w] = below[w];
-        wave_lds_sync();
+        const int nl = cca - (int)ca, nr = (int)n - nc - nl;
+        const uint32_t own_l = live && fits && nl > 0 ? ~0u << (32 - nl) : 0u;
+        const uint32_t own_r = live && fits && nr > 0 ? ~0u >> (32 - nr) : 0u;
         // the last rank r (from r0) with rank + own edge samples below <= k
+        const uint2* const masks = reinterpret_cast<const uint2*>(cw.over);
         int r = 0;
 #pragma unroll
-        for (int st = kCoreRanks / 2; st > 0; st >>= 1) {
-            int f = r0 + r + st;
-#pragma unroll
-            for (int w = 0; w < kCoreMaskWords; ++w)
-                f += __popc(cw.over[kCoreMaskWords * (r + st) + w] & own[w]);
+        for (int st = kRanks / 2; st > 0; st >>= 1) {
+            const uint2 b = masks[r + st];
+            const int f = r0 + r + st + __popc(b.x & own_l) + __popc(b.y & own_r);
             r += f <= k ? st : 0;
         }
-        if (live) {
+        if (live && fits) {
             // (past the last rank there is no gap: the median is that core
             // sample, as no edge sample lies below it)
-            int f = r0 + r;
-            const int r1 = min(r + 1, kCoreRanks - 1);
-            uint32_t gap[kCoreMaskWords];
-#pragma unroll
-            for (int w = 0; w < kCoreMaskWords; ++w) {
-                const uint32_t lo = cw.over[kCoreMaskWords * r + w] & own[w];
-                gap[w] = cw.over[kCoreMaskWords * r1 + w] & own[w] & ~lo;
-                f += __popc(lo);
-            }
-            int t = k - f;  // 0: the core sample; else the t-th of the gap
+            const uint2 b0 = masks[r], b1 = masks[min(r + 1, kRanks - 1)];
+            const uint32_t lo_l = b0.x & own_l, lo_r = b0.y & own_r;
+            // 0: the core sample; else the t-th of the gap
+            int t = k - (r0 + r + __popc(lo_l) + __popc(lo_r));
             m = mid[r];
             nplus = n - (uint32_t)k - 1u;
             float last = -__builtin_inff();
@@ -1435,9 +1486,10 @@ __device__ __forceinline__ void core_phase1(const MainSmem& sm, const CoreLds& c
                 float least = __builtin_inff();
                 int cnt = 0;
 #pragma unroll
-                for (int w = 0; w < kCoreMaskWords; ++w) {
-                    for (uint32_t b = gap[w]; b != 0; b &= b - 1) {
-                        const float x = cw.edge[32 * w + (w < 2 ? 0 : rem) + (int)__builtin_ctz(b)];
+                for (int w = 0; w < 2; ++w) {
+                    for (uint32_t b = w ? b1.y & own_r & ~lo_r : b1.x & own_l & ~lo_l; b != 0;
+                         b &= b - 1) {
+                        const float x = cw.edge[(w ? 32 + rem : 0) + (int)__builtin_ctz(b)];
                         if (x > last) {
                             cnt = x < least ? 1 : cnt + (x == least ? 1 : 0);
                             least = __builtin_fminf(least, x);
@@ -1480,21 +1532,22 @@ __device__ __forceinline__ void core_phase1(const MainSmem& sm, const CoreLds& c
     }
     const float* const x = sm.xv + ca;
     if (live && !found) {
-        // the (k + 1)-th pair of the window in the sorted tile (padded to a
-        // multiple of 64 with pairs of no window)
-        int need = k + 1;
-        for (int j0 = 0; j0 < nv; j0 += 8) {
-            uint64_t p[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) p[u] = sm.sortbuf[j0 + u];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const bool in = (uint32_t)p[u] - ca < n;
-                if (in && need == 1) m = key_value((uint32_t)(p[u] >> 32));
-                need -= in ? 1 : 0;
-            }
-            if (need <= 0) break;
+        // the rank of which k + 1 of the window's samples are at or below, by
+        // bisection, and its sample
+        const uint16_t* const rank = wv.seq[0] + ca;
+        int lo = 0, hi = nv - 1;
+        while (lo < hi) {
+            const int at = (lo + hi) >> 1;
+            int below = 0;
+#pragma unroll 8
+            for (int j = 0; j < (int)n; ++j) below += (int)rank[j] <= at ? 1 : 0;
+            if (below > k)
+                hi = at;
+            else
+                lo = at + 1;
         }
+        for (int j = 0; j < (int)n; ++j)
+            if ((int)rank[j] == lo) m = x[j];
         zero = true;
     }
     if (zero) {
@@ -1509,25 +1562,26 @@ __device__ __forceinline__ void core_phase1(const MainSmem& sm, const CoreLds& c
     }
 }
 
-// The last block whose first value is <= each knot (0 where none is): four
+// The last block whose first value is <= the knot (0 where none is): four
 // values per level of the tree, the first of which needs no test (a level
-// holds every 4th value of the next; beyond the last value stands NaN).  One
-// 16-byte load per level where a binary search takes two dependent ones.
-template <int K>
-__device__ __forceinline__ void core_find(const float* __restrict__ tree, int nb,
-                                          const float (&knot)[K], int (&b)[K])
+// holds every 4th value of the next; beyond the last value stands NaN), and
+// at the end the blocks' own first values.  One load per level where a binary
+// search takes two dependent ones.
+__device__ __forceinline__ int core_find(const CoreLds& cw, int nb, float knot)
 {
-#pragma unroll
-    for (int i = 0; i < K; ++i) b[i] = 0;
-    for (int st = 1 << (2 * (core_levels(nb) - 1)); st > 0; st >>= 2) {
-#pragma unroll
-        for (int i = 0; i < K; ++i) {
-            const float4 v = reinterpret_cast<const float4*>(tree)[b[i]];
-            b[i] = 4 * b[i] + (v.y <= knot[i] ? 1 : 0) + (v.z <= knot[i] ? 1 : 0) +
-                   (v.w <= knot[i] ? 1 : 0);
-        }
+    int b = 0;
+    const float* tree = cw.tree;
+    for (int st = 1 << (2 * (core_levels(nb) - 1)); st > 1; st >>= 2) {
+        const float4 v = reinterpret_cast<const float4*>(tree)[b];
+        b = 4 * b + (v.y <= knot ? 1 : 0) + (v.z <= knot ? 1 : 0) + (v.w <= knot ? 1 : 0);
         tree += core_level_len(nb, st);
     }
+    b = 4 * b;
+    const float* const v = cw.cv + kCoreBlock * b;
+    const float v1 = v[kCoreBlock], v2 = v[2 * kCoreBlock], v3 = v[3 * kCoreBlock];
+    const bool c1 = v1 <= knot, c2 = c1 && v2 <= knot, c3 = c2 && v3 <= knot;
+    // (past the last block stand other values)
+    return min(b + (c1 ? 1 : 0) + (c2 ? 1 : 0) + (c3 ? 1 : 0), nb - 1);
 }
 
 // Sums of w and w z over blocks [e0, e1) with z = (d - delta) kappa, |z| < 1:
@@ -1549,30 +1603,52 @@ __device__ __forceinline__ void core_poly(const float* __restrict__ g, int e0, i
     swz = kappa * __builtin_fmaf(k2, __builtin_fmaf(k2, d[5], -2.0f * d[3]), d[1]);
 }
 
-// f over the samples of block b, in value order
+// f over this lane's half of block b, in value order
 template <class F>
-__device__ __forceinline__ void core_block(const float* __restrict__ cv, int b, F&& f)
+__device__ __forceinline__ void core_block(const float* __restrict__ cv, int b, int half, F&& f)
 {
-    float v[kCoreBlock];
-#pragma unroll
-    for (int q = 0; q < kCoreBlock; ++q) v[q] = cv[kCoreBlock * b + q];
-#pragma unroll
-    for (int q = 0; q < kCoreBlock; ++q) f(v[q]);
+    const float4 v = reinterpret_cast<const float4*>(cv)[2 * b + half];
+    f(v.x);
+    f(v.y);
+    f(v.z);
+    f(v.w);
+}
+
+// f over this lane's half of the ne samples from xe (every second one); even:
+// the wave's windows all have ne_u of them
+template <class F>
+__device__ __forceinline__ void core_edges(const float* __restrict__ xe, int half, int ne, int ne_u,
+                                           bool even, F&& f)
+{
+    const float* const x = xe + half;
+    if (even) {
+        const int pairs = ne_u >> 1;
+#pragma unroll 8
+        for (int j = 0; j < pairs; ++j) f(x[2 * j]);
+        if ((ne_u & 1) && half == 0) f(x[2 * pairs]);
+    } else {
+        for (int j = 0; j + half < ne; j += 2) f(x[j]);
+    }
 }
 
 // Furthest a location may lie from the core's centre, in units of the
 // cut-off of the side summed by power sums.
 constexpr float kCoreReach = 0.5f;
 
+// The windows of one group, a pair of lanes each: the lanes take every second
+// edge sample, half of each block summed one by one, and one side's power
+// sums; their sums meet by DPP, so both hold the same bits and iterate in step.
 template <int kFeat>
-__device__ __forceinline__ void core_group(const MainSmem& sm, const CoreLds& cw, int nv, int npad, const CurveDesc& cd, int h, int s0,
-                                           int N, int t0, int t1, int g0,
-                                           bool multi, float alpha, float c,
-                                           int iters, int scale, const double* __restrict__ time,
+__device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv, const CoreLds& cw,
+                                           int nv, const CurveDesc& cd, int h, int s0, int N, int t0,
+                                           int t1, int g0, bool multi, const CoreParams& q, float c,
+                                           int iters, const double* __restrict__ time,
                                            float* __restrict__ trend, float* __restrict__ median,
                                            float* __restrict__ detrended)
 {
-    const int p = g0 + (thread_index() & 63);
+    const int lane = thread_index() & 63;
+    const int half = lane & 1;
+    const int p = g0 + (lane >> 1);
     const bool mine = p >= t0 && p < t1;
     uint32_t ca = 0, n = 0;
     // the ranges of positions outside the tile count too (cut at the staged
@@ -1591,125 +1667,122 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const CoreLds& cw
         const int ccb = __builtin_amdgcn_readlane((int)(ca + n), lane_lo);
         const int nc = min(ccb - cca, core_cap(cd.W));
         float centre = 0.0f, unit = 1.0f;
-        bool core = nc >= kCoreRanks;
-        if (core) core_collect(sm, cw, nv, npad, (uint32_t)cca, nc);
-        core_phase1(sm, cw, nv, core, nc, cca, live, ca, n, m, nplus);
-        core = core && core_build(cw, nc, alpha, centre, unit);
+        bool core = nc >= kCoreMin;
+        if (core) core_collect(sm, wv, cw, nv, cca, nc);
+        // nl edge samples before the core, nr after it; windows that differ in
+        // length (time windows) may have more than there are slots
+        const int nl = live ? cca - (int)ca : 0, nr = live ? (int)n - nc - nl : 0;
+        const bool timed = (kFeat & kFeatExtra) && cd.window_days > 0.0;
+        const bool wide = timed && nc >= 2 * kCoreMin;
+        const bool fits = !timed || ((uint32_t)nl <= 32u && (uint32_t)nr <= 32u &&
+                                     nl + nr < (wide ? 2 * kCoreGroup : kCoreGroup));
+        if ((kFeat & kFeatExtra) && wide)
+            core_phase1<2 * kCoreGroup>(sm, wv, cw, nv, core, fits, nc, cca, live, ca, n, m, nplus);
+        else
+            core_phase1<kCoreGroup>(sm, wv, cw, nv, core, fits, nc, cca, live, ca, n, m, nplus);
+        core = core && core_build(cw, nc, q.quantile, centre, unit);
         const int nb = nc / kCoreBlock;
-        // samples to sum one by one: nl before the core, what the core holds
-        // beyond its last whole block, and those after the core
-        const int nl = live ? cca - (int)ca : 0;
-        const float* const xe = cw.edge + 64 - nl;
-        const int ne = live ? (int)n - nb * kCoreBlock : 0;
-        const int src = (int)__builtin_ctzll(live_m);
-        const int ne_u = __builtin_amdgcn_readlane(ne, src);
+        // samples to sum one by one: those before the core, what the core
+        // holds beyond its last whole block, and those after the core
+        const bool edges = live && fits;
+        const float* const xe = cw.edge + 32 - (edges ? nl : 0);
+        const int ne = edges ? (int)n - nb * kCoreBlock : 0;
+        const int ne_u = __builtin_amdgcn_readlane(ne, (int)__builtin_ctzll(live_m));
         const bool even = __all(!live || ne == ne_u);
+        const float* const x = sm.xv + ca;
 
         // Phase 2 (Eq. 1)
-        float ssq = 0.0f;
+        float ssq = 0.0f, rest = 0.0f;
+        auto up2 = [&](float v) {
+            const float d = __builtin_fmaxf(v - m, 0.0f);
+            ssq = __builtin_fmaf(d, d, ssq);
+        };
         bool direct = true;
         if (core) {
-            auto up2 = [&](float x) {
-                const float d = __builtin_fmaxf(x - m, 0.0f);
-                ssq = __builtin_fmaf(d, d, ssq);
-            };
-            if (even) {
-#pragma unroll 8
-                for (int j = 0; j < ne_u; ++j) up2(xe[j]);
-            } else {
-                for (int j = 0; j < ne; ++j) up2(xe[j]);
-            }
-            const float knot[1] = {m};
-            int b[1];
-            core_find<1>(cw.tree, nb, knot, b);
-            core_block(cw.cv, b[0], up2);
-            const int e = b[0] + 1;
+            core_edges(xe, half, ne, ne_u, even, up2);
+            const int b = core_find(cw, nb, m);
+            core_block(cw.cv, b, half, up2);
+            const int e = b + 1;
             const float d0 = (float)(kCoreBlock * (nb - e));
             const float d1 = cw.g[5 * nb] - cw.g[5 * e];
             const float d2 = cw.g[5 * nb + 1] - cw.g[5 * e + 1];
             const float delta = (m - centre) * unit;
             const float whole = __builtin_fmaf(delta * delta, d0, d2);
-            const float rest = __builtin_fmaf(-2.0f * delta, d1, whole);
+            const float sum = __builtin_fmaf(-2.0f * delta, d1, whole);
             const float back = 1.0f / unit;  // a power of two
-            ssq += rest * back * back;
-            direct = !(rest >= 0.125f * whole && whole < 1e30f);
+            rest = sum * back * back;
+            direct = !(fits && sum >= 0.125f * whole && whole < 1e30f);
         }
-        if (live && direct) ssq = upper_ssq(sm.xv, (int)ca, (int)n, m);
+        if (live && direct) {
+            ssq = 0.0f;
+            rest = 0.0f;
+            strided_sweep<2>(x, half, (int)n, up2);
+        }
+        ssq = group_sum<2>(ssq) + rest;
         if (live && nplus > 0) sc = upper_scale(ssq, nplus);
 
         // Phase 3 (Eqs. 2-4)
-        const float kA = 0.5f * (1.0f + alpha);
-        const float beta = (1.0f - alpha) / (1.0f + alpha);
         mu = m;
         float k = 0.0f;
         bool act = false;
         if (live && sc > 0.0f && iters > 0) {
-            const float kk = bisquare_k(kA, c, sc);
+            const float kk = bisquare_k(q.kA, c, sc);
             if (isfinite(kk)) {
                 k = kk;
                 act = true;
             }
         }
-        const float cs = c * sc;          // upper cut-off
-        const float cl = cs / alpha;      // lower cut-off
-        const float ka = 1.0f / (cs * unit);  // per unit of the power sums
-        const float kb = alpha * ka;
+        const float beta = q.beta;
+        const float cs = c * sc;               // upper cut-off
+        const float cl = cs * q.inv_alpha;     // lower cut-off
+        // their inverses per unit of the power sums
+        const float ka = __builtin_amdgcn_rcpf(cs * unit);
+        const float kb = __builtin_amdgcn_rcpf(cl * unit);
         const bool scaled = ka > 1e-4f && ka < 1e4f;
         const float vmax = core ? cw.cv[kCoreBlock * nb - 1] : 0.0f;
+        // this lane's side of the power sums: above the location, or below
+        const float kside = half ? ka : kb, fside = half ? q.kA : q.kA * q.inv_alpha;
+        const float knot = half ? 0.0f : cl;
         for (int it = 0; it < iters; ++it) {
             const float bb = -mu * k;
             float sw = 0.0f, swv = 0.0f;
+            auto acc = [&](float v) { bisquare_acc(v, k, bb, beta, sw, swv); };
             direct = true;
             if (core) {
-                auto acc = [&](float x) { bisquare_acc(x, k, bb, beta, sw, swv); };
-                if (even) {
-#pragma unroll 8
-                    for (int j = 0; j < ne_u; ++j) acc(xe[j]);
-                } else {
-                    for (int j = 0; j < ne; ++j) acc(xe[j]);
-                }
-                const float knot[2] = {mu - cl, mu};
-                int b[3];
-                {
-                    int b2[2];
-                    core_find<2>(cw.tree, nb, knot, b2);
-                    b[0] = b2[0];
-                    b[1] = b2[1];
-                }
+                core_edges(xe, half, ne, ne_u, even, acc);
+                const int bm = core_find(cw, nb, mu - knot);
+                const int bo = __float_as_int(dpp_xor1(__int_as_float(bm)));
+                const int b0 = half ? bo : bm, b1 = half ? bm : bo;
                 // the upper cut-off is rarely inside the core: past its
                 // largest value every block above the location is whole
-                b[2] = nb;
+                int b2 = nb;
                 if (!(mu + cs >= vmax)) {
-                    const float hi[1] = {mu + cs};
-                    int b1[1];
-                    core_find<1>(cw.tree, nb, hi, b1);
-                    b[2] = b1[0];
-                    if (b[2] != b[1]) core_block(cw.cv, b[2], acc);
+                    b2 = core_find(cw, nb, mu + cs);
+                    if (b2 != b1) core_block(cw.cv, b2, half, acc);
                 }
-                core_block(cw.cv, b[0], acc);
-                if (b[1] != b[0]) core_block(cw.cv, b[1], acc);
+                core_block(cw.cv, b0, half, acc);
+                if (b1 != b0) core_block(cw.cv, b1, half, acc);
                 const float delta = (mu - centre) * unit;
                 const float far = __builtin_fabsf(delta);
-                const int eb = min(b[0] + 1, b[1]), ea = min(b[1] + 1, b[2]);
-                float pw, pz;
-                core_poly(cw.g, ea, b[2], delta, ka, pw, pz);
-                sw += pw;
-                swv = __builtin_fmaf(kA, pz, swv);
-                if (far * kb <= kCoreReach) {
-                    core_poly(cw.g, eb, b[1], delta, kb, pw, pz);
-                    sw += pw;
-                    swv = __builtin_fmaf(kA / alpha, pz, swv);
-                } else {
-                    for (int q = eb; q < b[1]; ++q) core_block(cw.cv, q, acc);
+                int e0 = half ? min(b1 + 1, b2) : min(b0 + 1, b1);
+                const int e1 = half ? b2 : b1;
+                if (!(far * kb <= kCoreReach)) {
+                    // too far for the side below: block by block
+                    for (int b = min(b0 + 1, b1); b < b1; ++b) core_block(cw.cv, b, half, acc);
+                    e0 = half ? e0 : e1;
                 }
-                direct = !(scaled && far * ka <= kCoreReach && sw > 0.03125f * (float)(int)n);
+                float pw, pz;
+                core_poly(cw.g, e0, e1, delta, kside, pw, pz);
+                sw = group_sum<2>(sw + pw);
+                swv = group_sum<2>(__builtin_fmaf(fside, pz, swv));
+                direct = !(fits && scaled && far * ka <= kCoreReach && sw > 0.03125f * (float)(int)n);
             }
             if (act && direct) {
                 sw = 0.0f;
                 swv = 0.0f;
-                const float* x = sm.xv + ca;
-#pragma unroll 8
-                for (int j = 0; j < (int)n; ++j) bisquare_acc(x[j], k, bb, beta, sw, swv);
+                strided_sweep<2>(x, half, (int)n, acc);
+                sw = group_sum<2>(sw);
+                swv = group_sum<2>(swv);
             }
             if (act) {
                 if (sw > 0.0f)
@@ -1722,9 +1795,11 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const CoreLds& cw
     }
     if (mine) {
         const float nanf_ = __builtin_nanf("");
-        trend[cd.off + p] = live ? mu : nanf_;
-        if (median) median[cd.off + p] = live ? m : nanf_;
-        if (detrended)
+        if (half == 0)
+            trend[cd.off + p] = live ? mu : nanf_;
+        else if (median)
+            median[cd.off + p] = live ? m : nanf_;
+        if (detrended && half == 1)
             detrended[cd.off + p] =
                 live ? sm.xv[rank1(sm.vbits, sm.vpre, (uint32_t)(p - s0))] / mu : nanf_;
     }
@@ -1859,7 +1934,7 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
             }
         }
         // lanes per window (1: R windows per lane)
-        const int G = (kFeat & kFeatSplit) ? split_lanes(cd.tile) : 1;
+        const int G = (kFeat & kFeatSplit) && !cd.core ? split_lanes(cd.tile) : 1;
         __syncthreads();
         if (wave == 0) resolve_segments(sm, f, tm, cd.len, s0, N, nwv, max(1, cd.W / 3));
         __syncthreads();
@@ -1893,7 +1968,6 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
             __syncthreads();
         } else {
         // --- compaction: values in index order, (key, index) for the sort ---
-        const bool counted = (kFeat & kFeatSplit) && npad <= kMainThreads;
         uint32_t kmin = ~0u, kmax = 0u;
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
@@ -1902,64 +1976,28 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
                 const uint32_t ci = rank1(sm.vbits, sm.vpre, (uint32_t)i);
                 sm.xv[ci] = xs[u];
                 const uint32_t key = order_key(xs[u]);
-                if (counted) sm.sortbuf[ci] = ((uint64_t)key << 32) | ci;
                 kmin = min(kmin, key);
                 kmax = max(kmax, key);
             }
         }
-        if (counted) {
-            for (int i = nv + tid; i < npad; i += kMainThreads) sm.sortbuf[i] = ~0ull;
-        } else {
-            kmin = wave_min(kmin);
-            kmax = wave_max(kmax);
-            if (lane == 63) {
-                atomicMin(&sm.kmin, kmin);
-                atomicMax(&sm.kmax, kmax);
-            }
-            // clear the tile sort's counters
-            reinterpret_cast<uint4*>(&wv)[tid] = make_uint4(0u, 0u, 0u, 0u);
+        kmin = wave_min(kmin);
+        kmax = wave_max(kmax);
+        if (lane == 63) {
+            atomicMin(&sm.kmin, kmin);
+            atomicMax(&sm.kmax, kmax);
         }
+        // clear the tile sort's counters
+        reinterpret_cast<uint4*>(&wv)[tid] = make_uint4(0u, 0u, 0u, 0u);
         __syncthreads();
 
-        if (counted) {
-            // --- a small tile: every element counts the elements below it ---
-            // The (key, index) pairs are distinct, so the counts are the
-            // ranks the sorting network would give, without a barrier per
-            // network stage; padding [nv, npad) already holds ~0.
-            uint64_t mine = 0;
-            uint32_t rank = 0;
-            if (tid < nv) {
-                mine = sm.sortbuf[tid];
-                // eight loads ahead of their compares; the padding up to the
-                // next multiple of eight (within npad) holds ~0 and counts 0
-                for (int j0 = 0; j0 < nv; j0 += 8) {
-                    uint64_t v[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) v[u] = sm.sortbuf[j0 + u];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) rank += v[u] < mine ? 1u : 0u;
-                }
-            }
-            __syncthreads();
-            if (tid < nv) sm.sortbuf[rank] = mine;
-            __syncthreads();
-        } else {
-            if (kFeat & kFeatExtra)
-                sort_tile_call(sm, reinterpret_cast<uint32_t*>(&wv), nv, npad);
-            else
-                sort_tile(sm, reinterpret_cast<uint32_t*>(&wv), nv, npad);
-        }
+        if (kFeat & kFeatExtra)
+            sort_tile_call(sm, wv, nv, npad, core_tile);
+        else
+            sort_tile(sm, wv, nv, npad, core_tile);
 
         // --- wavelet matrix over the sequence rank_of[compacted index]; split
         // tiles take their medians from the sorted tile directly ---
         if (!scan_tile && !core_tile) {
-        for (int r = tid; r < npad; r += kMainThreads) {
-            if (r < nv)
-                wv.seq[0][(uint32_t)(sm.sortbuf[r] & 0xffffffffull)] = (uint16_t)r;
-            else
-                wv.seq[0][r] = (uint16_t)(npad - 1);
-        }
-        __syncthreads();
         const int nwl = (npad >> 6) + 1;
         for (int l = 0; l < levels; ++l) {
             const uint16_t* cur = wv.seq[l & 1];
@@ -2008,10 +2046,12 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
             continue;
         }
         if (core_tile) {
-            const CoreLds cw = core_lds(cores + wave * core_floats, core_cap(cd.W));
-            for (int g0 = (t0 & ~63) + wave * 64; g0 < t1; g0 += kMainThreads)
-                core_group<kFeat>(sm, cw, nv, npad, cd, h, s0, N, t0, t1, g0, multi, alpha,
-                                  c, iters, scale, time, trend, median, detrended);
+            const CoreLds cw = core_lds(cores + kRankBytes / 4 + wave * core_floats, core_cap(cd.W));
+            const CoreParams cp = core_params(alpha);
+            for (int g0 = (t0 & -kCoreGroup) + wave * kCoreGroup; g0 < t1;
+                 g0 += kCoreGroup * (kMainThreads / 64))
+                core_group<kFeat>(sm, wv, cw, nv, cd, h, s0, N, t0, t1, g0, multi, cp, c,
+                                  iters, time, trend, median, detrended);
             __syncthreads();
             continue;
         }
@@ -2130,9 +2170,11 @@ hipError_t launch_main(const float* flux, const int32_t*, const BatchHeader* hdr
     // largest core; it also holds the wavelet build's sequences
     const int core_floats = core_floats_for(feat >> kFeatBits);
     feat &= (1 << kFeatBits) - 1;
+    if (feat & kFeatNoSplit) feat &= ~(kFeatSplit | kFeatNoSplit);
     const size_t dyn = (feat & kFeatCore)
                            ? std::max(sizeof(Wavelet),
-                                      (size_t)(kMainThreads / 64) * core_floats * sizeof(float))
+                                      kRankBytes + (size_t)(kMainThreads / 64) * core_floats *
+                                                       sizeof(float))
                            : 0;
 #define UMI_LAUNCH_MAIN(F)                                                                       \
     hipLaunchKernelGGL(umi_main_kernel<F>, dim3(grid), dim3(kMainThreads), dyn, stream, flux, hdr, \
