@@ -599,21 +599,26 @@ __device__ __forceinline__ float window_mad(const MainSmem& sm, const Wavelet& w
 }
 
 
-// Sort 32 keys in registers ascending (bitonic network).
+// Sort 32 keys in registers ascending: Batcher's merge exchange (Knuth, The Art
+// of Computer Programming 3, 5.2.2, Algorithm M).  With 23 keys and four
+// middle ranks asked for (W = 25) 193 minima and maxima are left of it, 245 of
+// a bitonic network.
 __device__ __forceinline__ void sort32(uint32_t (&k)[32])
 {
 #pragma unroll
-    for (int kk = 2; kk <= 32; kk <<= 1) {
+    for (int p = 16; p > 0; p >>= 1) {
 #pragma unroll
-        for (int jj = kk >> 1; jj > 0; jj >>= 1) {
+        for (int q = 16; q >= p; q >>= 1) {
+            // comparators (i, i + d) at i & p == r: first d = p, r = 0, then
+            // d = q' - p, r = p for q' = 32 / 2, 32 / 4, ..., 2 p
+            const int d = q == 16 ? p : 2 * q - p;
+            const int r = q == 16 ? 0 : p;
 #pragma unroll
-            for (int i = 0; i < 32; ++i) {
-                const int l = i ^ jj;
-                if (l > i) {
-                    const uint32_t a = k[i], b = k[l];
-                    const uint32_t lo = a < b ? a : b, hi = a < b ? b : a;
-                    k[i] = (i & kk) == 0 ? lo : hi;
-                    k[l] = (i & kk) == 0 ? hi : lo;
+            for (int i = 0; i < 32 - d; ++i) {
+                if ((i & p) == r) {
+                    const uint32_t a = k[i], b = k[i + d];
+                    k[i] = a < b ? a : b;
+                    k[i + d] = a < b ? b : a;
                 }
             }
         }
@@ -627,7 +632,9 @@ __device__ __forceinline__ void sort32(uint32_t (&k)[32])
 // q = (W-1)/2 is min(A[q], max(A[q-1], lo), max(A[q-2], hi)) for the sorted
 // core A (an index below 0 reads as the smallest key): the rank-q element of
 // a union of two sorted lists, split over the at most two keys of the second.
-// The points strictly above each median are counted on the unsorted keys.
+// The element of the next rank comes the same way; unless it ties with the
+// median, the points strictly above are those ranked after it, else they are
+// counted on the unsorted keys.
 // Keys past kp[lim] are never read.  Same results as the tile-sort path,
 // without the tile sort and wavelet matrix.
 // kW > 0 fixes W at compile time: the padding and the median rank are then
@@ -639,18 +646,22 @@ __device__ __forceinline__ void small_window_medians(const uint32_t* __restrict_
 {
     const int W = kW > 0 ? kW : W_rt;
     const int q = (W - 1) >> 1;  // <= 15, the same for the whole tile
-    uint32_t med[3];
+    uint32_t med[3], next[3];
     if (W == 1) {
 #pragma unroll
-        for (int r = 0; r < 3; ++r) med[r] = kp[min(r, lim)];
+        for (int r = 0; r < 3; ++r) {
+            med[r] = kp[min(r, lim)];
+            next[r] = 0xffffffffu;
+        }
     } else {
         uint32_t k[32];
 #pragma unroll
         for (int i = 0; i < 32; ++i) k[i] = i < W - 2 ? kp[2 + i] : 0xffffffffu;
         sort32(k);
-        uint32_t a0 = k[0], a1 = 0u, a2 = 0u;  // A[q], A[q-1], A[q-2]
+        uint32_t a0 = k[0], a1 = 0u, a2 = 0u, a3 = k[1];  // A[q], A[q-1], A[q-2], A[q+1]
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
+            a3 = q == i ? k[i + 1] : a3;
             a0 = q == i ? k[i] : a0;
             a1 = q - 1 == i ? k[i] : a1;
             a2 = q - 2 == i ? k[i] : a2;
@@ -660,6 +671,7 @@ __device__ __forceinline__ void small_window_medians(const uint32_t* __restrict_
         for (int r = 0; r < 3; ++r) {
             const uint32_t lo = min(ex[r], ex[r + 1]), hi = max(ex[r], ex[r + 1]);
             med[r] = min(a0, min(max(a1, lo), max(a2, hi)));
+            next[r] = min(a3, min(max(a0, lo), max(a1, hi)));
         }
     }
 #pragma unroll
@@ -668,8 +680,11 @@ __device__ __forceinline__ void small_window_medians(const uint32_t* __restrict_
             const float m = key_value(med[r]);
             // strictly above, numerically: -0 and +0 are equal
             const uint32_t T = m == 0.0f ? order_key(0.0f) : med[r];
-            uint32_t cnt = 0;
-            for (int j = 0; j < W; ++j) cnt += kp[r + j] > T ? 1u : 0u;
+            uint32_t cnt = (uint32_t)(W - 1 - q);
+            if (next[r] <= T) {
+                cnt = 0;
+                for (int j = 0; j < W; ++j) cnt += kp[r + j] > T ? 1u : 0u;
+            }
             pm[r] = m;
             pn[r] = cnt;
         }
