@@ -187,7 +187,7 @@ def copy_async(dst_ptrs, src_ptrs, nbytes, kind: int, stream=None):
     b = np.ascontiguousarray(nbytes, np.int64)
     if not (d.shape == s.shape == b.shape and b.ndim == 1):
         raise ValueError("copy_async: three 1-D arrays of equal length")
-    st = ctypes.c_void_p(stream) if isinstance(stream, int) else _stream_handle(stream)
+    st = stream if isinstance(stream, int) else _stream_handle(stream)
     _check(lib.umi_copy_async(d.ctypes.data, s.ctypes.data, b.ctypes.data, b.size, int(kind), st))
 
 
@@ -225,18 +225,34 @@ def _torch():
     return torch
 
 
+_Tensor = _torch().Tensor
+
+
+def _raw_stream_call():
+    """The handle of torch's current stream, without the Stream object that
+    torch.cuda.current_stream() builds (0.2 us against 2.7, a quarter of a short
+    curve's call) where this torch has the calls for it."""
+    c = _torch()._C
+    get, device = (getattr(c, name, None) for name in ("_cuda_getCurrentRawStream",
+                                                       "_cuda_getDevice"))
+    if get is None or device is None:
+        return lambda: int(_torch().cuda.current_stream().cuda_stream)
+    return lambda: get(device())
+
+
+_raw_stream = _raw_stream_call()
+
+
 def _stream_handle(stream):
-    torch = _torch()
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(int(stream.cuda_stream))
+    """A hipStream_t address: of `stream`, or of the current one."""
+    return _raw_stream() if stream is None else int(stream.cuda_stream)
 
 
 def _dev_ptr(t, dtype, name, n):
-    torch = _torch()
+    """The address of a contiguous device tensor of n elements (None for None)."""
     if t is None:
         return None
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    if not isinstance(t, _Tensor) or not t.is_cuda:
         raise TypeError("%s must be a CUDA (HIP) tensor" % name)
     if t.dtype != dtype:
         raise TypeError("%s must be %s, got %s" % (name, dtype, t.dtype))
@@ -244,7 +260,7 @@ def _dev_ptr(t, dtype, name, n):
         raise ValueError("%s must be contiguous" % name)
     if t.numel() != n:
         raise ValueError("%s has %d elements, expected %d" % (name, t.numel(), n))
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 @dataclass
