@@ -45,20 +45,19 @@ __host__ __device__ constexpr int core_cap(int W)
 }
 // the search tree over nb blocks' first values: levels of every 4^k-th value,
 // each a whole number of fours (the level of every value is the blocks' own)
-__host__ __device__ constexpr int core_levels(int nb)
+// (the first level holds every 4^(levels - 1)-th value)
+__host__ __device__ constexpr int core_top(int nb)  // log2 of that stride
 {
-    int n = 1;
-    while ((1 << (2 * n)) < nb) ++n;
-    return n;
+    return nb > 1 ? (31 - __builtin_clz((unsigned)(nb - 1))) & ~1 : 0;
 }
-__host__ __device__ constexpr int core_level_len(int nb, int stride)
+__host__ __device__ constexpr int core_level_len(int nb, int sh)  // of every 2^sh-th value
 {
-    return ((nb + stride - 1) / stride + 3) & ~3;
+    return (((nb + (1 << sh) - 1) >> sh) + 3) & ~3;
 }
 __host__ __device__ constexpr int core_tree(int nb)
 {
     int len = 0;
-    for (int st = 1 << (2 * (core_levels(nb) - 1)); st > 1; st >>= 2) len += core_level_len(nb, st);
+    for (int sh = core_top(nb); sh > 0; sh -= 2) len += core_level_len(nb, sh);
     return len;
 }
 // floats of LDS one wave's core takes: values, edge samples, and the larger
