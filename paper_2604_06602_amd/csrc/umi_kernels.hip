@@ -1339,22 +1339,17 @@ __device__ __forceinline__ CoreParams core_params(float alpha)
     return q;
 }
 
-// The core's block table and power sums.  False when the deviations' scale
-// is unusable.
+// The core's block table and power sums, of its values less the centre: the
+// values and the edge samples are shifted by it in place, so that a
+// residual's rounding is relative to the deviation and not to the flux
+// (trends' error against 64 bits at alpha = 10, c = 2.5, W = 361: 6.61e-8
+// without, 6.31e-8 with, 6.39e-8 for windows summed sample by sample; the
+// shift is free, the table's pass reads every value anyway).  False when the deviations' scale is unusable.
 __device__ __forceinline__ bool core_build(const CoreLds& cw, int nc, float quantile, float& centre,
                                            float& unit)
 {
     const int lane = thread_index() & 63;
     const int nb = nc / kCoreBlock;
-    {
-        float* t = cw.tree;
-        for (int sh = core_top(nb); sh > 0; sh -= 2) {
-            const int len = core_level_len(nb, sh);
-            for (int i = lane; i < len; i += 64)
-                t[i] = (i << sh) < nb ? cw.cv[(kCoreBlock * i) << sh] : __builtin_nanf("");
-            t += len;
-        }
-    }
     // the centre, and a power of two near the core's spread
     const int cq = (int)(quantile * (float)nc);
     centre = cw.cv[cq];
@@ -1362,6 +1357,19 @@ __device__ __forceinline__ bool core_build(const CoreLds& cw, int nc, float quan
     const int ex = __builtin_amdgcn_frexp_expf(spread);
     if (!(spread > 0.0f) || ex < -60 || ex > 60) return false;
     unit = __builtin_amdgcn_ldexpf(1.0f, -ex);
+    {
+        float* t = cw.tree;
+        for (int sh = core_top(nb); sh > 0; sh -= 2) {
+            const int len = core_level_len(nb, sh);
+            for (int i = lane; i < len; i += 64)
+                t[i] = (i << sh) < nb ? cw.cv[(kCoreBlock * i) << sh] - centre : __builtin_nanf("");
+            t += len;
+        }
+    }
+    // (LDS operations of a wave keep their order, so the values may change now)
+    const float e0 = cw.edge[lane], e1 = cw.edge[64 + (lane & 7)];
+    cw.edge[lane] = e0 - centre;
+    if (lane < kCoreEdge - 64) cw.edge[64 + lane] = e1 - centre;
     const int bc = cq / kCoreBlock;
     // power sums from the centre's block edge outwards: upwards in the lower
     // half of the wave, downwards (with a minus sign) in the upper half
@@ -1373,10 +1381,16 @@ __device__ __forceinline__ bool core_build(const CoreLds& cw, int nc, float quan
         const bool act = up ? b < nb : b >= 0;
         float s[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
         if (act) {
-            const float* v = cw.cv + kCoreBlock * b;
+            float4* const at = reinterpret_cast<float4*>(cw.cv + kCoreBlock * b);
+            float4 lo = at[0], hi = at[1];
+            lo = make_float4(lo.x - centre, lo.y - centre, lo.z - centre, lo.w - centre);
+            hi = make_float4(hi.x - centre, hi.y - centre, hi.z - centre, hi.w - centre);
+            at[0] = lo;
+            at[1] = hi;
+            const float v[kCoreBlock] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
 #pragma unroll
             for (int q = 0; q < kCoreBlock; ++q) {
-                const float d = (v[q] - centre) * unit;
+                const float d = v[q] * unit;
                 const float d2 = d * d;
                 const float d4 = d2 * d2;
                 s[0] += d;
@@ -1711,20 +1725,21 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv
 
         // Phase 2 (Eq. 1)
         float ssq = 0.0f, rest = 0.0f;
+        float at = m - centre;
         auto up2 = [&](float v) {
-            const float d = __builtin_fmaxf(v - m, 0.0f);
+            const float d = __builtin_fmaxf(v - at, 0.0f);
             ssq = __builtin_fmaf(d, d, ssq);
         };
         bool direct = true;
         if (core) {
             core_edges(xe, half, ne, ne_u, even, up2);
-            const int b = core_find(cw, nb, m);
+            const int b = core_find(cw, nb, at);
             core_block(cw.cv, b, half, up2);
             const int e = b + 1;
             const float d0 = (float)(kCoreBlock * (nb - e));
             const float d1 = cw.g[5 * nb] - cw.g[5 * e];
             const float d2 = cw.g[5 * nb + 1] - cw.g[5 * e + 1];
-            const float delta = (m - centre) * unit;
+            const float delta = at * unit;
             const float whole = __builtin_fmaf(delta * delta, d0, d2);
             const float sum = __builtin_fmaf(-2.0f * delta, d1, whole);
             const float back = 1.0f / unit;  // a power of two
@@ -1732,6 +1747,7 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv
             direct = !(fits && sum >= 0.125f * whole && whole < 1e30f);
         }
         if (live && direct) {
+            at = m;
             ssq = 0.0f;
             rest = 0.0f;
             strided_sweep<2>(x, half, (int)n, up2);
@@ -1762,25 +1778,26 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv
         const float kside = half ? ka : kb, fside = half ? q.kA : q.kA * q.inv_alpha;
         const float knot = half ? 0.0f : cl;
         for (int it = 0; it < iters; ++it) {
-            const float bb = -mu * k;
+            const float mu_c = mu - centre;
+            float bb = -mu_c * k;
             float sw = 0.0f, swv = 0.0f;
             auto acc = [&](float v) { bisquare_acc(v, k, bb, beta, sw, swv); };
             direct = true;
             if (core) {
                 core_edges(xe, half, ne, ne_u, even, acc);
-                const int bm = core_find(cw, nb, mu - knot);
+                const int bm = core_find(cw, nb, mu_c - knot);
                 const int bo = __float_as_int(dpp_xor1(__int_as_float(bm)));
                 const int b0 = half ? bo : bm, b1 = half ? bm : bo;
                 // the upper cut-off is rarely inside the core: past its
                 // largest value every block above the location is whole
                 int b2 = nb;
-                if (!(mu + cs >= vmax)) {
-                    b2 = core_find(cw, nb, mu + cs);
+                if (!(mu_c + cs >= vmax)) {
+                    b2 = core_find(cw, nb, mu_c + cs);
                     if (b2 != b1) core_block(cw.cv, b2, half, acc);
                 }
                 core_block(cw.cv, b0, half, acc);
                 if (b1 != b0) core_block(cw.cv, b1, half, acc);
-                const float delta = (mu - centre) * unit;
+                const float delta = mu_c * unit;
                 const float far = __builtin_fabsf(delta);
                 int e0 = half ? min(b1 + 1, b2) : min(b0 + 1, b1);
                 const int e1 = half ? b2 : b1;
@@ -1796,6 +1813,7 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv
                 direct = !(fits && scaled && far * ka <= kCoreReach && sw > 0.03125f * (float)(int)n);
             }
             if (act && direct) {
+                bb = -mu * k;
                 sw = 0.0f;
                 swv = 0.0f;
                 strided_sweep<2>(x, half, (int)n, acc);
