@@ -57,7 +57,7 @@ __host__ __device__ constexpr int core_level_len(int nb, int sh)  // of every 2^
 __host__ __device__ constexpr int core_tree(int nb)
 {
     int len = 0;
-    for (int sh = core_top(nb); sh > 0; sh -= 2) len += core_level_len(nb, sh);
+    for (int sh = core_top(nb) - 2; sh > 0; sh -= 2) len += core_level_len(nb, sh);
     return len;
 }
 // floats of LDS one wave's core takes: values, edge samples, and the larger

@@ -1320,6 +1320,24 @@ __device__ __forceinline__ void core_collect(const MainSmem& sm, const Wavelet& 
 }
 static_assert(kStageMax == 64 * 32, "a word of marks per lane");
 
+// The tree's first level, the same for every lane: kept in scalar registers, a
+// load less in each search's chain (one curve of 20,000 samples at W = 361:
+// 20.5 -> 19.5 us; 200 x 19,440 at W = 1081: 614 -> 600 us).
+struct CoreRoot {
+    float v1, v2, v3;
+};
+
+__device__ __forceinline__ CoreRoot core_root(const CoreLds& cw, int nb)
+{
+    const int st = 1 << core_top(nb);
+    const float nan = __builtin_nanf("");
+    CoreRoot r;
+    r.v1 = st < nb ? lane_value(cw.cv[kCoreBlock * st], 0) : nan;
+    r.v2 = 2 * st < nb ? lane_value(cw.cv[2 * kCoreBlock * st], 0) : nan;
+    r.v3 = 3 * st < nb ? lane_value(cw.cv[3 * kCoreBlock * st], 0) : nan;
+    return r;
+}
+
 // What a curve's alpha fixes for its groups, formed once per tile.
 struct CoreParams {
     float kA, beta;   // A = (1 + alpha)/2 and B/A of the folded residual
@@ -1359,7 +1377,7 @@ __device__ __forceinline__ bool core_build(const CoreLds& cw, int nc, float quan
     unit = __builtin_amdgcn_ldexpf(1.0f, -ex);
     {
         float* t = cw.tree;
-        for (int sh = core_top(nb); sh > 0; sh -= 2) {
+        for (int sh = core_top(nb) - 2; sh > 0; sh -= 2) {
             const int len = core_level_len(nb, sh);
             for (int i = lane; i < len; i += 64)
                 t[i] = (i << sh) < nb ? cw.cv[(kCoreBlock * i) << sh] - centre : __builtin_nanf("");
@@ -1599,11 +1617,14 @@ __device__ __forceinline__ void core_phase1(const MainSmem& sm, const Wavelet& w
 // quotient by a stride that only the loop knew it cost a 30-instruction
 // integer division per level, search and iteration (1,000 x 18,000 samples at
 // W = 361: 1.72 ms against 1.62; 200 x 19,440 at W = 1081: 693 us against 626).
-__device__ __forceinline__ int core_find(const CoreLds& cw, int nb, float knot)
+__device__ __forceinline__ int core_find(const CoreLds& cw, const CoreRoot& root, int nb,
+                                         float knot)
 {
-    int b = 0;
+    int b = (root.v1 <= knot ? 1 : 0) + (root.v2 <= knot ? 1 : 0) + (root.v3 <= knot ? 1 : 0);
     const float* tree = cw.tree;
-    for (int sh = core_top(nb); sh > 0; sh -= 2) {
+    int sh = core_top(nb);
+    if (sh == 0) return b;
+    for (sh -= 2; sh > 0; sh -= 2) {
         const float4 v = reinterpret_cast<const float4*>(tree)[b];
         b = 4 * b + (v.y <= knot ? 1 : 0) + (v.z <= knot ? 1 : 0) + (v.w <= knot ? 1 : 0);
         tree += core_level_len(nb, sh);
@@ -1646,20 +1667,29 @@ __device__ __forceinline__ void core_block(const float* __restrict__ cv, int b, 
     f(v.w);
 }
 
-// f over this lane's half of the ne samples from xe (every second one); even:
-// the wave's windows all have ne_u of them
+// Edge samples a lane keeps in registers: half of the most a group of index
+// windows has (31 that the windows differ by, and 7 beyond the last block).
+// Read from LDS in every iteration by a loop, a wave alone on its SIMD spent
+// 1,000 cycles of an iteration on them, and 2,100 where the windows' counts
+// differ (at a segment's ends, which set a small batch's time); from registers
+// 620, absent ones as samples of no weight.  1,000 x 18,000 samples at W = 361:
+// 1.62 -> 1.54 ms, at W = 191: 1.55 -> 1.40 ms; one curve of 9,337 at W = 721:
+// 22.7 -> 21.0 us (both with the root above).
+constexpr int kEdgeRegs = (kCoreGroup - 1 + kCoreBlock - 1 + 1) / 2;
+static_assert(32 + 2 * kEdgeRegs <= kCoreEdge, "loads stay inside the edge samples");
+
+// f over this lane's edge samples: e in registers (the last three only where
+// a window has them), the rest of a time window's from xe
 template <class F>
-__device__ __forceinline__ void core_edges(const float* __restrict__ xe, int half, int ne, int ne_u,
-                                           bool even, F&& f)
+__device__ __forceinline__ void core_edges(const float (&e)[kEdgeRegs], const float* xe, int half,
+                                           int ne, bool more, F&& f)
 {
-    const float* const x = xe + half;
-    if (even) {
-        const int pairs = ne_u >> 1;
-#pragma unroll 8
-        for (int j = 0; j < pairs; ++j) f(x[2 * j]);
-        if ((ne_u & 1) && half == 0) f(x[2 * pairs]);
-    } else {
-        for (int j = 0; j + half < ne; j += 2) f(x[j]);
+#pragma unroll
+    for (int i = 0; i < kCoreGroup / 2; ++i) f(e[i]);
+    if (more) {
+#pragma unroll
+        for (int i = kCoreGroup / 2; i < kEdgeRegs; ++i) f(e[i]);
+        for (int j = 2 * kEdgeRegs + half; j < ne; j += 2) f(xe[j]);
     }
 }
 
@@ -1719,8 +1749,18 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv
         const bool edges = live && fits;
         const float* const xe = cw.edge + 32 - (edges ? nl : 0);
         const int ne = edges ? (int)n - nb * kCoreBlock : 0;
-        const int ne_u = __builtin_amdgcn_readlane(ne, (int)__builtin_ctzll(live_m));
-        const bool even = __all(!live || ne == ne_u);
+        const CoreRoot root = core_root(cw, nb);
+        const bool full = __all(ne >= kCoreGroup - 1), more = __any(ne > kCoreGroup);
+        float e[kEdgeRegs];
+#pragma unroll
+        for (int i = 0; i < kEdgeRegs; ++i) e[i] = xe[2 * i + half];
+        auto take = [&](int i) { e[i] = 2 * i + half < ne ? e[i] : -__builtin_inff(); };
+        if (!full) {
+#pragma unroll
+            for (int i = 0; i < kCoreGroup / 2 - 1; ++i) take(i);
+        }
+#pragma unroll
+        for (int i = kCoreGroup / 2 - 1; i < kEdgeRegs; ++i) take(i);
         const float* const x = sm.xv + ca;
 
         // Phase 2 (Eq. 1)
@@ -1732,13 +1772,13 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv
         };
         bool direct = true;
         if (core) {
-            core_edges(xe, half, ne, ne_u, even, up2);
-            const int b = core_find(cw, nb, at);
+            core_edges(e, xe, half, ne, more, up2);
+            const int b = core_find(cw, root, nb, at);
             core_block(cw.cv, b, half, up2);
-            const int e = b + 1;
-            const float d0 = (float)(kCoreBlock * (nb - e));
-            const float d1 = cw.g[5 * nb] - cw.g[5 * e];
-            const float d2 = cw.g[5 * nb + 1] - cw.g[5 * e + 1];
+            const int b1 = b + 1;
+            const float d0 = (float)(kCoreBlock * (nb - b1));
+            const float d1 = cw.g[5 * nb] - cw.g[5 * b1];
+            const float d2 = cw.g[5 * nb + 1] - cw.g[5 * b1 + 1];
             const float delta = at * unit;
             const float whole = __builtin_fmaf(delta * delta, d0, d2);
             const float sum = __builtin_fmaf(-2.0f * delta, d1, whole);
@@ -1774,6 +1814,14 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv
         const float kb = __builtin_amdgcn_rcpf(cl * unit);
         const bool scaled = ka > 1e-4f && ka < 1e4f;
         const float vmax = core ? cw.cv[kCoreBlock * nb - 1] : 0.0f;
+        // samples that are not there, and any as far out, weigh nothing
+        const float lowest = -1e9f * __builtin_fmaxf(cs, cl);
+        if (!full) {
+#pragma unroll
+            for (int i = 0; i < kCoreGroup / 2 - 1; ++i) e[i] = __builtin_fmaxf(e[i], lowest);
+        }
+#pragma unroll
+        for (int i = kCoreGroup / 2 - 1; i < kEdgeRegs; ++i) e[i] = __builtin_fmaxf(e[i], lowest);
         // this lane's side of the power sums: above the location, or below
         const float kside = half ? ka : kb, fside = half ? q.kA : q.kA * q.inv_alpha;
         const float knot = half ? 0.0f : cl;
@@ -1784,15 +1832,15 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv
             auto acc = [&](float v) { bisquare_acc(v, k, bb, beta, sw, swv); };
             direct = true;
             if (core) {
-                core_edges(xe, half, ne, ne_u, even, acc);
-                const int bm = core_find(cw, nb, mu_c - knot);
+                core_edges(e, xe, half, ne, more, acc);
+                const int bm = core_find(cw, root, nb, mu_c - knot);
                 const int bo = __float_as_int(dpp_xor1(__int_as_float(bm)));
                 const int b0 = half ? bo : bm, b1 = half ? bm : bo;
                 // the upper cut-off is rarely inside the core: past its
                 // largest value every block above the location is whole
                 int b2 = nb;
                 if (!(mu_c + cs >= vmax)) {
-                    b2 = core_find(cw, nb, mu_c + cs);
+                    b2 = core_find(cw, root, nb, mu_c + cs);
                     if (b2 != b1) core_block(cw.cv, b2, half, acc);
                 }
                 core_block(cw.cv, b0, half, acc);

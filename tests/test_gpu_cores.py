@@ -84,6 +84,19 @@ def test_cores_against_oracle(torch, umi, oracle_lib, Ws, tile):
                       what="cores W=%s tile %d a=%g c=%g" % (Ws, tile, a, c))
 
 
+@pytest.mark.parametrize("W", [117, 159, 167, 543, 551])
+def test_core_block_counts(torch, umi, oracle_lib, W):
+    """Cores whose search tree just fills its levels (16, 64 blocks) or needs
+    one more (17, 65); windows that grow and shrink at segment ends, whose edge
+    samples differ in number; cut-offs far apart."""
+    b = core_batch((W,), 13)
+    mag = window_magnitude(b.flux, b.time, b.lengths, b.W, oracle_lib)
+    for a, c in [(2.0, 5.0), (20.0, 5.0), (0.05, 5.0)]:
+        g_tr, g_md = run_batch(torch, umi, b.flux, b.time, b.lengths, b.W, alpha=a, c=c, iters=5)
+        o_tr, o_md = oracle_lib.detrend_batch(b.flux, b.time, b.lengths, b.W, alpha=a, c=c, iters=5)
+        assert_parity(g_tr, g_md, o_tr, o_md, scale=mag, what="W=%d a=%g" % (W, a))
+
+
 def test_cores_do_not_depend_on_the_tile(torch, umi):
     b = core_batch((195, 361, 701), 9)
     ref = run_batch(torch, umi, b.flux, b.time, b.lengths, b.W, launch=umi.LaunchOptions(tile=1024))
