@@ -91,7 +91,7 @@ def test_core_block_counts(torch, umi, oracle_lib, W):
     samples differ in number; cut-offs far apart."""
     b = core_batch((W,), 13)
     mag = window_magnitude(b.flux, b.time, b.lengths, b.W, oracle_lib)
-    for a, c in [(2.0, 5.0), (20.0, 5.0), (0.05, 5.0)]:
+    for a, c in [(2.0, 5.0), (16.0, 5.0), (0.25, 5.0)]:
         g_tr, g_md = run_batch(torch, umi, b.flux, b.time, b.lengths, b.W, alpha=a, c=c, iters=5)
         o_tr, o_md = oracle_lib.detrend_batch(b.flux, b.time, b.lengths, b.W, alpha=a, c=c, iters=5)
         assert_parity(g_tr, g_md, o_tr, o_md, scale=mag, what="W=%d a=%g" % (W, a))
