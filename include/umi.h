@@ -74,8 +74,9 @@ typedef enum {
 /* Tuning knobs; zero in a field means "use the library's choice" (its
  * built-in defaults, or the tuning table loaded with umi_set_tuning).  With
  * tile = 0, a batch that the chosen tiles would cut into fewer tiles than the
- * device has compute units runs with tiles of at most 1024, 512, 256, 128,
- * then 64 output positions, so that more of the chip shares it.  Tiles of
+ * device runs at once takes smaller ones, from 1280 down to 64 output
+ * positions, as long as all of them still run at once (below 256 positions: as
+ * long as every compute unit has at most one).  Tiles of
  * more than 256 positions give each window one lane and results that do not
  * depend on the tile size; tiles of at most 256 split every window over 2,
  * 4 or 8 lanes (kept in step by cross-lane sums), which orders the sums

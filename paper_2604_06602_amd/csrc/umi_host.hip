@@ -233,25 +233,35 @@ struct PackView {
     int feat = kFeatAll;      // estimate-kernel paths the batch needs (kFeat* bits)
 };
 
-// Tile sizes a batch that does not fill the GPU falls back to, largest first.
-// Above 256 positions each lane takes a window (cores: a pair of lanes, 256
-// positions of a tile at a time), at 256, 128 and 64 two, four and eight lanes
-// share one.
+// Tile sizes a batch that does not fill the GPU falls back to.  Without sorted
+// cores, largest first: above 256 positions each lane takes a window, at 256,
+// 128 and 64 two, four and eight lanes share one.
 constexpr int kSmallBatchTiles[] = {1280, 1024, 768, 512, 320, 256, 128, 64};
 
 // Workgroups per CU the GPU holds at once (LDS: four, with cores three), and
-// what a small batch may be cut into: as many tiles as run together, since a
-// tile's time hardly depends on how many others do; a second round of them
-// would.  Tiles below 256 positions only while every CU has at most one: they
-// halve a workgroup's windows, not what it does for the tile.  (16 curves of
-// 20,000, us a call: W = 361 640 tiles of 512 52, 320 of 1024 74, 848 of 384 64,
-// 1250 of 256 51; W = 25 1000 tiles of 320 30, 640 of 512 32, 320 of 1024 43.
-// One curve of 20,000 at W = 361: 157 tiles of 128 22.3, 63 of 320 33.)
+// what a small batch may be cut into: as many tiles as run together; a second
+// round of them would take a tile's time again.  Without cores a tile's time
+// hardly depends on how many others run, so the smallest tile is taken (16
+// curves of 20,000 at W = 25, us a call: 1008 tiles of 320 29, 640 of 512 32,
+// 320 of 1024 43).  Tiles below 256 positions only while every CU has at most
+// one: they halve a workgroup's windows, not what it does for the tile (one
+// curve at W = 361: 157 tiles of 128 18.4, 79 of 256 19.2, 63 of 320 27).
 constexpr int kSmallBatchSlots = 4;
 constexpr int kSmallBatchCoreSlots = 3;
 
-// Whether a curve's tiles take sorted cores: wide windows with the upper-RMS scale, tiles that hold a group of windows (all but those of the
-// very widest), and asymmetries whose two sides' cut-offs are not far apart.
+// With cores a tile's time grows with the tiles a CU holds: per position about
+// as 25, 35 and 48 for one, two and three (W = 361: tiles of 512 take 30, 37 and
+// 48 us, of 1024 49, 64 and 82).  So of the multiples of 128 that run together
+// the one with the least tile times weight is taken, k the tiles per CU rounded
+// up.  Against the smallest that runs together in whole passes of the
+// workgroup, us a call: 16 curves of 20,000 51 -> 49, 24 68 -> 60, 32 83 -> 74,
+// 40 112 -> 100, 100 of 4,408 at W = 121 78 -> 68, 300 of 1,200 79 -> 71.
+constexpr int kCoreTileStep = 128;
+constexpr int kCoreTileCost[kSmallBatchCoreSlots] = {25, 35, 48};
+
+// Whether a curve's tiles take sorted cores: wide windows with the upper-RMS
+// scale, tiles that hold a group of windows (all but those of the very
+// widest), and asymmetries whose two sides' cut-offs are not far apart.
 bool core_window(int W, float alpha, int32_t scale)
 {
     return W >= kCoreMinW && max_tile(W) >= kCoreGroup && scale == UMI_SCALE_UPPER_RMS &&
@@ -289,21 +299,40 @@ umi_status pack_into(const int64_t* offsets, const int64_t* lengths, int64_t n, 
         for (int64_t i = 0; i < nord; ++i) {
             const int32_t b = order[i];
             const int tb = cap > 0 ? std::min(tile_of[b], cap) : tile_of[b];
-            t += (lengths[b] + tb - 1) / tb;
+            t += ((uint32_t)lengths[b] + (uint32_t)tb - 1u) / (uint32_t)tb;  // < 2^31 samples
         }
         return t;
     };
     if (opt.tile == 0 && !any_sized) {
         bool cores = false;
         for (int64_t i = 0; i < nord; ++i) cores = cores || is_core(order[i]);
-        const int64_t slots = (int64_t)n_cu * (cores ? kSmallBatchCoreSlots : kSmallBatchSlots);
-        for (int cap : kSmallBatchTiles) {
-            if (cores && cap % (kCoreGroup * kMainThreads / 64) != 0 && cap > kSplitMaxTile)
-                continue;  // a round of groups nearly empty
-            const int64_t t = count_tiles(cap);
-            if (t > max_tiles || t > (cap < kSplitMaxTile ? n_cu : slots)) break;
-            for (int64_t i = 0; i < nord; ++i) tile_of[order[i]] = std::min(tile_of[order[i]], cap);
+        int widest = 0, chosen = 0;
+        for (int64_t i = 0; i < nord; ++i) widest = std::max(widest, tile_of[order[i]]);
+        if (cores) {
+            int64_t least = INT64_MAX;
+            for (int cap = widest; cap >= kSplitMaxTile;
+                 cap = (cap - 1) / kCoreTileStep * kCoreTileStep) {
+                const int64_t t = count_tiles(cap);
+                if (t > max_tiles || t > (int64_t)n_cu * kSmallBatchCoreSlots) break;
+                if (t == 0) break;
+                const int64_t cost = (int64_t)cap * kCoreTileCost[(t - 1) / n_cu];
+                if (cost < least) {
+                    least = cost;
+                    chosen = cap;
+                }
+            }
         }
+        for (int cap : kSmallBatchTiles) {
+            if (cores && cap >= kSplitMaxTile) continue;
+            const int64_t t = count_tiles(cap);
+            if (t > max_tiles ||
+                t > (cap < kSplitMaxTile ? n_cu : (int64_t)n_cu * kSmallBatchSlots))
+                break;
+            chosen = cap;
+        }
+        if (chosen > 0)
+            for (int64_t i = 0; i < nord; ++i)
+                tile_of[order[i]] = std::min(tile_of[order[i]], chosen);
     }
     // costliest tiles first; ties by length, then by input position (a total
     // order, so std::sort needs no scratch and the table is deterministic)
@@ -486,8 +515,8 @@ int setup_grid(int64_t ncurves) { return (int)std::min<int64_t>(ncurves, kSetupG
 // Whether a batch's table goes to the estimate kernel by value, one workgroup
 // per tile: no set-up launch, staging block or tile queue.  Up to kSmallTable
 // curves it fits the kernel arguments; a limit on the workgroups per CU asks
-// for the queue.  (One curve of 20,000 samples at W = 361: 50 us a call with a
-// pre-pass and the queue, 36 by value.)
+// for the queue.  (The set-up launch takes 4.5 us and the gap after it 6; one
+// curve of 20,000 samples at W = 361 takes 19 in all.)
 bool by_value(int64_t ncurves, const umi_launch& opt, int gpc)
 {
     return ncurves <= kSmallTable && opt.mode == UMI_MODE_PERSISTENT && opt.groups_per_cu == 0 &&

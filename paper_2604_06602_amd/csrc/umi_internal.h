@@ -36,6 +36,8 @@ constexpr int kCoreBlock = 8;
 // Waves per SIMD the core instances are built for: LDS (47 KB at W = 361)
 // allows three workgroups per CU, and 80 registers spill little; at 4 waves
 // (128 registers) two workgroups fit and W = 361 took 3.3 ms against 2.5.
+// (Edge samples in registers spill some of the tile's own values, outside the
+// groups' loop.)
 constexpr int kCoreWaves = 6;
 constexpr int kCoreGroup = 32;               // windows that share a core
 constexpr int kCoreEdge = 32 + kCoreBlock + 32;  // samples a wave sums one by one
@@ -44,8 +46,8 @@ __host__ __device__ constexpr int core_cap(int W)
     return W >= kCoreGroup ? W - (kCoreGroup - 1) : 0;
 }
 // the search tree over nb blocks' first values: levels of every 4^k-th value,
-// each a whole number of fours (the level of every value is the blocks' own)
-// (the first level holds every 4^(levels - 1)-th value)
+// each a whole number of fours.  The first level, of every 2^core_top-th value,
+// stands in registers; the last, of every value, is the blocks' own.
 __host__ __device__ constexpr int core_top(int nb)  // log2 of that stride
 {
     return nb > 1 ? (31 - __builtin_clz((unsigned)(nb - 1))) & ~1 : 0;
@@ -96,7 +98,7 @@ struct BatchHeader {
     int32_t n_tiles;    // tiles over all curves
     int32_t iters;      // Phase 3 iterations
     int32_t scale;      // umi_scale: Phase 2 estimator
-    int32_t n_chunks;   // pre-pass chunks over all curves
+    int32_t n_chunks;   // chunks of kPrepChunk samples over all curves
     int32_t reserved;
     float* detrended;   // flux / trend output (curve offsets as for trend), or null
     const double* time; // the batch's times (read by the time-window scans), or null
@@ -113,7 +115,7 @@ struct CurveDesc {
     float alpha;        // asymmetry factor (Eq. 2) of this curve
     float c;            // bisquare tuning constant of this curve
     double window_days; // > 0: time window of this length (W still bounds it)
-    int32_t chunk_base; // index of this curve's first pre-pass chunk
+    int32_t chunk_base; // index of this curve's first chunk
     int32_t core;       // its tiles sum windows by sorted cores
 };
 static_assert(sizeof(CurveDesc) == 48, "CurveDesc layout");

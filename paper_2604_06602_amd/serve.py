@@ -13,8 +13,9 @@ A scheduler thread
   * launches steps: all admitted, not yet launched groups that share the
     iteration count go into one batch -- each curve keeps its own alpha and
     c (the Table 4 settings mix freely) -- run through a replayable plan (a
-    captured hipGraph of the tile-table copy, the segmentation pre-pass and
-    the persistent estimate kernel) on the compute stream.  Up to two steps
+    captured hipGraph of the set-up launch, which copies the tile table, and
+    the persistent estimate kernel; a step of at most 32 curves launches the
+    estimate kernel alone) on the compute stream.  Up to two steps
     are in flight, so requests that arrive while one step runs are uploaded
     and staged concurrently and run in the next step;
   * completes steps: the trend of each group comes back with one
