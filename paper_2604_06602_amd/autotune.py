@@ -65,9 +65,10 @@ def tile_candidates(W: int):
 
 def small_batch_candidates(W: int):
     """Tiles for a batch too small to fill the GPU: the large-batch ones of at
-    least 512 positions and the split tiles."""
+    least 512 positions, the split tiles, and what the library's own rule takes
+    between them."""
     c = {t for t in tile_candidates(W) if t >= THREADS}
-    c.update(t for t in SPLIT_TILES if t <= max_tile(W))
+    c.update(t for t in SPLIT_TILES + [320, 384, 640] if t <= max_tile(W))
     c.add(max_tile(W))
     return sorted(c)
 
@@ -117,16 +118,21 @@ def tune(n_curves=400, length=20000, steps=5, log=print):
         for curves, samples_max in SMALL_BATCHES:
             flux, time_, lengths, Ws = _workload(W, curves, SMALL_LENGTH, seed=curves)
             trend = torch.empty_like(flux)
-            results = sorted((time_candidate(flux, time_, lengths, Ws, trend, tile, GROUPS[-1],
+            # the library's workgroups per CU, so that the call takes the path
+            # (by value, without a queue) that it takes in use
+            results = sorted((time_candidate(flux, time_, lengths, Ws, trend, tile, 0,
                                              steps=max(steps, 20)), tile)
                              for tile in small_batch_candidates(W))
-            rows.append((w_max, results[0][1], GROUPS[-1], samples_max))
+            # a row serves batches of up to twice the size timed here: of equally
+            # fast tiles the largest, which that batch still runs at once
+            tile = max(t for m, t in results if m <= results[0][0] * (1 + 2 * TIE))
+            rows.append((w_max, tile, GROUPS[-1], samples_max))
             detail["%d/%d" % (w_max, samples_max)] = {
                 "W": W, "curves": curves, "length": SMALL_LENGTH, "best_ms": results[0][0],
                 "candidates": [{"tile": t, "groups_per_cu": GROUPS[-1], "ms": m}
                                for m, t in results]}
             log("W<=%d (W=%d), %d curve(s) of %d: tile %d, %.3f ms per call (tile %d: %.3f ms)"
-                % (w_max, W, curves, SMALL_LENGTH, results[0][1], results[0][0],
+                % (w_max, W, curves, SMALL_LENGTH, tile, results[0][0],
                    results[-1][1], results[-1][0]))
             del flux, time_, trend
         flux, time_, lengths, Ws = _workload(W, n_curves, length)

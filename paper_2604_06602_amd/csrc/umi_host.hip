@@ -1421,7 +1421,7 @@ void umi_release(void)
     umi::g_ws.clear();
 }
 
-const char* umi_version(void) { return "umi-mi355x 0.8.5"; }
+const char* umi_version(void) { return "umi-mi355x 0.9.0"; }
 
 void umi_debug_inject_error(umi_status s) { umi::t_inject = s; }
 
