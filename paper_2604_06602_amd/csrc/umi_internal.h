@@ -29,8 +29,10 @@ constexpr int kFeatBits = 8;                 // the batch's largest core stands 
 // each; the core is that shared run, a whole number of blocks of kCoreBlock.
 // Narrower windows sum their samples directly: what a wave does for a group,
 // and the 33 edge and 16 block samples of a window's iteration, cost the same
-// whatever W (1,000 curves of 18,000: W = 109 1.51 ms directly, 1.57 by cores;
-// W = 121 1.64 and 1.51).
+// whatever W.  The line lies between where batches gain (500 curves of 18,000:
+// W = 97 737 us directly, 740 by cores; W = 113 818 and 731) and where one curve
+// of 20,000 does, in small tiles whose windows several lanes share (W = 113 17
+// and 19 us; W = 161 18 and 19; W = 201 19.5 and 19; W = 361 24.5 and 19.5).
 constexpr int kCoreMinW = 117;
 constexpr int kCoreBlock = 8;
 // Waves per SIMD the core instances are built for: LDS (47 KB at W = 361)
