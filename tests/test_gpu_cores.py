@@ -1,4 +1,4 @@
-"""GPU parity of the wide windows' sorted cores (64 aligned windows share a
+"""GPU parity of the wide windows' sorted cores (32 aligned windows share a
 core summed by its power sums) against the FP64 oracle: medians bit-exact,
 trends within the trend tolerance, one result whatever the tile.
 
@@ -105,6 +105,23 @@ def test_cores_do_not_depend_on_the_tile(torch, umi):
         out = run_batch(torch, umi, b.flux, b.time, b.lengths, b.W, launch=lo)
         assert np.array_equal(out[0].view(np.uint32), ref[0].view(np.uint32)), lo
         assert np.array_equal(out[1].view(np.uint32), ref[1].view(np.uint32)), lo
+
+
+@pytest.mark.parametrize("curves,n", [(1, 117), (1, 20000), (8, 20000), (12, 20000), (16, 20000), (40, 20000),
+                                      (300, 1200)])
+def test_small_batches_take_any_tile(torch, umi, curves, n):
+    """Batches that the library cuts into small tiles, one to three a CU, give
+    the bits of tiles of 1,024 positions."""
+    umi.set_tuning(None)
+    rng = np.random.default_rng(curves)
+    flux = (1 + 1e-3 * rng.standard_normal(curves * n)).astype(np.float32)
+    flux[rng.random(flux.size) < 0.01] = np.nan
+    time = np.tile(np.arange(n) * DT, curves)
+    auto = run_batch(torch, umi, flux, time, [n] * curves, [361] * curves)
+    ref = run_batch(torch, umi, flux, time, [n] * curves, [361] * curves,
+                    launch=umi.LaunchOptions(tile=1024))
+    for a, r in zip(auto, ref):
+        assert np.array_equal(a.view(np.uint32), r.view(np.uint32))
 
 
 def test_plans_take_the_kernel_their_windows_need(torch, umi):
