@@ -249,6 +249,16 @@ constexpr int kSmallBatchTiles[] = {1280, 1024, 768, 512, 320, 256, 128, 64};
 constexpr int kSmallBatchSlots = 4;
 constexpr int kSmallBatchCoreSlots = 3;
 
+// Windows that take the register networks leave a tile little to set up, and
+// what costs a batch of a few rounds is its last, unequal one: tiles of 512 up
+// to three rounds of them, of 1024 up to eight, where the largest tile is
+// otherwise the best (W = 25, us a call with tiles of 512, 1024, 1536: 36 curves
+// of 18,000 55, 65, 70; 70 72, 78, 89; 150 109, 114, 121; 400 227, 212, 218; 1000
+// 510, 453, 455).  At W = 61, with a sort per tile, 1536 is the best from 100
+// curves on (150, 152, 160).
+constexpr int kNarrowTiles[] = {512, 1024};
+constexpr int kNarrowRounds[] = {3, 8};
+
 // With cores a tile's time grows with the tiles a CU holds: per position about
 // as 25, 35 and 48 for one, two and three (W = 361: tiles of 512 take 30, 37 and
 // 48 us, of 1024 49, 64 and 82).  So of the multiples of 128 that run together
@@ -322,8 +332,17 @@ umi_status pack_into(const int64_t* offsets, const int64_t* lengths, int64_t n, 
                 }
             }
         }
+        bool narrow = !cores && o.scale == UMI_SCALE_UPPER_RMS && !o.window_days;
+        for (int64_t i = 0; narrow && i < nord; ++i) narrow = W[order[i]] <= kSmallW;
+        for (int u = 0; narrow && chosen == 0 && u < 2; ++u) {
+            const int64_t most =
+                std::min(max_tiles, (int64_t)kNarrowRounds[u] * kSmallBatchSlots * n_cu);
+            if (samples <= most * kNarrowTiles[u] && count_tiles(kNarrowTiles[u]) <= most)
+                chosen = kNarrowTiles[u];
+        }
         for (int cap : kSmallBatchTiles) {
             if (cores && cap >= kSplitMaxTile) continue;
+            if (narrow && chosen > 0 && cap >= chosen) continue;
             const int64_t t = count_tiles(cap);
             if (t > max_tiles ||
                 t > (cap < kSplitMaxTile ? n_cu : (int64_t)n_cu * kSmallBatchSlots))
@@ -1199,7 +1218,7 @@ umi_status umi_plan_create(umi_plan** out, int64_t capacity, int64_t max_curves,
     // Tiles the plan must hold: the whole capacity at the smallest tile any
     // W <= max_W takes for batches of any size; batches at most samples_max
     // long at their batch-size rows' tiles; and the small-batch rule, which
-    // cuts a batch into at most kSmallBatchSlots tiles per CU.  With room for
+    // cuts a batch into at most kNarrowRounds rounds of them.  With room for
     // all of these, a run is cut exactly as the direct calls cut the same batch.
     int64_t min_tile = std::min(umi::max_tile(max_W), umi::core_tile(umi::default_tile(max_W)));
     int64_t sized_tiles = 0;
@@ -1215,7 +1234,8 @@ umi_status umi_plan_create(umi_plan** out, int64_t capacity, int64_t max_curves,
         }
     }
     const int64_t max_tiles = std::max(capacity / std::max<int64_t>(1, min_tile),
-                                       std::max(sized_tiles, umi::kSmallBatchSlots * n_cu)) +
+                                       std::max(sized_tiles, umi::kNarrowRounds[1] *
+                                                                 umi::kSmallBatchSlots * n_cu)) +
                               max_curves;
     if (max_tiles > (int64_t)INT32_MAX)
         return umi::fail(UMI_ERR_UNSUPPORTED, "plan capacity needs too many tiles");

@@ -124,6 +124,22 @@ def test_small_batches_take_any_tile(torch, umi, curves, n):
         assert np.array_equal(a.view(np.uint32), r.view(np.uint32))
 
 
+@pytest.mark.parametrize("curves,n", [(36, 18000), (100, 18000), (100, 4408), (300, 4408)])
+def test_narrow_windows_take_any_tile(torch, umi, curves, n):
+    """Batches of W = 25 of one round of tiles and of several give the bits of
+    tiles of 1,536 positions."""
+    umi.set_tuning(None)
+    rng = np.random.default_rng(n)
+    flux = (1 + 1e-3 * rng.standard_normal(curves * n)).astype(np.float32)
+    flux[rng.random(flux.size) < 1e-4] = np.nan
+    time = np.tile(np.arange(n) * DT, curves)
+    auto = run_batch(torch, umi, flux, time, [n] * curves, [25] * curves)
+    ref = run_batch(torch, umi, flux, time, [n] * curves, [25] * curves,
+                    launch=umi.LaunchOptions(tile=1536))
+    for a, r in zip(auto, ref):
+        assert np.array_equal(a.view(np.uint32), r.view(np.uint32))
+
+
 def test_plans_take_the_kernel_their_windows_need(torch, umi):
     """One plan's runs without cores, with cores of middling windows and with
     the widest windows give the direct call's bits."""
