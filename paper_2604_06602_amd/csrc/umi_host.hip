@@ -534,12 +534,14 @@ int setup_grid(int64_t ncurves) { return (int)std::min<int64_t>(ncurves, kSetupG
 // Whether a batch's table goes to the estimate kernel by value, one workgroup
 // per tile: no set-up launch, staging block or tile queue.  Up to kSmallTable
 // curves it fits the kernel arguments; a limit on the workgroups per CU asks
-// for the queue.  (The set-up launch takes 4.5 us and the gap after it 6; one
-// curve of 20,000 samples at W = 361 takes 19 in all.)
-bool by_value(int64_t ncurves, const umi_launch& opt, int gpc)
+// for the queue, and so do more tiles than a launch may have workgroups (17
+// million samples at W = 2047, whose tiles are two positions).  (The set-up
+// launch takes 4.5 us and the gap after it 6; one curve of 20,000 samples at W =
+// 361 takes 19 in all.)
+bool by_value(int64_t ncurves, int64_t ntiles, const umi_launch& opt, int gpc)
 {
-    return ncurves <= kSmallTable && opt.mode == UMI_MODE_PERSISTENT && opt.groups_per_cu == 0 &&
-           gpc >= kDefaultGroupsPerCU;
+    return ncurves <= kSmallTable && grid_fits(ntiles) && opt.mode == UMI_MODE_PERSISTENT &&
+           opt.groups_per_cu == 0 && gpc >= kDefaultGroupsPerCU;
 }
 
 // Enqueue the kernels of a staged block (header + curve table).  With `stage`
@@ -753,7 +755,7 @@ umi_status detrend_gather(const float* flux, const double* time, const int64_t* 
     if ((e = ws->reserve(nc, p.ntiles, p.nchunks)) != hipSuccess)
         return fail_hip(e, "workspace allocation");
     const int grid = (int)std::min<int64_t>(p.ntiles, (int64_t)p.gpc * cu_count(device));
-    if (by_value(nc, opt, p.gpc)) {
+    if (by_value(nc, p.ntiles, opt, p.gpc)) {
         uint8_t block[sizeof(BatchHeader) + kSmallTable * sizeof(CurveDesc)];
         write_block(block, p.curves.data(), nc, p.ntiles, p.nchunks, iters, o, time);
         e = enqueue_kernels(flux, time, trend, median, block, nullptr, ws->buf, opt.mode, true,
@@ -1108,7 +1110,7 @@ umi_status detrend_batch(const float* flux, const double* time, const int64_t* l
     b.recs = reinterpret_cast<ChunkRec*>(base + kRecsOff);
     b.cap_recs = kMaxChunks;
     const int grid = (int)std::min<int64_t>(v.ntiles, (int64_t)v.gpc * n_cu);
-    const bool value = by_value(v.ncurves, opt, v.gpc);
+    const bool value = by_value(v.ncurves, v.ntiles, opt, v.gpc);
     // from pageable host memory: the source is free again once the call returns
     if (!value && (e = hipMemcpyAsync(base + kBlockOff, g_block, block_bytes(v.ncurves),
                                       hipMemcpyHostToDevice, stream)) != hipSuccess)
@@ -1324,7 +1326,7 @@ umi_status umi_plan_run_ex(umi_plan* p, const int64_t* offsets, const int64_t* l
     std::lock_guard<std::mutex> lk(p->mu);
     hipError_t e;
     const int64_t nc = (int64_t)pk.curves.size();
-    if (nc > 0 && umi::by_value(nc, opt, pk.gpc)) {
+    if (nc > 0 && umi::by_value(nc, pk.ntiles, opt, pk.gpc)) {
         uint8_t block[sizeof(umi::BatchHeader) + umi::kSmallTable * sizeof(umi::CurveDesc)];
         umi::write_block(block, pk.curves.data(), nc, pk.ntiles, pk.nchunks, iters, o, p->time);
         e = umi::enqueue_kernels(p->flux, p->time, p->trend, p->median, block, nullptr, p->buf,

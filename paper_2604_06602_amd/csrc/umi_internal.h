@@ -133,6 +133,13 @@ struct SmallTable {
 };
 static_assert(sizeof(SmallTable) <= 2048, "SmallTable fits the kernel arguments");
 
+// Workgroups of the estimate kernel that one launch may have: HIP counts a
+// launch's threads in 32 bits.
+__host__ __device__ constexpr bool grid_fits(int64_t groups)
+{
+    return groups * kMainThreads <= (int64_t)UINT32_MAX;
+}
+
 // One record per chunk of the launch interface (launch_prepass): two words.
 constexpr int kSegWords = 1;
 struct ChunkRec {

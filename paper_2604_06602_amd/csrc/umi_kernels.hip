@@ -2250,6 +2250,7 @@ hipError_t launch_main(const float* flux, const int32_t*, const BatchHeader* hdr
         hdr = nullptr;
         curves = nullptr;
     }
+    if (!grid_fits(grid)) return hipErrorInvalidValue;
     // instances with sorted cores size their dynamic LDS for the batch's
     // largest core; it also holds the wavelet build's sequences
     const int core_floats = core_floats_for(feat >> kFeatBits);
