@@ -116,7 +116,9 @@ struct MainSmem {
     int tile;
     int nvalid;
     int multi;                            // the span holds more than one segment
-    int dead;                             // and some of its valid samples are not live
+    int check;                            // some of them may be shorter than W/3
+    int seg_n[2];                         // samples of the span's first and last segment (>= W/3: at least)
+    int any_live;                         // some segment is live
     uint32_t kmin, kmax;                  // smallest and largest staged key
     uint32_t wsum[kMainThreads / 64];     // per wave: bucket counts of its threads
 };
@@ -285,8 +287,9 @@ __device__ __forceinline__ int segment_beyond(const float* __restrict__ flux,
 }
 
 // From the span's validity and in-word start bits: the prefix counts, the
-// starts at word borders, and the live bits (valid samples of segments of at
-// least m_min valid samples).  Run by wave 0.
+// starts at word borders, and the sizes of the span's first and last segment
+// (the same one without starts), with their samples beyond the span.  Run by
+// wave 0.
 __device__ __forceinline__ void resolve_segments(MainSmem& sm, const float* __restrict__ flux,
                                                  const double* __restrict__ time, int len, int s0,
                                                  int N, int nwv, int m_min)
@@ -311,50 +314,77 @@ __device__ __forceinline__ void resolve_segments(MainSmem& sm, const float* __re
         sm.vpre[lane] = (uint32_t)(incl - c);
         sm.live[lane] = v;
     }
-    const bool multi = __ballot(s != 0) != 0;
+    const uint64_t starts = __ballot(s != 0);
+    const bool multi = starts != 0;
+    const bool check = total > 0 && m_min > 1 && (multi || total < m_min);
     if (lane == 0) {
         sm.nvalid = total;
         sm.multi = multi ? 1 : 0;
-        sm.dead = 0;
+        sm.check = check ? 1 : 0;
+        sm.any_live = 0;
     }
-    if (total == 0 || (!multi && total >= m_min)) return;
-    // segment by segment: a valid sample starts one, the first of the span too
+    if (!check) return;
     wave_lds_sync();
     const int wf = (int)__builtin_ctzll(some), wl = 63 - (int)__builtin_clzll(some);
-    int lo = 0, begin = 0;     // the segment's first sample (as a word walk), samples before it
-    int w = 0;
-    uint64_t bits = __shfl(s, 0, 64);
-    bool dead = false;
-    for (;;) {
-        while (bits == 0 && ++w < nwv) bits = __shfl(s, w, 64);
-        const bool last = w >= nwv;
-        const int hi = last ? N : 64 * w + (int)__builtin_ctzll(bits);
-        const int upto = last ? total
-                              : __builtin_amdgcn_readlane(incl - c, w) +
-                                    (int)__popcll(__shfl(v, w, 64) & ((bits & -bits) - 1ull));
-        int n = upto - begin;
-#pragma unroll 1
-        for (int dir = -1; dir <= 1; dir += 2) {
-            if (n > 0 && n < m_min && (dir < 0 ? begin == 0 : last))
-                n += segment_beyond(flux, time, len, dir < 0 ? s0 - 1 : s0 + N, dir,
-                                    !time ? 0.0 : (dir < 0 ? sm.tfirst[wf] : sm.tlast[wl]),
-                                    m_min - n);
-        }
-        if (n < m_min && upto > begin) {
-            // a dead segment: its samples [lo, hi) give NaN
-            dead = true;
-            const int a = min(max(lo - 64 * lane, 0), 64), b = min(max(hi - 64 * lane, 0), 64);
-            if (lane < nwv && a < b) {
-                const uint64_t up = b >= 64 ? ~0ull : (1ull << b) - 1ull;
-                sm.live[lane] &= ~(up & (~0ull << a));
-            }
-        }
-        if (last) break;
-        lo = hi;
-        begin = upto;
-        bits &= bits - 1;
+    int n0 = total, n1 = total;
+    if (multi) {  // samples before the first start, and from the last one on
+        const int w0 = (int)__builtin_ctzll(starts), w1 = 63 - (int)__builtin_clzll(starts);
+        const uint64_t sf = sm.sbits[w0], sl = sm.sbits[w1];
+        n0 = (int)sm.vpre[w0] + (int)__popcll(sm.vbits[w0] & ((sf & -sf) - 1ull));
+        n1 = total - (int)sm.vpre[w1] -
+             (int)__popcll(sm.vbits[w1] & ((1ull << (63 - (int)__builtin_clzll(sl))) - 1ull));
     }
-    if (lane == 0) sm.dead = dead ? 1 : 0;
+    if (n0 < m_min)
+        n0 += segment_beyond(flux, time, len, s0 - 1, -1, time ? sm.tfirst[wf] : 0.0, m_min - n0);
+    if (!multi) n1 = n0;
+    if (n1 < m_min)
+        n1 += segment_beyond(flux, time, len, s0 + N, 1, time ? sm.tlast[wl] : 0.0, m_min - n1);
+    if (lane == 0) {
+        sm.seg_n[0] = multi ? n0 : n1;
+        sm.seg_n[1] = n1;
+    }
+}
+
+// The live bits of a span with segments to check: every sample finds its
+// segment by the nearest start bits, a word per wave at a time.  (A walk of one
+// wave from segment to segment set the time where segments are many: 40 curves
+// of 18,000 with a sample a day, 510 us a call at W = 25 and 615 at W = 361,
+// against 48 and 34.)
+__device__ __forceinline__ void live_segments(MainSmem& sm, int nwv, int m_min)
+{
+    const int lane = thread_index() & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const uint64_t starts = __ballot(lane < nwv && sm.sbits[lane < nwv ? lane : 0] != 0);
+    const int total = sm.nvalid;
+    for (int w = wave; w < nwv; w += kMainThreads / 64) {
+        const uint64_t v = sm.vbits[w], s = sm.sbits[w];
+        const int pre = (int)sm.vpre[w];
+        // samples before the segment that reaches into the word, and before the
+        // first one that starts after it (-1: the span's first, its last)
+        int before = -1, after = -1;
+        const uint64_t lower = starts & ((1ull << w) - 1ull);
+        const uint64_t upper = starts & ~((2ull << w) - 1ull);
+        if (lower != 0) {
+            const int u = 63 - (int)__builtin_clzll(lower);
+            const int b = 63 - (int)__builtin_clzll(sm.sbits[u]);
+            before = (int)sm.vpre[u] + (int)__popcll(sm.vbits[u] & ((1ull << b) - 1ull));
+        }
+        if (upper != 0) {
+            const int u = (int)__builtin_ctzll(upper);
+            const uint64_t su = sm.sbits[u];
+            after = (int)sm.vpre[u] + (int)__popcll(sm.vbits[u] & ((su & -su) - 1ull));
+        }
+        const uint64_t upto = s & (~0ull >> (63 - lane)), from = s & ~(~0ull >> (63 - lane));
+        if (upto != 0)
+            before = pre + (int)__popcll(v & ((1ull << (63 - (int)__builtin_clzll(upto))) - 1ull));
+        if (from != 0) after = pre + (int)__popcll(v & ((from & -from) - 1ull));
+        const int n = before < 0 ? sm.seg_n[0] : (after < 0 ? sm.seg_n[1] : after - before);
+        const uint64_t bits = __ballot(((v >> lane) & 1ull) != 0 && n >= m_min);
+        if (lane == 0) {
+            sm.live[w] = bits;
+            if (bits != 0) sm.any_live = 1;
+        }
+    }
 }
 
 // k-th smallest (0-based) value of the level-0 sequence within [s, e).
@@ -2020,15 +2050,23 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
         // lanes per window (1: R windows per lane)
         const int G = (kFeat & kFeatSplit) && !cd.core ? split_lanes(cd.tile) : 1;
         __syncthreads();
-        if (wave == 0) resolve_segments(sm, f, tm, cd.len, s0, N, nwv, max(1, cd.W / 3));
+        const int m_min = max(1, cd.W / 3);
+        if (wave == 0) resolve_segments(sm, f, tm, cd.len, s0, N, nwv, m_min);
         __syncthreads();
-        const int nv = __builtin_amdgcn_readfirstlane(sm.nvalid);
+        const bool check = __builtin_amdgcn_readfirstlane(sm.check) != 0;
+        if (check) {
+            live_segments(sm, nwv, m_min);
+            __syncthreads();
+        }
+        // (of a span without a live sample nothing is sorted: its outputs are NaN)
+        const int nv = check && __builtin_amdgcn_readfirstlane(sm.any_live) == 0
+                           ? 0
+                           : __builtin_amdgcn_readfirstlane(sm.nvalid);
         const bool multi = __builtin_amdgcn_readfirstlane(sm.multi) != 0;
         // A tile is "simple" when every one of its windows is full: a small
-        // W, no curve end within reach, and the whole span valid, live and in
+        // W, no curve end within reach, and the whole span valid and in
         // one segment.  Its medians then come from per-window networks.
-        const bool simple = (kFeat & kFeatSmall) && nv == N && !multi &&
-                            __builtin_amdgcn_readfirstlane(sm.dead) == 0 && cd.W <= kSmallW &&
+        const bool simple = (kFeat & kFeatSmall) && nv == N && !multi && cd.W <= kSmallW &&
                             scale != UMI_SCALE_MAD && cd.window_days == 0.0 && t0 >= h &&
                             t1 + h <= cd.len && G == 1;
         int npad = 64;
