@@ -119,6 +119,10 @@ struct MainSmem {
     int check;                            // some of them may be shorter than W/3
     int seg_n[2];                         // samples of the span's first and last segment (>= W/3: at least)
     int any_live;                         // some segment is live
+    int walk;                             // bit 0, 1: seg_n[0], seg_n[1] is still short and its
+                                          // segment goes on before, behind
+    uint32_t walk_e[2];                   // curve sample walk_beyond() resumes at,
+    double walk_t[2];                     // and the time of the last valid one before it
     uint32_t kmin, kmax;                  // smallest and largest staged key
     uint32_t wsum[kMainThreads / 64];     // per wave: bucket counts of its threads
 };
@@ -250,21 +254,25 @@ __device__ __forceinline__ void word_prefix(const uint64_t* bits, uint32_t* pre,
 
 // Valid samples of the segment that reaches the span's border, beyond it:
 // from curve sample e in direction dir (the nearest valid sample inside the
-// span is at time tn), until `need` are found.  Run by one whole wave.
+// span is at time tn), until `need` are found or the segment ends (`open` is
+// cleared), in kNearSteps steps at most.  Run by one whole wave.  Indexes are
+// unsigned: one before the curve's start lies beyond its end.
+constexpr int kNearSteps = 4;
+
 __device__ __forceinline__ int segment_beyond(const float* __restrict__ flux,
-                                           const double* __restrict__ time, int len, int e, int dir,
-                                           double tn, int need)
+                                           const double* __restrict__ time, int len, uint32_t& e,
+                                           int dir, double& tn, int need, bool& open)
 {
     const int lane = thread_index() & 63;
     constexpr int K = 4;  // samples per lane and step, loaded together
     int got = 0;
-    while (got < need && e >= 0 && e < len) {
+    for (int step = 0; step < kNearSteps && got < need && e < (uint32_t)len; ++step) {
         float x[K];
         double t[K];
 #pragma unroll
         for (int u = 0; u < K; ++u) {
-            const int i = e + dir * (64 * u + lane);
-            const bool in = i >= 0 && i < len;
+            const uint32_t i = e + (uint32_t)(dir * (64 * u + lane));
+            const bool in = i < (uint32_t)len;
             x[u] = in ? flux[i] : __builtin_nanf("");
             t[u] = in && time ? time[i] : 0.0;
         }
@@ -277,13 +285,117 @@ __device__ __forceinline__ int segment_beyond(const float* __restrict__ flux,
             const double t_in = nearer ? ts : tn;
             const bool cut = ok && time && (dir > 0 ? t[u] - t_in : t_in - t[u]) > kGapDays;
             const uint64_t c = __ballot(cut);
-            if (c != 0) return got + (int)__popcll(m & ((c & -c) - 1ull));
+            if (c != 0) {
+                open = false;
+                return got + (int)__popcll(m & ((c & -c) - 1ull));
+            }
             got += (int)__popcll(m);
             if (m != 0) tn = __shfl(t[u], 63 - (int)__builtin_clzll(m), 64);
         }
-        e += dir * 64 * K;
+        e += (uint32_t)(dir * 64 * K);
     }
+    open = open && e < (uint32_t)len;
     return got;
+}
+
+// What a wave found of its part of a step of walk_beyond().
+struct WalkPart {
+    double first, last;  // times of its valid samples nearest to the span and furthest
+    int count, head;     // valid samples, and those before the first break among them
+    int cut;             // there is one
+    int reserved;
+};
+
+// segment_beyond() further out, by the whole workgroup: a step takes 16,384
+// samples, of which only the valid ones' times are read.  Where valid samples
+// are few and far apart a tile looks through up to the whole curve; done by one
+// wave, 256 samples a step, that set the time (one curve without times, us a
+// call: 118 valid samples among 2,000,000 at W = 361 10,200, now 730; one in
+// 1,000 of 200,000 at W = 1441 1,730, now 133; one in 1,000 of 100,000 at W =
+// 2047, in tiles of two positions, 20,800, now 2,600; with a pass over the
+// samples ahead, 108, 45 and 598).  What is left is latency, 1.4 us per 4,096
+// samples; loads of 16 or 32 samples a lane, or of the next while these are
+// counted, gain a tenth there, and cost the ordinary tiles registers (a curve of
+// 2,000,000 at W = 25 64, 69 and 74 us with 8, 16 and 32).  At worst a tile reads
+// the samples up to W/3 valid ones away on either side.
+__device__ __forceinline__ void walk_beyond(MainSmem& sm, WalkPart* parts,
+                                         const float* __restrict__ flux,
+                                         const double* __restrict__ time, int len, int m_min)
+{
+    constexpr int K = 8;      // samples per lane, loaded together
+    constexpr int kParts = 4; // of them per step
+    constexpr int kStep = kMainThreads * K * kParts;
+    const int tid = thread_index();
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool multi = sm.multi != 0;
+    const int walk = sm.walk;
+    int n = sm.seg_n[0];
+#pragma unroll 1
+    for (int side = 0; side < 2; ++side) {
+        if (side == 1 && multi) n = sm.seg_n[1];
+        if (((walk >> side) & 1) == 0) continue;
+        const uint32_t dir = side ? 1u : ~0u;
+        uint32_t e = sm.walk_e[side];
+        double tn = sm.walk_t[side];
+        bool open = true;
+        while (open && n < m_min && e < (uint32_t)len) {
+            WalkPart p = {0.0, 0.0, 0, 0, 0, 0};
+            uint32_t i0 = e + dir * (uint32_t)(wave * 64 * K * kParts + lane);
+#pragma unroll 1
+            for (int part = 0; part < kParts && !p.cut; ++part, i0 += dir * (64u * K)) {
+                float x[K];
+#pragma unroll
+                for (int u = 0; u < K; ++u)  // (outside the curve: sample 0, not counted)
+                    x[u] = flux[i0 + dir * (64u * u) < (uint32_t)len ? i0 + dir * (64u * u) : 0u];
+#pragma unroll
+                for (int u = 0; u < K; ++u) {
+                    const uint32_t i = i0 + dir * (64u * u);
+                    bool ok = i < (uint32_t)len && isfinite(x[u]);
+                    if (p.cut || __ballot(ok) == 0) continue;
+                    double t = 0.0;
+                    if (time != nullptr) {
+                        if (ok) t = time[i];
+                        ok = ok && isfinite(t);
+                    }
+                    const uint64_t m = __ballot(ok);
+                    if (m == 0) continue;
+                    if (time != nullptr) {
+                        const uint64_t nearer = m & ((1ull << lane) - 1ull);
+                        const double ts =
+                            __shfl(t, nearer ? 63 - (int)__builtin_clzll(nearer) : lane, 64);
+                        const double t_in = nearer ? ts : p.last;
+                        const uint64_t c = __ballot(ok && (nearer != 0 || p.count > 0) &&
+                                                    (side ? t - t_in : t_in - t) > kGapDays);
+                        if (c != 0) {
+                            p.head = p.count + (int)__popcll(m & ((c & -c) - 1ull));
+                            p.cut = 1;
+                        }
+                        if (p.count == 0) p.first = __shfl(t, (int)__builtin_ctzll(m), 64);
+                        p.last = __shfl(t, 63 - (int)__builtin_clzll(m), 64);
+                    }
+                    p.count += (int)__popcll(m);
+                }
+            }
+            if (lane == 0) parts[wave] = p;
+            __syncthreads();
+            for (int w = 0; w < kMainThreads / 64 && open && n < m_min; ++w) {
+                const WalkPart q = parts[w];
+                if (q.count == 0) continue;
+                if (time != nullptr && (side ? q.first - tn : tn - q.first) > kGapDays) {
+                    open = false;
+                } else {
+                    n += q.cut ? q.head : q.count;
+                    open = q.cut == 0;
+                    tn = q.last;
+                }
+            }
+            __syncthreads();
+            e += dir * (uint32_t)kStep;
+        }
+        if (tid == 0) sm.seg_n[multi ? side : 0] = n;
+    }
+    __syncthreads();
 }
 
 // From the span's validity and in-word start bits: the prefix counts, the
@@ -334,14 +446,23 @@ __device__ __forceinline__ void resolve_segments(MainSmem& sm, const float* __re
         n1 = total - (int)sm.vpre[w1] -
              (int)__popcll(sm.vbits[w1] & ((1ull << (63 - (int)__builtin_clzll(sl))) - 1ull));
     }
-    if (n0 < m_min)
-        n0 += segment_beyond(flux, time, len, s0 - 1, -1, time ? sm.tfirst[wf] : 0.0, m_min - n0);
+    uint32_t e0 = (uint32_t)(s0 - 1), e1 = (uint32_t)(s0 + N);
+    double t0 = time ? sm.tfirst[wf] : 0.0, t1 = time ? sm.tlast[wl] : 0.0;
+    bool open0 = n0 < m_min;
+    if (open0) n0 += segment_beyond(flux, time, len, e0, -1, t0, m_min - n0, open0);
     if (!multi) n1 = n0;
-    if (n1 < m_min)
-        n1 += segment_beyond(flux, time, len, s0 + N, 1, time ? sm.tlast[wl] : 0.0, m_min - n1);
+    bool open1 = n1 < m_min;
+    if (open1) n1 += segment_beyond(flux, time, len, e1, 1, t1, m_min - n1, open1);
+    if (!multi) n0 = n1;
+    const int walk = (open0 && n0 < m_min ? 1 : 0) | (open1 && n1 < m_min ? 2 : 0);
     if (lane == 0) {
-        sm.seg_n[0] = multi ? n0 : n1;
+        sm.seg_n[0] = n0;
         sm.seg_n[1] = n1;
+        sm.walk = walk;
+        sm.walk_e[0] = e0;
+        sm.walk_e[1] = e1;
+        sm.walk_t[0] = t0;
+        sm.walk_t[1] = t1;
     }
 }
 
@@ -355,7 +476,6 @@ __device__ __forceinline__ void live_segments(MainSmem& sm, int nwv, int m_min)
     const int lane = thread_index() & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const uint64_t starts = __ballot(lane < nwv && sm.sbits[lane < nwv ? lane : 0] != 0);
-    const int total = sm.nvalid;
     for (int w = wave; w < nwv; w += kMainThreads / 64) {
         const uint64_t v = sm.vbits[w], s = sm.sbits[w];
         const int pre = (int)sm.vpre[w];
@@ -2055,6 +2175,8 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
         __syncthreads();
         const bool check = __builtin_amdgcn_readfirstlane(sm.check) != 0;
         if (check) {
+            if (__builtin_amdgcn_readfirstlane(sm.walk) != 0)
+                walk_beyond(sm, reinterpret_cast<WalkPart*>(&wv), f, tm, cd.len, m_min);
             live_segments(sm, nwv, m_min);
             __syncthreads();
         }

@@ -87,3 +87,83 @@ def test_many_segments_cost_no_more_than_one(torch, umi, W):
     one = call_us(torch, umi, flux, np.arange(n) * DT, 40, W)
     many = call_us(torch, umi, flux, np.arange(n) * 1.0, 40, W)
     assert many < 2.5 * one, (many, one)
+
+
+# steps outwards: four of 256 samples by a wave, then of 16,384 by the
+# workgroup, 2,048 a wave, 512 at a time
+FAR = [1, 255, 1023, 1025, 1536, 3071, 9000, 17407, 17409, 40000]
+
+
+def _far_samples(W, tile, rng):
+    """A group of valid samples in one tile, W/3 of them only with another far
+    outside its staged span: after or before it, on both sides, one sample too
+    few, behind a break, with invalid times between."""
+    m = max(2, W // 3)
+    dt = 1e-6  # no break by itself, however far
+    for far in FAR:
+        for short in (0, 1):
+            for sides in (1, 2, 3):
+                n = 2 * (far + tile + W) + max(300, 2 * m + 20)
+                here, most = n // 2, m // 2
+                f = np.full(n, np.nan)
+                f[here:here + most] = rng.normal(1, 1e-3, most)
+                rest = m - most - short
+                for side, k in ((1, rest if sides == 1 else rest - rest // 2 * (sides == 3)),
+                                (2, rest if sides == 2 else rest // 2)):
+                    if not sides & side:
+                        continue
+                    at = here + most + W + tile + far if side == 1 else here - W - tile - far - k
+                    f[at:at + k] = rng.normal(1, 1e-3, k)
+                t = np.arange(n) * dt
+                yield f, t
+                if short == 0:
+                    u = t.copy()                      # a break where nothing is valid
+                    u[here + most + W // 2:] += 0.75
+                    yield f, u
+                    u = t.copy()                      # invalid by their times
+                    g = f.copy()
+                    bad = rng.random(n) < 0.3
+                    g[bad & np.isnan(f)] = 1.0
+                    u[bad & np.isnan(f)] = np.nan
+                    yield g, u
+    n = 60000                                         # one in 500, breaks among them
+    f = np.full(n, np.nan)
+    f[::500] = rng.normal(1, 1e-3, f[::500].size)
+    t = np.arange(n) * dt
+    yield f, t
+    for at in (4000, 20001, 20500, 52000):
+        t = t.copy()
+        t[at:] += 0.75
+        yield f, t
+
+
+@pytest.mark.parametrize("W,tile", [(25, 300), (361, 1536), (361, 64), (2047, 2)])
+def test_far_samples_against_oracle(torch, umi, oracle_lib, W, tile):
+    rng = np.random.default_rng(23 + W)
+    curves = [(np.asarray(f, np.float32), t, W) for f, t in _far_samples(W, tile, rng)]
+    if W == 2047:
+        curves = curves[:12] + curves[-3:]
+    b = synth.lightcurves.pack(curves)
+    mag = window_magnitude(b.flux, b.time, b.lengths, b.W, oracle_lib)
+    g = run_batch(torch, umi, b.flux, b.time, b.lengths, b.W, launch=umi.LaunchOptions(tile=tile))
+    o = oracle_lib.detrend_batch(b.flux, b.time, b.lengths, b.W)
+    live = np.isfinite(o[0])
+    assert live.any() and (np.isfinite(b.flux) & ~live).any()
+    assert_parity(*g, *o, scale=mag, what="far samples W=%d tile %d" % (W, tile))
+    # without times nothing ends a segment
+    flux = np.where(np.isfinite(b.time), b.flux, np.nan).astype(np.float32)
+    g = run_batch(torch, umi, flux, None, b.lengths, b.W, launch=umi.LaunchOptions(tile=tile))
+    o = oracle_lib.detrend_batch(flux, None, b.lengths, b.W)
+    assert_parity(*g, *o, scale=mag, what="no times W=%d tile %d" % (W, tile))
+
+
+@pytest.mark.parametrize("W,every", [(361, 1000), (1441, 1000), (721, 0)])
+def test_sparse_curves_cost_little_more_than_full_ones(torch, umi, W, every):
+    """One sample in 1,000 valid, or fewer than W/3 among all, without times."""
+    rng = np.random.default_rng(W)
+    n = 200_000
+    flux = rng.normal(1, 1e-3, n)
+    keep = rng.random(n) < 1 / every if every else np.isin(np.arange(n), rng.choice(n, W // 3 - 2))
+    full = call_us(torch, umi, flux, None, 1, W)
+    sparse = call_us(torch, umi, np.where(keep, flux, np.nan), None, 1, W)
+    assert sparse < 3 * full, (sparse, full)
