@@ -1809,14 +1809,18 @@ __device__ __forceinline__ void core_phase1(const MainSmem& sm, const Wavelet& w
         zero = true;
     }
     if (zero) {
-        // n+ by counting, and the negative zeros of a zero median
-        int above = 0, negative = 0;
-        for (int j = 0; j < (int)n; ++j) {
-            above += x[j] > m ? 1 : 0;
-            negative += (int)(__float_as_uint(x[j]) >> 31);
-        }
-        nplus = (uint32_t)above;
-        if (m == 0.0f) m = k < negative ? -0.0f : 0.0f;
+        // n+ by counting, and the negative zeros of a zero median; each lane
+        // of the pair takes every second sample (one after the other by both:
+        // one curve of 18,000 at W = 721 with values of three digits around
+        // zero 66 us against 38, 100 at W = 361 480 against 310)
+        uint32_t above = 0, negative = 0;
+        strided_sweep<2>(x, lane & 1, (int)n, [&](float v) {
+            above += v > m ? 1u : 0u;
+            negative += __float_as_uint(v) >> 31;
+        });
+        nplus = group_sum_u32<2>(above);
+        const int minus = (int)group_sum_u32<2>(negative);
+        if (m == 0.0f) m = k < minus ? -0.0f : 0.0f;
     }
 }
 

@@ -1,0 +1,59 @@
+"""Sorted cores on values that leave the ordinary way, against the FP64 oracle
+and, in time, against ordinary noise: medians of zero of either sign among ties,
+and cores most of whose samples are equal."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import synth
+from tests.test_gpu_parity import assert_parity, run_batch, window_magnitude
+from tests.test_gpu_sparse import call_us
+
+pytestmark = pytest.mark.gpu
+
+DT = 2 / 1440
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as _t
+    if not _t.cuda.is_available():
+        pytest.skip("no GPU")
+    return _t
+
+
+@pytest.fixture(scope="module")
+def umi(torch):
+    import paper_2604_06602_amd as _u
+    return _u
+
+
+def _zeros(n, rng):
+    """Values whose windows' medians are zero."""
+    yield np.round(1e-3 * rng.standard_normal(n), 3)
+    yield rng.choice(np.array([-0.0, 0.0, 1e-3, -1e-3]), n)
+    yield np.where(rng.random(n) < 0.5, -0.0, 1e-3 * np.abs(rng.standard_normal(n)))
+    yield np.where(rng.random(n) < 0.5, 0.0, -1e-3 * np.abs(rng.standard_normal(n)))
+    yield np.full(n, -0.0)
+
+
+@pytest.mark.parametrize("W", [117, 361, 1441])
+def test_medians_of_zero(torch, umi, oracle_lib, W):
+    rng = np.random.default_rng(W)
+    n = 2 * W + 700
+    b = synth.lightcurves.pack([(f.astype(np.float32), np.arange(n) * DT, W)
+                                for f in _zeros(n, rng)])
+    mag = window_magnitude(b.flux, b.time, b.lengths, b.W, oracle_lib)
+    g = run_batch(torch, umi, b.flux, b.time, b.lengths, b.W)
+    o = oracle_lib.detrend_batch(b.flux, b.time, b.lengths, b.W)
+    assert_parity(*g, *o, scale=mag, what="zero medians W=%d" % W)
+
+
+def test_medians_of_zero_cost_little_more_than_others(torch, umi):
+    n, W = 18000, 361
+    rng = np.random.default_rng(2)
+    noise = 1e-3 * rng.standard_normal(n)
+    other = call_us(torch, umi, 1 + noise, np.arange(n) * DT, 100, W)
+    zero = call_us(torch, umi, np.round(noise, 3), np.arange(n) * DT, 100, W)
+    assert zero < 2.2 * other, (zero, other)
