@@ -1665,6 +1665,83 @@ __device__ __forceinline__ uint32_t wave_or_scan(uint32_t v)
     return v | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);
 }
 
+// Phase 1 of a window by its samples' ranks in the sorted tile: those of a core
+// of nc samples from cca on, which core_collect() left marked, and those of the
+// nl samples before it and the nr after it, one by one (nc = 0: the nl samples
+// from ca on).  The median has the first rank that k + 1 of them do not pass, by
+// bisection.  For time windows whose lengths differ by more samples than a group
+// has slots for, and groups without a core.  Run by pairs of lanes, which take
+// every second sample.  (Over all samples of such windows, by both lanes and with
+// two more passes, this took twice as long as all the sums; with those sample by
+// sample too, 40 curves of 18,000 at random times, W = 1081 and 648 samples a
+// window, took 1,700 us a call, now 305; in bursts of 60, W = 361, 697, now 204.)
+__device__ __forceinline__ void rank_phase1(const MainSmem& sm, const Wavelet& wv,
+                                            const CoreLds& cw, int nv, int cca, int nc, int ca,
+                                            int nl, int nr, float& m, uint32_t& nplus)
+{
+    const int half = thread_index() & 1;
+    const int k = (nl + nc + nr - 1) >> 1;
+    const uint2* const marks = reinterpret_cast<const uint2*>(cw.over);
+    const uint16_t* const rl = wv.seq[0] + ca;
+    const uint16_t* const rr = wv.seq[0] + cca + nc;
+    int lo = 0, hi = nv - 1;
+    while (lo < hi) {
+        const int at = (lo + hi) >> 1;
+        uint32_t below = 0;
+        if (nc > 0 && half == 0) {
+            const uint2 b = marks[at >> 5];
+            below = b.y + (uint32_t)__popc(b.x & (~0u >> (31u - ((uint32_t)at & 31u))));
+        }
+#pragma unroll 8
+        for (int j = half; j < nl; j += 2) below += (int)rl[j] <= at ? 1u : 0u;
+#pragma unroll 8
+        for (int j = half; j < nr; j += 2) below += (int)rr[j] <= at ? 1u : 0u;
+        if ((int)group_sum_u32<2>(below) > k)
+            hi = at;
+        else
+            lo = at + 1;
+    }
+    // its value: the core's, or that of the one sample of this rank
+    const float* const xl = sm.xv + ca;
+    const float* const xr = sm.xv + cca + nc;
+    int next = 0;  // core samples of this rank or below
+    bool of_core = false;
+    if (nc > 0) {
+        const uint2 b = marks[lo >> 5];
+        const uint32_t bit = 1u << ((uint32_t)lo & 31u);
+        next = (int)(b.y + (uint32_t)__popc(b.x & (bit - 1u)));
+        of_core = (b.x & bit) != 0;
+        if (of_core) m = cw.cv[next++];
+    }
+    if (!of_core) {
+        uint32_t v = 0;
+#pragma unroll 8
+        for (int j = half; j < nl; j += 2)
+            if ((int)rl[j] == lo) v = __float_as_uint(xl[j]);
+#pragma unroll 8
+        for (int j = half; j < nr; j += 2)
+            if ((int)rr[j] == lo) v = __float_as_uint(xr[j]);
+        m = __uint_as_float(group_sum_u32<2>(v));
+    }
+    // n+: the core's from the first value above it, and the others above it
+    if (next < nc && cw.cv[next] == m) {
+        int last = next, end = nc;  // cv[last] == m
+        while (end - last > 1) {
+            const int at = (last + end) >> 1;
+            if (cw.cv[at] == m)
+                last = at;
+            else
+                end = at;
+        }
+        next = end;
+    }
+    uint32_t above = 0;
+    auto count = [&](float v) { above += v > m ? 1u : 0u; };
+    strided_sweep<2>(xl, half, nl, count);
+    strided_sweep<2>(xr, half, nr, count);
+    nplus = group_sum_u32<2>(above) + (uint32_t)(nc - next);
+}
+
 // Phase 1 (Section 2.1) of a group's windows.  A window is the core plus at
 // most 31 edge samples (63 with time windows, which differ in length), so its
 // median lies at one of the kRanks core samples around the core's middle, or
@@ -1676,7 +1753,8 @@ __device__ __forceinline__ uint32_t wave_or_scan(uint32_t v)
 // sample at or below the median.  The median is that sample or one of the few
 // edge samples between it and the next.  No tile-wide structure beyond the
 // sorted tile.  Values compare as floats; a median of zero takes its sign by
-// counting.  Windows without a core bisect the ranks.  Also n+ of Eq. 1.
+// counting.  Also n+ of Eq. 1.  Windows that do not fit the edge samples' slots,
+// and groups without a core, take theirs from rank_phase1().
 // Against the wavelet matrix (a build of 44 barriers, then a descent per
 // window): 1,000 x 18,000 samples at W = 361 without iterations 1.50 -> 0.88 ms.
 template <int kRanks>
@@ -1688,7 +1766,7 @@ __device__ __forceinline__ void core_phase1(const MainSmem& sm, const Wavelet& w
     static_assert(kRanks == 32 || kRanks == 64, "a rank per lane of a wave or of its half");
     const int lane = thread_index() & 63;
     const int k = (int)((n - 1) >> 1);
-    bool found = false, zero = false;
+    bool zero = false;
     if (core) {
         const int r0 = (nc >> 1) - kRanks / 2;
         const float* const mid = cw.cv + r0;
@@ -1762,7 +1840,6 @@ __device__ __forceinline__ void core_phase1(const MainSmem& sm, const Wavelet& w
                 t -= cnt;
                 last = least;
             }
-            found = true;
             // an edge sample equal to a core sample ranks below it, so what
             // else ties with the median after it are the next core samples:
             // the first one above it by a galloping search
@@ -1788,39 +1865,18 @@ __device__ __forceinline__ void core_phase1(const MainSmem& sm, const Wavelet& w
         }
         wave_lds_sync();  // the masks give way to the block table
     }
-    const float* const x = sm.xv + ca;
-    if (live && !found) {
-        // the rank of which k + 1 of the window's samples are at or below, by
-        // bisection, and its sample
-        const uint16_t* const rank = wv.seq[0] + ca;
-        int lo = 0, hi = nv - 1;
-        while (lo < hi) {
-            const int at = (lo + hi) >> 1;
-            int below = 0;
-#pragma unroll 8
-            for (int j = 0; j < (int)n; ++j) below += (int)rank[j] <= at ? 1 : 0;
-            if (below > k)
-                hi = at;
-            else
-                lo = at + 1;
-        }
-        for (int j = 0; j < (int)n; ++j)
-            if ((int)rank[j] == lo) m = x[j];
-        zero = true;
-    }
     if (zero) {
         // n+ by counting, and the negative zeros of a zero median; each lane
         // of the pair takes every second sample (one after the other by both:
         // one curve of 18,000 at W = 721 with values of three digits around
         // zero 66 us against 38, 100 at W = 361 480 against 310)
         uint32_t above = 0, negative = 0;
-        strided_sweep<2>(x, lane & 1, (int)n, [&](float v) {
-            above += v > m ? 1u : 0u;
+        strided_sweep<2>(sm.xv + ca, lane & 1, (int)n, [&](float v) {
+            above += v > 0.0f ? 1u : 0u;
             negative += __float_as_uint(v) >> 31;
         });
         nplus = group_sum_u32<2>(above);
-        const int minus = (int)group_sum_u32<2>(negative);
-        if (m == 0.0f) m = k < minus ? -0.0f : 0.0f;
+        m = k < (int)group_sum_u32<2>(negative) ? -0.0f : 0.0f;
     }
 }
 
@@ -1953,6 +2009,15 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv
         const bool wide = timed && nc >= 2 * kCoreMin;
         const bool fits = !timed || ((uint32_t)nl <= 32u && (uint32_t)nr <= 32u &&
                                      nl + nr < (wide ? 2 * kCoreGroup : kCoreGroup));
+        // (a window that does not hold the core: times that decrease)
+        const bool holds = core && nl >= 0 && nr >= 0;
+        const bool ranked = live && !(core && fits);
+        if (__any(ranked)) {
+            if (ranked)
+                rank_phase1(sm, wv, cw, nv, cca, holds ? nc : 0, (int)ca, holds ? nl : (int)n,
+                            holds ? nr : 0, m, nplus);
+            wave_lds_sync();
+        }
         if ((kFeat & kFeatExtra) && wide)
             core_phase1<2 * kCoreGroup>(sm, wv, cw, nv, core, fits, nc, cca, live, ca, n, m, nplus);
         else
@@ -1977,6 +2042,17 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv
 #pragma unroll
         for (int i = kCoreGroup / 2 - 1; i < kEdgeRegs; ++i) take(i);
         const float* const x = sm.xv + ca;
+        // time windows with more edge samples than slots read theirs where
+        // they are
+        const bool more_edges = (kFeat & kFeatExtra) && core && live && holds && !fits;
+        const bool any_more = (kFeat & kFeatExtra) && __any(more_edges);
+        auto far_edges = [&](auto&& f) {
+            auto centred = [&](float v) { f(v - centre); };
+            strided_sweep<2>(x, half, more_edges ? nl : 0, centred);
+            strided_sweep<2>(cw.edge + 32, half, more_edges ? nc - nb * kCoreBlock : 0, f);
+            strided_sweep<2>(sm.xv + cca + nc, half, more_edges ? nr : 0, centred);
+        };
+        const bool served = (live && fits) || more_edges;
 
         // Phase 2 (Eq. 1)
         float ssq = 0.0f, rest = 0.0f;
@@ -1988,6 +2064,7 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv
         bool direct = true;
         if (core) {
             core_edges(e, xe, half, ne, more, up2);
+            if (any_more) far_edges(up2);
             const int b = core_find(cw, root, nb, at);
             core_block(cw.cv, b, half, up2);
             const int b1 = b + 1;
@@ -1999,7 +2076,7 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv
             const float sum = __builtin_fmaf(-2.0f * delta, d1, whole);
             const float back = 1.0f / unit;  // a power of two
             rest = sum * back * back;
-            direct = !(fits && sum >= 0.125f * whole && whole < 1e30f);
+            direct = !(served && sum >= 0.125f * whole && whole < 1e30f);
         }
         if (live && direct) {
             at = m;
@@ -2048,6 +2125,7 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv
             direct = true;
             if (core) {
                 core_edges(e, xe, half, ne, more, acc);
+                if (any_more) far_edges(acc);
                 const int bm = core_find(cw, root, nb, mu_c - knot);
                 const int bo = __float_as_int(dpp_xor1(__int_as_float(bm)));
                 const int b0 = half ? bo : bm, b1 = half ? bm : bo;
@@ -2073,7 +2151,7 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv
                 core_poly(cw.g, e0, e1, delta, kside, pw, pz);
                 sw = group_sum<2>(sw + pw);
                 swv = group_sum<2>(__builtin_fmaf(fside, pz, swv));
-                direct = !(fits && scaled && far * ka <= kCoreReach && sw > 0.03125f * (float)(int)n);
+                direct = !(served && scaled && far * ka <= kCoreReach && sw > 0.03125f * (float)(int)n);
             }
             if (act && direct) {
                 bb = -mu * k;

@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 
 import synth
+from tests.test_gpu_cores import _shapes
 from tests.test_gpu_parity import assert_parity, run_batch, window_magnitude
 from tests.test_gpu_sparse import call_us
 
@@ -80,3 +81,35 @@ def test_short_time_windows_cost_little_more_than_index_windows(torch, umi):
     index = call_us(torch, umi, flux, time, 40, W)
     short = call_us(torch, umi, flux, time, 40, W, window_days=0.05)
     assert short < 4 * index, (short, index)
+
+
+@pytest.mark.parametrize("W", [121, 361, 1081])
+def test_uneven_windows_of_any_values(torch, umi, oracle_lib, W):
+    """Windows of neighbouring samples that differ by more samples than a group
+    of windows has slots for, over ties, steps, outliers and signed zeros."""
+    rng = np.random.default_rng(29 + W)
+    curves = []
+    for f, t in _shapes(W, rng):
+        n = len(f)
+        u = np.sort(rng.random(n)) * (t[-1] - t[0])
+        burst = np.cumsum(np.where(np.arange(n) % 60 == 0, DT * 30, DT / 4))
+        curves += [(np.asarray(f, np.float32), x, W) for x in (u, burst)]
+    b = synth.lightcurves.pack(curves)
+    mag = window_magnitude(b.flux, b.time, b.lengths, b.W, oracle_lib)
+    for a, c, share in [(2.0, 5.0, 0.6), (1.0, 5.0, 0.3), (10.0, 2.5, 0.6)]:
+        L = share * W * DT
+        g = run_batch(torch, umi, b.flux, b.time, b.lengths, b.W, alpha=a, c=c, window_days=L)
+        o = oracle_lib.detrend_batch(b.flux, b.time, b.lengths, b.W, alpha=a, c=c, window_days=L)
+        assert_parity(*g, *o, scale=mag, what="uneven W=%d a=%g L=%g" % (W, a, L))
+
+
+@pytest.mark.parametrize("W,kind", [(1081, "random"), (361, "bursts")])
+def test_uneven_windows_cost_little_more_than_even_ones(torch, umi, W, kind):
+    n, L = 18000, 0.9 * W / 1081
+    rng = np.random.default_rng(3)
+    flux = 1 + 1e-3 * rng.standard_normal(n)
+    uneven = (np.sort(rng.random(n)) * n * DT if kind == "random" else
+              np.cumsum(np.where(np.arange(n) % 60 == 0, DT * 30, DT / 4)))
+    even = call_us(torch, umi, flux, np.arange(n) * DT, 40, W, window_days=L)
+    us = call_us(torch, umi, flux, uneven, 40, W, window_days=L)
+    assert us < 4 * even, (us, even)
