@@ -1582,7 +1582,12 @@ __device__ __forceinline__ bool core_build(const CoreLds& cw, int nc, float quan
     // the centre, and a power of two near the core's spread
     const int cq = (int)(quantile * (float)nc);
     centre = cw.cv[cq];
-    const float spread = cw.cv[(27 * nc) >> 5] - cw.cv[(5 * nc) >> 5];
+    float spread = cw.cv[(27 * nc) >> 5] - cw.cv[(5 * nc) >> 5];
+    // most of the core equal: the spread of the rest (summed sample by sample,
+    // 100 curves of 18,000 with 75 or 97 of 100 samples equal took 2,900 us at
+    // W = 1441 instead of 970 and 1,000)
+    if (!(spread > 0.0f)) spread = cw.cv[(31 * nc) >> 5] - cw.cv[nc >> 5];
+    if (!(spread > 0.0f)) spread = cw.cv[nc - 1] - cw.cv[0];
     const int ex = __builtin_amdgcn_frexp_expf(spread);
     if (!(spread > 0.0f) || ex < -60 || ex > 60) return false;
     unit = __builtin_amdgcn_ldexpf(1.0f, -ex);

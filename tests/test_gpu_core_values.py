@@ -57,3 +57,34 @@ def test_medians_of_zero_cost_little_more_than_others(torch, umi):
     other = call_us(torch, umi, 1 + noise, np.arange(n) * DT, 100, W)
     zero = call_us(torch, umi, np.round(noise, 3), np.arange(n) * DT, 100, W)
     assert zero < 2.2 * other, (zero, other)
+
+
+@pytest.mark.parametrize("W", [117, 361, 1441])
+def test_mostly_equal_cores(torch, umi, oracle_lib, W):
+    """Half to all but a few of a core's samples equal, the rest noise on both
+    sides, on one side, or far out."""
+    rng = np.random.default_rng(31 + W)
+    n = 2 * W + 700
+    curves = []
+    for share in (0.6, 0.75, 0.9, 0.97, 0.999):
+        for rest in (1e-3 * rng.standard_normal(n), 1e-3 * np.abs(rng.standard_normal(n)),
+                     -1e-3 * np.abs(rng.standard_normal(n)), 1e-3 * rng.standard_cauchy(n)):
+            curves.append((np.where(rng.random(n) < share, 1.0, 1 + rest).astype(np.float32),
+                           np.arange(n) * DT, W))
+    b = synth.lightcurves.pack(curves)
+    mag = window_magnitude(b.flux, b.time, b.lengths, b.W, oracle_lib)
+    for a, c in [(2.0, 5.0), (10.0, 2.5), (1.0, 5.0)]:
+        g = run_batch(torch, umi, b.flux, b.time, b.lengths, b.W, alpha=a, c=c)
+        o = oracle_lib.detrend_batch(b.flux, b.time, b.lengths, b.W, alpha=a, c=c)
+        assert_parity(*g, *o, scale=mag, what="mostly equal W=%d a=%g" % (W, a))
+
+
+@pytest.mark.parametrize("share", [0.75, 0.97])
+def test_mostly_equal_cores_cost_little_more_than_others(torch, umi, share):
+    n, W = 18000, 1441
+    rng = np.random.default_rng(4)
+    noise = 1 + 1e-3 * rng.standard_normal(n)
+    other = call_us(torch, umi, noise, np.arange(n) * DT, 40, W)
+    equal = call_us(torch, umi, np.where(rng.random(n) < share, 1.0, noise), np.arange(n) * DT,
+                    40, W)
+    assert equal < 3 * other, (equal, other)
