@@ -1973,25 +1973,41 @@ __device__ __forceinline__ void core_edges(const float (&e)[kEdgeRegs], const fl
 // cut-off of the side summed by power sums.
 constexpr float kCoreReach = 0.5f;
 
-// The windows of one group, a pair of lanes each: the lanes take every second
+// Where the next live segment starts after curve position p, which is staged
+// (s0 + N or more: not within the next 63 positions).
+__device__ __forceinline__ int next_segment(const MainSmem& sm, int s0, int N, int p)
+{
+    const uint32_t i = (uint32_t)(p + 1 - s0);
+    const uint32_t w = i >> 6, b = i & 63u;
+    uint64_t m = (sm.sbits[w] & sm.live[w]) >> b;
+    if (b != 0u && 64u * (w + 1u) <= (uint32_t)N) m |= (sm.sbits[w + 1] & sm.live[w + 1]) << (64u - b);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)m);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(m >> 32));
+    const uint64_t u = ((uint64_t)hi << 32) | lo;
+    return u != 0 ? p + 1 + (int)__builtin_ctzll(u) : s0 + N;
+}
+
+// The windows of one group at positions [from, to), all of the group's of one
+// segment, a pair of lanes each: the lanes take every second
 // edge sample, half of each block summed one by one, and one side's power
 // sums; their sums meet by DPP, so both hold the same bits and iterate in step.
 template <int kFeat>
 __device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv, const CoreLds& cw,
                                            int nv, const CurveDesc& cd, int h, int s0, int N, int t0,
-                                           int t1, int g0, bool multi, const CoreParams& q, float c,
-                                           int iters, const double* __restrict__ time,
+                                           int t1, int g0, int from, int to, bool multi,
+                                           const CoreParams& q, float c, int iters, const double* __restrict__ time,
                                            float* __restrict__ trend, float* __restrict__ median,
                                            float* __restrict__ detrended)
 {
     const int lane = thread_index() & 63;
     const int half = lane & 1;
     const int p = g0 + (lane >> 1);
-    const bool mine = p >= t0 && p < t1;
+    const bool part = p >= from && p < to;
+    const bool mine = part && p >= t0 && p < t1;
     uint32_t ca = 0, n = 0;
     // the ranges of positions outside the tile count too (cut at the staged
     // span, which the core never reaches): the core is the group's
-    const bool alive = p < cd.len && window_range<kFeat, true>(sm, cd, time, multi, h, s0, N, p, ca, n);
+    const bool alive = part && window_range<kFeat, true>(sm, cd, time, multi, h, s0, N, p, ca, n);
     const bool live = alive && mine;
     const uint64_t alive_m = __ballot(alive);
     const uint64_t live_m = __ballot(live);
@@ -2440,10 +2456,18 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
         if (core_tile) {
             const CoreLds cw = core_lds(cores + kRankBytes / 4 + wave * core_floats, core_cap(cd.W));
             const CoreParams cp = core_params(alpha);
-            for (int g0 = (t0 & -kCoreGroup) + wave * kCoreGroup; g0 < t1;
-                 g0 += kCoreGroup * (kMainThreads / 64))
-                core_group<kFeat>(sm, wv, cw, nv, cd, h, s0, N, t0, t1, g0, multi, cp, c,
+            // where a segment ends inside a group, the windows on either side
+            // share nothing and have a core each (as one group without a core,
+            // 100 curves of 18,000 in segments of 500 took 1,470 us at W = 1441, now
+            // 670, and one at W = 721 80, now 31)
+            for (int from = (t0 & -kCoreGroup) + wave * kCoreGroup; from < t1;) {
+                const int g0 = from & -kCoreGroup;
+                int to = min(g0 + kCoreGroup, cd.len);
+                if (multi) to = min(to, next_segment(sm, s0, N, from));
+                core_group<kFeat>(sm, wv, cw, nv, cd, h, s0, N, t0, t1, g0, from, to, multi, cp, c,
                                   iters, time, trend, median, detrended);
+                from = to - g0 == kCoreGroup ? g0 + kCoreGroup * (kMainThreads / 64) : to;
+            }
             __syncthreads();
             continue;
         }

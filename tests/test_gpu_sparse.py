@@ -167,3 +167,37 @@ def test_sparse_curves_cost_little_more_than_full_ones(torch, umi, W, every):
     full = call_us(torch, umi, flux, None, 1, W)
     sparse = call_us(torch, umi, np.where(keep, flux, np.nan), None, 1, W)
     assert sparse < 3 * full, (sparse, full)
+
+
+def test_segments_of_a_group_do_not_depend_on_the_tile(torch, umi):
+    """Groups of wide windows in which one or two segments end: each segment's
+    windows have a core of their own, whatever tile the group lies in."""
+    rng = np.random.default_rng(41)
+    curves = []
+    for W in (117, 121, 361, 721):
+        n, m = 4000, W // 3
+        for lo, hi in [(m, m + 3), (m, 2 * m), (m - 3, m + 4)]:
+            at = np.cumsum(rng.integers(lo, hi, n))
+            cut = np.zeros(n)
+            cut[at[at < n]] = 0.75
+            f = rng.normal(1, 1e-3, n)
+            f[rng.random(n) < 0.01] = np.nan
+            curves.append((f.astype(np.float32), np.arange(n) * DT + np.cumsum(cut), W))
+    b = synth.lightcurves.pack(curves)
+    ref = run_batch(torch, umi, b.flux, b.time, b.lengths, b.W, launch=umi.LaunchOptions(tile=1024))
+    assert np.isfinite(ref[0]).any()
+    for tile in (1300, 640, 257, 96, 33):
+        out = run_batch(torch, umi, b.flux, b.time, b.lengths, b.W,
+                        launch=umi.LaunchOptions(tile=tile))
+        for a, r in zip(out, ref):
+            assert np.array_equal(a.view(np.uint32), r.view(np.uint32)), tile
+
+
+@pytest.mark.parametrize("W", [361, 1441])
+def test_segments_of_half_a_window_cost_little_more_than_one(torch, umi, W):
+    n = 18000
+    flux = np.random.default_rng(W).normal(1, 1e-3, n)
+    one = call_us(torch, umi, flux, np.arange(n) * DT, 100, W)
+    cut = np.floor(np.arange(n) / (W // 3 + 20)) * 0.7
+    many = call_us(torch, umi, flux, np.arange(n) * DT + cut, 100, W)
+    assert many < 1.8 * one, (many, one)
