@@ -1573,15 +1573,25 @@ __device__ __forceinline__ CoreParams core_params(float alpha)
 // residual's rounding is relative to the deviation and not to the flux
 // (trends' error against 64 bits at alpha = 10, c = 2.5, W = 361: 6.61e-8
 // without, 6.31e-8 with, 6.39e-8 for windows summed sample by sample; the
-// shift is free, the table's pass reads every value anyway).  False when the deviations' scale is unusable.
+// shift is free, the table's pass reads every value anyway).
+// The sums start at that edge of the centre's block behind which fewer of its
+// values lie far away: where a step or an eclipse ends inside the block, sums
+// that took in the far values would lose the near ones' digits (a step of 300
+// times the scale: trends off by 6e-4 instead of 1e-7).  `gap` is how far the
+// values on the other side reach, below the centre when `below`.  Of the other
+// blocks between the centre and a window's location all values lie within its
+// cut-offs.  False when the deviations' scale is unusable.
 __device__ __forceinline__ bool core_build(const CoreLds& cw, int nc, float quantile, float& centre,
-                                           float& unit)
+                                           float& unit, float& gap, bool& below)
 {
     const int lane = thread_index() & 63;
     const int nb = nc / kCoreBlock;
     // the centre, and a power of two near the core's spread
     const int cq = (int)(quantile * (float)nc);
+    const int block = cq / kCoreBlock;
     centre = cw.cv[cq];
+    const float under = centre - cw.cv[kCoreBlock * block];
+    const float over = cw.cv[kCoreBlock * block + kCoreBlock - 1] - centre;
     float spread = cw.cv[(27 * nc) >> 5] - cw.cv[(5 * nc) >> 5];
     // most of the core equal: the spread of the rest (summed sample by sample,
     // 100 curves of 18,000 with 75 or 97 of 100 samples equal took 2,900 us at
@@ -1604,9 +1614,11 @@ __device__ __forceinline__ bool core_build(const CoreLds& cw, int nc, float quan
     const float e0 = cw.edge[lane], e1 = cw.edge[64 + (lane & 7)];
     cw.edge[lane] = e0 - centre;
     if (lane < kCoreEdge - 64) cw.edge[64 + lane] = e1 - centre;
-    const int bc = cq / kCoreBlock;
-    // power sums from the centre's block edge outwards: upwards in the lower
-    // half of the wave, downwards (with a minus sign) in the upper half
+    gap = __builtin_fminf(under, over);
+    below = __builtin_amdgcn_readfirstlane(under <= over ? 1 : 0) != 0;
+    const int bc = block + (below ? 0 : 1);
+    // power sums from that edge outwards: upwards in the lower half of the
+    // wave, downwards (with a minus sign) in the upper half
     const bool up = lane < 32;
     float carry[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
     for (int r0 = 0; r0 < max(nb - bc, bc); r0 += 32) {
@@ -2043,7 +2055,9 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv
             core_phase1<2 * kCoreGroup>(sm, wv, cw, nv, core, fits, nc, cca, live, ca, n, m, nplus);
         else
             core_phase1<kCoreGroup>(sm, wv, cw, nv, core, fits, nc, cca, live, ca, n, m, nplus);
-        core = core && core_build(cw, nc, q.quantile, centre, unit);
+        float gap = 0.0f;
+        bool gap_below = false;
+        core = core && core_build(cw, nc, q.quantile, centre, unit, gap, gap_below);
         const int nb = nc / kCoreBlock;
         // samples to sum one by one: those before the core, what the core
         // holds beyond its last whole block, and those after the core
@@ -2125,7 +2139,9 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv
         // their inverses per unit of the power sums
         const float ka = __builtin_amdgcn_rcpf(cs * unit);
         const float kb = __builtin_amdgcn_rcpf(cl * unit);
-        const bool scaled = ka > 1e-4f && ka < 1e4f;
+        // (values of the centre's block that the sums of one side hold, though
+        // they may lie beyond the cut-offs, are near enough)
+        const bool scaled = ka > 1e-4f && ka < 1e4f && gap * unit * (gap_below ? ka : kb) <= 1.5f;
         const float vmax = core ? cw.cv[kCoreBlock * nb - 1] : 0.0f;
         // samples that are not there, and any as far out, weigh nothing
         const float lowest = -1e9f * __builtin_fmaxf(cs, cl);
