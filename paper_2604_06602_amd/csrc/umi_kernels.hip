@@ -119,10 +119,9 @@ struct MainSmem {
     int check;                            // some of them may be shorter than W/3
     int seg_n[2];                         // samples of the span's first and last segment (>= W/3: at least)
     int any_live;                         // some segment is live
-    int walk;                             // bit 0, 1: seg_n[0], seg_n[1] is still short and its
-                                          // segment goes on before, behind
-    uint32_t walk_e[2];                   // curve sample walk_beyond() resumes at,
-    double walk_t[2];                     // and the time of the last valid one before it
+    int walk;                             // bit 0, 1: short of W/3, and the segment goes on
+                                          // beyond kNearSamples before, behind the span
+    double walk_t[2];                     // time of its valid sample nearest to there
     uint32_t kmin, kmax;                  // smallest and largest staged key
     uint32_t wsum[kMainThreads / 64];     // per wave: bucket counts of its threads
 };
@@ -252,53 +251,19 @@ __device__ __forceinline__ void word_prefix(const uint64_t* bits, uint32_t* pre,
 // per sample took 0.47 ms of 3.0 on 2,000 curves of 40,000-70,000 samples at
 // W = 25, and 12 of 50 us on one of 20,000 at W = 361).
 
-// Valid samples of the segment that reaches the span's border, beyond it:
-// from curve sample e in direction dir (the nearest valid sample inside the
-// span is at time tn), until `need` are found or the segment ends (`open` is
-// cleared), in kNearSteps steps at most.  Run by one whole wave.  Indexes are
-// unsigned: one before the curve's start lies beyond its end.
-constexpr int kNearSteps = 4;
-
-__device__ __forceinline__ int segment_beyond(const float* __restrict__ flux,
-                                           const double* __restrict__ time, int len, uint32_t& e,
-                                           int dir, double& tn, int need, bool& open)
+// The double in lane l, in scalar registers.
+__device__ __forceinline__ double lane_double(double v, int l)
 {
-    const int lane = thread_index() & 63;
-    constexpr int K = 4;  // samples per lane and step, loaded together
-    int got = 0;
-    for (int step = 0; step < kNearSteps && got < need && e < (uint32_t)len; ++step) {
-        float x[K];
-        double t[K];
-#pragma unroll
-        for (int u = 0; u < K; ++u) {
-            const uint32_t i = e + (uint32_t)(dir * (64 * u + lane));
-            const bool in = i < (uint32_t)len;
-            x[u] = in ? flux[i] : __builtin_nanf("");
-            t[u] = in && time ? time[i] : 0.0;
-        }
-        for (int u = 0; u < K && got < need; ++u) {
-            const bool ok = isfinite(x[u]) && isfinite(t[u]);
-            const uint64_t m = __ballot(ok);
-            const uint64_t nearer = m & ((1ull << lane) - 1ull);
-            // the nearest valid sample towards the span
-            const double ts = __shfl(t[u], nearer ? 63 - (int)__builtin_clzll(nearer) : lane, 64);
-            const double t_in = nearer ? ts : tn;
-            const bool cut = ok && time && (dir > 0 ? t[u] - t_in : t_in - t[u]) > kGapDays;
-            const uint64_t c = __ballot(cut);
-            if (c != 0) {
-                open = false;
-                return got + (int)__popcll(m & ((c & -c) - 1ull));
-            }
-            got += (int)__popcll(m);
-            if (m != 0) tn = __shfl(t[u], 63 - (int)__builtin_clzll(m), 64);
-        }
-        e += (uint32_t)(dir * 64 * K);
-    }
-    open = open && e < (uint32_t)len;
-    return got;
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)u, l);
+    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(u >> 32), l);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
-// What a wave found of its part of a step of walk_beyond().
+constexpr int kNearSamples = 256;  // beyond the span, looked at by one wave
+
+// What a wave found in a run of samples beyond the span, in the order away
+// from it.
 struct WalkPart {
     double first, last;  // times of its valid samples nearest to the span and furthest
     int count, head;     // valid samples, and those before the first break among them
@@ -306,25 +271,100 @@ struct WalkPart {
     int reserved;
 };
 
-// segment_beyond() further out, by the whole workgroup: a step takes 16,384
-// samples, of which only the valid ones' times are read.  Where valid samples
-// are few and far apart a tile looks through up to the whole curve; done by one
-// wave, 256 samples a step, that set the time (one curve without times, us a
-// call: 118 valid samples among 2,000,000 at W = 361 10,200, now 730; one in
-// 1,000 of 200,000 at W = 1441 1,730, now 133; one in 1,000 of 100,000 at W =
-// 2047, in tiles of two positions, 20,800, now 2,600; with a pass over the
-// samples ahead, 108, 45 and 598).  What is left is latency, 1.4 us per 4,096
-// samples; loads of 16 or 32 samples a lane, or of the next while these are
-// counted, gain a tenth there, and cost the ordinary tiles registers (a curve of
-// 2,000,000 at W = 25 64, 69 and 74 us with 8, 16 and 32).  At worst a tile reads
-// the samples up to W/3 valid ones away on either side.
+// Adds K rows of 64 samples to a part: row u holds the samples of times t[u],
+// valid where the lane's ok has bit u, lane after lane; dir > 0: times go up.  The
+// predecessors' times come from the lanes for all rows first, so that their
+// latencies overlap.
+template <int K>
+__device__ __forceinline__ void walk_rows(uint32_t ok, const double (&t)[K], int dir, WalkPart& p)
+{
+    const int lane = thread_index() & 63;
+    const uint64_t lower = (1ull << lane) - 1ull;
+    uint64_t m[K];
+    double ts[K];
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+        m[u] = __ballot(((ok >> u) & 1u) != 0 && isfinite(t[u]));
+        const uint64_t nearer = m[u] & lower;
+        ts[u] = __shfl(t[u], nearer ? 63 - (int)__builtin_clzll(nearer) : lane, 64);
+    }
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+        if (p.cut || m[u] == 0) continue;
+        const bool none = (m[u] & lower) == 0;  // no valid sample before it in the row
+        const double t_in = none ? p.last : ts[u];
+        const uint64_t c = __ballot(((m[u] >> lane) & 1ull) != 0 && !(none && p.count == 0) &&
+                                    (dir > 0 ? t[u] - t_in : t_in - t[u]) > kGapDays);
+        if (c != 0) {
+            p.head = p.count + (int)__popcll(m[u] & ((c & -c) - 1ull));
+            p.cut = 1;
+        }
+        if (p.count == 0) p.first = lane_double(t[u], (int)__builtin_ctzll(m[u]));
+        p.last = lane_double(t[u], 63 - (int)__builtin_clzll(m[u]));
+        p.count += (int)__popcll(m[u]);
+    }
+}
+
+// Joins a part to the n samples counted so far, the furthest of them at time
+// tn; open: the segment goes on.
+__device__ __forceinline__ void walk_join(const WalkPart& p, bool timed, int dir, int& n, double& tn,
+                                          bool& open)
+{
+    if (p.count == 0) return;
+    if (timed && (dir > 0 ? p.first - tn : tn - p.first) > kGapDays) {
+        open = false;
+        return;
+    }
+    n += p.cut ? p.head : p.count;
+    open = p.cut == 0;
+    tn = p.last;
+}
+
+// The 256 samples from curve sample e on in direction dir, added to the n that
+// a segment has up to there.  Run by one wave.
+__device__ __forceinline__ void walk_near(const float* __restrict__ flux,
+                                          const double* __restrict__ time, int len, uint32_t e,
+                                          int dir, int& n, double& tn, bool& open)
+{
+    constexpr int K = kNearSamples / 64;
+    const int lane = thread_index() & 63;
+    double t[K];
+    float x[K];
+    uint32_t ok = 0;
+#pragma unroll
+    for (int u = 0; u < K; ++u) {
+        const uint32_t i = e + (uint32_t)(dir * (64 * u + lane));
+        x[u] = flux[i < (uint32_t)len ? i : 0u];  // (outside the curve: sample 0, not counted)
+        t[u] = time != nullptr ? time[i < (uint32_t)len ? i : 0u] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < K; ++u)
+        ok |= e + (uint32_t)(dir * (64 * u + lane)) < (uint32_t)len && isfinite(x[u]) ? 1u << u : 0u;
+    WalkPart p = {0.0, 0.0, 0, 0, 0, 0};
+    walk_rows<K>(ok, t, dir, p);
+    walk_join(p, time != nullptr, dir, n, tn, open);
+}
+
+// Valid samples further beyond the span of the segments that reach its borders,
+// added to sm.seg_n until W/3 are found or the segment ends.  By the whole workgroup,
+// from the border outwards: 4,096 samples in the first step, 16,384 in the others,
+// of which only times of rows with valid samples are read.  Indexes are unsigned:
+// one before the curve's start lies beyond its end.
+// By one wave, 256 samples a step, this set the time where valid samples are few
+// and far apart (one curve without times, us a call: 118 valid samples among
+// 2,000,000 at W = 361 10,200, now 605; one in 1,000 of 200,000 at W = 1441 1,735,
+// now 108; one in 1,000 of 100,000 at W = 2047, in tiles of two positions, 20,900,
+// now 2,090; with times, one in 16 of 18,000 at W = 1081 42, now 28; with a pass
+// over the samples ahead 108, 45, 598 and 31).  What is left is latency: loads
+// of 16 or 32 samples a lane, of the next while these are counted, or of eight
+// consecutive ones a lane gained nothing or cost the ordinary tiles registers.
+// At worst a tile reads the samples up to W/3 valid ones away.
 __device__ __forceinline__ void walk_beyond(MainSmem& sm, WalkPart* parts,
                                          const float* __restrict__ flux,
-                                         const double* __restrict__ time, int len, int m_min)
+                                         const double* __restrict__ time, int len, int s0, int N,
+                                         int m_min)
 {
-    constexpr int K = 8;      // samples per lane, loaded together
-    constexpr int kParts = 4; // of them per step
-    constexpr int kStep = kMainThreads * K * kParts;
+    constexpr int K = 8;  // rows of 64 samples that a wave loads together
     const int tid = thread_index();
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -332,66 +372,48 @@ __device__ __forceinline__ void walk_beyond(MainSmem& sm, WalkPart* parts,
     const int walk = sm.walk;
     int n = sm.seg_n[0];
 #pragma unroll 1
-    for (int side = 0; side < 2; ++side) {
+    for (int side = 0; side < 2; ++side) {  // before the span, behind it
         if (side == 1 && multi) n = sm.seg_n[1];
-        if (((walk >> side) & 1) == 0) continue;
         const uint32_t dir = side ? 1u : ~0u;
-        uint32_t e = sm.walk_e[side];
+        uint32_t e = side ? (uint32_t)(s0 + N + kNearSamples) : (uint32_t)(s0 - 1 - kNearSamples);
         double tn = sm.walk_t[side];
-        bool open = true;
+        bool open = ((walk >> side) & 1) != 0;
+        int turns = 1;
         while (open && n < m_min && e < (uint32_t)len) {
             WalkPart p = {0.0, 0.0, 0, 0, 0, 0};
-            uint32_t i0 = e + dir * (uint32_t)(wave * 64 * K * kParts + lane);
+            uint32_t i0 = e + dir * (uint32_t)(wave * 64 * K * turns + lane);
 #pragma unroll 1
-            for (int part = 0; part < kParts && !p.cut; ++part, i0 += dir * (64u * K)) {
+            for (int turn = 0; turn < turns && !p.cut && p.count < m_min - n;
+                 ++turn, i0 += dir * (64u * K)) {
                 float x[K];
 #pragma unroll
                 for (int u = 0; u < K; ++u)  // (outside the curve: sample 0, not counted)
                     x[u] = flux[i0 + dir * (64u * u) < (uint32_t)len ? i0 + dir * (64u * u) : 0u];
+                uint32_t ok = 0;
 #pragma unroll
-                for (int u = 0; u < K; ++u) {
-                    const uint32_t i = i0 + dir * (64u * u);
-                    bool ok = i < (uint32_t)len && isfinite(x[u]);
-                    if (p.cut || __ballot(ok) == 0) continue;
-                    double t = 0.0;
-                    if (time != nullptr) {
-                        if (ok) t = time[i];
-                        ok = ok && isfinite(t);
-                    }
-                    const uint64_t m = __ballot(ok);
-                    if (m == 0) continue;
-                    if (time != nullptr) {
-                        const uint64_t nearer = m & ((1ull << lane) - 1ull);
-                        const double ts =
-                            __shfl(t, nearer ? 63 - (int)__builtin_clzll(nearer) : lane, 64);
-                        const double t_in = nearer ? ts : p.last;
-                        const uint64_t c = __ballot(ok && (nearer != 0 || p.count > 0) &&
-                                                    (side ? t - t_in : t_in - t) > kGapDays);
-                        if (c != 0) {
-                            p.head = p.count + (int)__popcll(m & ((c & -c) - 1ull));
-                            p.cut = 1;
-                        }
-                        if (p.count == 0) p.first = __shfl(t, (int)__builtin_ctzll(m), 64);
-                        p.last = __shfl(t, 63 - (int)__builtin_clzll(m), 64);
-                    }
-                    p.count += (int)__popcll(m);
+                for (int u = 0; u < K; ++u)
+                    ok |= i0 + dir * (64u * u) < (uint32_t)len && isfinite(x[u]) ? 1u << u : 0u;
+                if (!__any(ok != 0)) continue;
+                if (time == nullptr) {
+                    p.count += __builtin_amdgcn_readlane((int)wave_scan((uint32_t)__popc(ok)), 63);
+                    continue;
+                }
+#pragma unroll
+                for (int u0 = 0; u0 < K; u0 += K / 2) {
+                    double t[K / 2];
+#pragma unroll
+                    for (int u = 0; u < K / 2; ++u)
+                        t[u] = time[((ok >> (u0 + u)) & 1u) != 0 ? i0 + dir * (64u * (u0 + u)) : 0u];
+                    walk_rows<K / 2>(ok >> u0, t, side ? 1 : -1, p);
                 }
             }
             if (lane == 0) parts[wave] = p;
             __syncthreads();
-            for (int w = 0; w < kMainThreads / 64 && open && n < m_min; ++w) {
-                const WalkPart q = parts[w];
-                if (q.count == 0) continue;
-                if (time != nullptr && (side ? q.first - tn : tn - q.first) > kGapDays) {
-                    open = false;
-                } else {
-                    n += q.cut ? q.head : q.count;
-                    open = q.cut == 0;
-                    tn = q.last;
-                }
-            }
+            for (int w = 0; w < kMainThreads / 64 && open && n < m_min; ++w)
+                walk_join(parts[w], time != nullptr, side ? 1 : -1, n, tn, open);
             __syncthreads();
-            e += dir * (uint32_t)kStep;
+            e += dir * (uint32_t)(kMainThreads * K * turns);
+            turns = 4;
         }
         if (tid == 0) sm.seg_n[multi ? side : 0] = n;
     }
@@ -400,7 +422,7 @@ __device__ __forceinline__ void walk_beyond(MainSmem& sm, WalkPart* parts,
 
 // From the span's validity and in-word start bits: the prefix counts, the
 // starts at word borders, and the sizes of the span's first and last segment
-// (the same one without starts), with their samples beyond the span.  Run by
+// (the same one without starts), with the samples next to the span.  Run by
 // wave 0.
 __device__ __forceinline__ void resolve_segments(MainSmem& sm, const float* __restrict__ flux,
                                                  const double* __restrict__ time, int len, int s0,
@@ -437,7 +459,6 @@ __device__ __forceinline__ void resolve_segments(MainSmem& sm, const float* __re
     }
     if (!check) return;
     wave_lds_sync();
-    const int wf = (int)__builtin_ctzll(some), wl = 63 - (int)__builtin_clzll(some);
     int n0 = total, n1 = total;
     if (multi) {  // samples before the first start, and from the last one on
         const int w0 = (int)__builtin_ctzll(starts), w1 = 63 - (int)__builtin_clzll(starts);
@@ -446,23 +467,27 @@ __device__ __forceinline__ void resolve_segments(MainSmem& sm, const float* __re
         n1 = total - (int)sm.vpre[w1] -
              (int)__popcll(sm.vbits[w1] & ((1ull << (63 - (int)__builtin_clzll(sl))) - 1ull));
     }
-    uint32_t e0 = (uint32_t)(s0 - 1), e1 = (uint32_t)(s0 + N);
-    double t0 = time ? sm.tfirst[wf] : 0.0, t1 = time ? sm.tlast[wl] : 0.0;
-    bool open0 = n0 < m_min;
-    if (open0) n0 += segment_beyond(flux, time, len, e0, -1, t0, m_min - n0, open0);
+    // what lies next to the span decides most of them
+    double t0 = 0.0, t1 = 0.0;
+    bool open0 = n0 < m_min && s0 > 0, open1 = false;
+    if (open0) {
+        t0 = time != nullptr ? sm.tfirst[__builtin_ctzll(some)] : 0.0;
+        walk_near(flux, time, len, (uint32_t)(s0 - 1), -1, n0, t0, open0);
+    }
     if (!multi) n1 = n0;
-    bool open1 = n1 < m_min;
-    if (open1) n1 += segment_beyond(flux, time, len, e1, 1, t1, m_min - n1, open1);
+    if (n1 < m_min && s0 + N < len) {
+        open1 = true;
+        t1 = time != nullptr ? sm.tlast[63 - (int)__builtin_clzll(some)] : 0.0;
+        walk_near(flux, time, len, (uint32_t)(s0 + N), 1, n1, t1, open1);
+    }
     if (!multi) n0 = n1;
-    const int walk = (open0 && n0 < m_min ? 1 : 0) | (open1 && n1 < m_min ? 2 : 0);
     if (lane == 0) {
         sm.seg_n[0] = n0;
         sm.seg_n[1] = n1;
-        sm.walk = walk;
-        sm.walk_e[0] = e0;
-        sm.walk_e[1] = e1;
         sm.walk_t[0] = t0;
         sm.walk_t[1] = t1;
+        sm.walk = (open0 && n0 < m_min && s0 > kNearSamples ? 1 : 0) |
+                  (open1 && n1 < m_min && len - (s0 + N) > kNearSamples ? 2 : 0);
     }
 }
 
@@ -2356,7 +2381,7 @@ __global__ __launch_bounds__(kMainThreads, (kFeat & kFeatCore) ? kCoreWaves : 8)
         const bool check = __builtin_amdgcn_readfirstlane(sm.check) != 0;
         if (check) {
             if (__builtin_amdgcn_readfirstlane(sm.walk) != 0)
-                walk_beyond(sm, reinterpret_cast<WalkPart*>(&wv), f, tm, cd.len, m_min);
+                walk_beyond(sm, reinterpret_cast<WalkPart*>(&wv), f, tm, cd.len, s0, N, m_min);
             live_segments(sm, nwv, m_min);
             __syncthreads();
         }

@@ -201,3 +201,13 @@ def test_segments_of_half_a_window_cost_little_more_than_one(torch, umi, W):
     cut = np.floor(np.arange(n) / (W // 3 + 20)) * 0.7
     many = call_us(torch, umi, flux, np.arange(n) * DT + cut, 100, W)
     assert many < 1.8 * one, (many, one)
+
+
+def test_sparse_curves_with_times_cost_little_more_than_full_ones(torch, umi):
+    """One sample in 16 valid, no gap over half a day: no break between them."""
+    n, W = 18000, 1801
+    rng = np.random.default_rng(16)
+    flux, t = rng.normal(1, 1e-3, n), np.arange(n) * DT
+    full = call_us(torch, umi, flux, t, 100, W)
+    sparse = call_us(torch, umi, np.where(rng.random(n) < 1 / 16, flux, np.nan), t, 100, W)
+    assert sparse < 1.3 * full, (sparse, full)
