@@ -269,12 +269,12 @@ constexpr int kNarrowRounds[] = {3, 8};
 constexpr int kCoreTileStep = 128;
 constexpr int kCoreTileCost[kSmallBatchCoreSlots] = {25, 35, 48};
 
-// Whether a curve's tiles take sorted cores: wide windows with the upper-RMS
-// scale, tiles that hold a group of windows (all but those of the very
-// widest), and asymmetries whose two sides' cut-offs are not far apart.
+// Whether a curve's windows take sorted cores: wide ones with the upper-RMS
+// scale, whose tiles can hold kCoreMinTile positions (all but the very widest),
+// and asymmetries whose two sides' cut-offs are not far apart.
 bool core_window(int W, float alpha, int32_t scale)
 {
-    return W >= kCoreMinW && max_tile(W) >= kCoreGroup && scale == UMI_SCALE_UPPER_RMS &&
+    return W >= kCoreMinW && max_tile(W) >= kCoreMinTile && scale == UMI_SCALE_UPPER_RMS &&
            alpha >= 0.25f && alpha <= 16.0f;
 }
 
@@ -383,7 +383,7 @@ umi_status pack_into(const int64_t* offsets, const int64_t* lengths, int64_t n, 
         d.c = o.c ? o.c[b] : c;
         d.window_days = o.window_days ? o.window_days[b] : 0.0;
         d.chunk_base = (int32_t)out->nchunks;
-        d.core = is_core(b) ? 1 : 0;
+        d.core = is_core(b) && tile_of[b] >= kCoreMinTile ? 1 : 0;
         out->curve_tiles[i] = nt;
         out->ntiles += nt;
         out->nchunks += nch;

@@ -35,6 +35,14 @@ constexpr int kFeatBits = 8;                 // the batch's largest core stands 
 // and 19 us; W = 161 18 and 19; W = 201 19.5 and 19; W = 361 24.5 and 19.5).
 constexpr int kCoreMinW = 117;
 constexpr int kCoreBlock = 8;
+// Tiles smaller than this (an explicit tile, or W > 1985) leave most of a
+// workgroup's waves without a group of windows; the lanes that share a window
+// directly use them all (us a call, by cores and directly: 838 curves of 1,740
+// with ties at W = 2017, tiles of 32, one iteration 6,990 and 2,715; 40 of 18,000
+// at W = 1987, tiles of 62, 1,129 and 1,096; 7 of 2,671 at W = 361 with tiles of one
+// position 653 and 293; with tiles of 64, 40 of 18,000 at W = 117 take 229 and
+// 232, at W = 361 247 and 500).
+constexpr int kCoreMinTile = 64;
 // Waves per SIMD the core instances are built for: LDS (47 KB at W = 361)
 // allows three workgroups per CU, and 80 registers spill little; at 4 waves
 // (128 registers) two workgroups fit and W = 361 took 3.3 ms against 2.5.

@@ -59,7 +59,7 @@ void check_tile(const BatchHeader& hdr, const CurveDesc& cd, int t0, int feat, f
     const int h = (cd.W - 1) / 2, t1 = (int)std::min<int64_t>((int64_t)t0 + cd.tile, cd.len);
     CHECK(t0 >= 0 && t0 < cd.len && cd.tile >= 1 && cd.tile <= kMaxTile);
     CHECK(std::min<int64_t>((int64_t)t1 + h, cd.len) - std::max(t0 - h, 0) <= kStageMax);
-    CHECK(cd.core == (core_window(cd.W, cd.alpha, hdr.scale) ? 1 : 0));
+    CHECK(cd.core == (core_window(cd.W, cd.alpha, hdr.scale) && cd.tile >= kCoreMinTile ? 1 : 0));
     if (cd.core) {
         CHECK((feat & kFeatCore) && cap >= core_cap(cd.W));
     } else if (cd.tile <= kSplitMaxTile) {
