@@ -314,6 +314,13 @@ umi_status pack_into(const int64_t* offsets, const int64_t* lengths, int64_t n, 
         return t;
     };
     if (opt.tile == 0 && !any_sized) {
+        // workgroups per CU that run together, which the call may limit (one per
+        // CU: 40 curves of 7,662 at W = 241 without cores 165 us, 250 with tiles for
+        // four; 200 of 3,000 at W = 61 135 and 154; narrow windows gain from the
+        // smaller tiles all the same, 94 and 87)
+        const int limit = opt.groups_per_cu > 0 ? opt.groups_per_cu : kSmallBatchSlots;
+        const int slots = std::min(limit, kSmallBatchSlots);
+        const int core_slots = std::min(limit, kSmallBatchCoreSlots);
         bool cores = false;
         for (int64_t i = 0; i < nord; ++i) cores = cores || is_core(order[i]);
         int widest = 0, chosen = 0;
@@ -323,7 +330,7 @@ umi_status pack_into(const int64_t* offsets, const int64_t* lengths, int64_t n, 
             for (int cap = widest; cap >= kSplitMaxTile;
                  cap = (cap - 1) / kCoreTileStep * kCoreTileStep) {
                 const int64_t t = count_tiles(cap);
-                if (t > max_tiles || t > (int64_t)n_cu * kSmallBatchCoreSlots) break;
+                if (t > max_tiles || t > (int64_t)n_cu * core_slots) break;
                 if (t == 0) break;
                 const int64_t cost = (int64_t)cap * kCoreTileCost[(t - 1) / n_cu];
                 if (cost < least) {
@@ -345,7 +352,7 @@ umi_status pack_into(const int64_t* offsets, const int64_t* lengths, int64_t n, 
             if (narrow && chosen > 0 && cap >= chosen) continue;
             const int64_t t = count_tiles(cap);
             if (t > max_tiles ||
-                t > (cap < kSplitMaxTile ? n_cu : (int64_t)n_cu * kSmallBatchSlots))
+                t > (cap < kSplitMaxTile ? n_cu : (int64_t)n_cu * (narrow ? kSmallBatchSlots : slots)))
                 break;
             chosen = cap;
         }

@@ -16,6 +16,7 @@ namespace {
 
 int g_failures = 0;
 long g_setup = 0, g_value = 0, g_staged = 0, g_per_curve = 0;
+int g_tiles = 0;        // tiles of the last estimate launch
 bool g_outputs = true;  // the stand-in writes the outputs (off for very long curves)
 
 #define CHECK(cond)                                                               \
@@ -92,6 +93,7 @@ hipError_t launch_main(const float*, const int32_t*, const BatchHeader* hdr,
     }
     return fake_hip::record_or_run([=] {
         ++(tile_count < 0 ? g_staged : g_per_curve);
+        g_tiles = hdr->n_tiles;
         CHECK(grid >= 1 && (int64_t)grid * kMainThreads <= (int64_t)UINT32_MAX);
         if (tile_count < 0)
             CHECK(*counter == 0u);
@@ -191,11 +193,32 @@ void check_many_tiles()
     }
 }
 
+// A small batch is cut into no more tiles than the workgroups that the call
+// lets run at once, where larger tiles leave it as few.
+void check_limited_groups()
+{
+    g_outputs = false;
+    const int64_t n = 40, len = 7662;
+    std::vector<int64_t> lens((size_t)n, len);
+    std::vector<float> flux((size_t)(n * len), 1.0f), trend((size_t)(n * len));
+    for (int W : {61, 115, 241, 361}) {
+        const std::vector<int32_t> Ws((size_t)n, W);
+        for (float alpha : {2.0f, 0.1f})
+            for (int groups = 1; groups <= 4; ++groups) {
+                const umi_launch lo = {UMI_MODE_PERSISTENT, 0, groups, 0, nullptr, nullptr};
+                CHECK(umi_detrend_batch(flux.data(), nullptr, lens.data(), n, Ws.data(), alpha, 5.0f,
+                                        5, trend.data(), nullptr, &lo, nullptr) == UMI_OK);
+                CHECK(g_tiles <= 256 * groups);
+            }
+    }
+}
+
 }  // namespace
 
 int main()
 {
     check_batches();
+    check_limited_groups();
     check_many_tiles();
     umi_release();
     if (g_failures == 0) std::printf("launch checks ok\n");
