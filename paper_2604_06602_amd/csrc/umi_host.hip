@@ -324,10 +324,20 @@ umi_status pack_into(const int64_t* offsets, const int64_t* lengths, int64_t n, 
         bool cores = false;
         for (int64_t i = 0; i < nord; ++i) cores = cores || is_core(order[i]);
         int widest = 0, chosen = 0;
-        for (int64_t i = 0; i < nord; ++i) widest = std::max(widest, tile_of[order[i]]);
+        int64_t longest = 0;
+        for (int64_t i = 0; i < nord; ++i) {
+            widest = std::max(widest, tile_of[order[i]]);
+            longest = std::max(longest, lengths[order[i]]);
+        }
         if (cores) {
             int64_t least = INT64_MAX;
-            for (int cap = widest; cap >= kSplitMaxTile;
+            // (larger tiles than the longest curve make no fewer, and cost more)
+            int first = widest;
+            if (longest < widest)
+                first = std::min<int>(
+                    widest, std::max<int>(kSplitMaxTile, (int)((longest + kCoreTileStep - 1) /
+                                                               kCoreTileStep * kCoreTileStep)));
+            for (int cap = first; cap >= kSplitMaxTile;
                  cap = (cap - 1) / kCoreTileStep * kCoreTileStep) {
                 const int64_t t = count_tiles(cap);
                 if (t > max_tiles || t > (int64_t)n_cu * core_slots) break;
