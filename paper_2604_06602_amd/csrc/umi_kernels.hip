@@ -1785,9 +1785,10 @@ __device__ __forceinline__ void rank_phase1(const MainSmem& sm, const Wavelet& w
 }
 
 // Phase 1 (Section 2.1) of a group's windows.  A window is the core plus at
-// most 31 edge samples (63 with time windows, which differ in length), so its
-// median lies at one of the kRanks core samples around the core's middle, or
-// between two of them.  For each of
+// most 31 edge samples (63 with time windows, which differ in length, and fewer
+// than the core has), so its median lies at one of the kRanks core samples around
+// the core's middle (of all, where a core behind which infinity stands has fewer),
+// or between two of them.  For each of
 // those core ranks the wave forms the set of edge samples below that core
 // sample (a bit mask: the edge samples' ranks by binary search, set in LDS,
 // then a prefix "or" over the lanes); a window counts its own ones with a mask
@@ -1810,7 +1811,7 @@ __device__ __forceinline__ void core_phase1(const MainSmem& sm, const Wavelet& w
     const int k = (int)((n - 1) >> 1);
     bool zero = false;
     if (core) {
-        const int r0 = (nc >> 1) - kRanks / 2;
+        const int r0 = max((nc >> 1) - kRanks / 2, 0);
         const float* const mid = cw.cv + r0;
         const int rem = nc & (kCoreBlock - 1);
         // masks of core rank r0 + r: words 2r (samples before the core) and
@@ -2059,14 +2060,17 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv
         const int nc = min(ccb - cca, core_cap(cd.W));
         float centre = 0.0f, unit = 1.0f;
         bool core = nc >= kCoreMin;
+        const bool timed = (kFeat & kFeatExtra) && cd.window_days > 0.0;
         if (core) core_collect(sm, wv, cw, nv, cca, nc);
+        if (core && timed && nc < 2 * kCoreMin) {  // core_phase1's ranks beyond the core
+            if (nc + lane < 2 * kCoreMin) cw.cv[nc + lane] = __builtin_inff();
+            wave_lds_sync();
+        }
         // nl edge samples before the core, nr after it; windows that differ in
         // length (time windows) may have more than there are slots
         const int nl = live ? cca - (int)ca : 0, nr = live ? (int)n - nc - nl : 0;
-        const bool timed = (kFeat & kFeatExtra) && cd.window_days > 0.0;
-        const bool wide = timed && nc >= 2 * kCoreMin;
         const bool fits = !timed || ((uint32_t)nl <= 32u && (uint32_t)nr <= 32u &&
-                                     nl + nr < (wide ? 2 * kCoreGroup : kCoreGroup));
+                                     nl + nr < min(2 * kCoreGroup, nc));
         // (a window that does not hold the core: times that decrease)
         const bool holds = core && nl >= 0 && nr >= 0;
         const bool ranked = live && !(core && fits);
@@ -2076,7 +2080,7 @@ __device__ __forceinline__ void core_group(const MainSmem& sm, const Wavelet& wv
                             holds ? nr : 0, m, nplus);
             wave_lds_sync();
         }
-        if ((kFeat & kFeatExtra) && wide)
+        if ((kFeat & kFeatExtra) && timed)
             core_phase1<2 * kCoreGroup>(sm, wv, cw, nv, core, fits, nc, cca, live, ca, n, m, nplus);
         else
             core_phase1<kCoreGroup>(sm, wv, cw, nv, core, fits, nc, cca, live, ca, n, m, nplus);

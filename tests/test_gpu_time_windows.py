@@ -113,3 +113,32 @@ def test_uneven_windows_cost_little_more_than_even_ones(torch, umi, W, kind):
     even = call_us(torch, umi, flux, np.arange(n) * DT, 40, W, window_days=L)
     us = call_us(torch, umi, flux, uneven, 40, W, window_days=L)
     assert us < 4 * even, (us, even)
+
+
+@pytest.mark.parametrize("W,n_curves,n", [(121, 40, 18000), (361, 40, 18000), (121, 1, 1229)])
+def test_windows_of_72_and_73_samples_cost_what_82_do(torch, umi, W, n_curves, n):
+    """At 0.1 days the windows' ends fall on samples, whose times are rounded:
+    neighbouring windows differ by a sample, and the group's core by two."""
+    rng = np.random.default_rng(7)
+    flux, t = 1 + 1e-3 * rng.standard_normal(n), np.arange(n) * DT
+    other = call_us(torch, umi, flux, t, n_curves, W, window_days=0.115)
+    us = call_us(torch, umi, flux, t, n_curves, W, window_days=0.1)
+    assert us < 1.6 * other, (us, other)
+
+
+@pytest.mark.parametrize("days", [0.055, 0.0612, 0.08, 0.1, 0.12])
+def test_short_cores_of_time_windows(torch, umi, oracle_lib, days):
+    """Cores of 9 to 60 samples, with up to as many samples beside them."""
+    rng = np.random.default_rng(11)
+    curves = []
+    for W in (121, 361):
+        for f, t in _shapes(W, rng):
+            n = len(f)
+            for u in (t, t + 0.3 * DT * rng.random(n), np.cumsum(rng.uniform(0.5, 1.5, n)) * DT):
+                curves.append((np.asarray(f, np.float32), np.sort(u), W))
+    b = synth.lightcurves.pack(curves)
+    mag = window_magnitude(b.flux, b.time, b.lengths, b.W, oracle_lib)
+    for a, c in [(2.0, 5.0), (1.0, 2.0)]:
+        g = run_batch(torch, umi, b.flux, b.time, b.lengths, b.W, alpha=a, c=c, window_days=days)
+        o = oracle_lib.detrend_batch(b.flux, b.time, b.lengths, b.W, alpha=a, c=c, window_days=days)
+        assert_parity(*g, *o, scale=mag, what="short cores %g days a=%g" % (days, a))
