@@ -904,9 +904,11 @@ CopyPool& copy_pool(int which = 0)
 // Estimate kernels a plan's graphs launch.  Sorted cores take LDS in
 // proportion to the widest window, and LDS is what limits the workgroups per
 // CU, so a run takes the smallest that covers it: no cores (four workgroups
-// per CU), cores of windows up to kPlanMidW (three), of any window up to max_W.
+// per CU), cores of windows up to kPlanMidW (three; LDS allows them up to W =
+// 737), of any window up to max_W (300 curves of 18,000 at W = 601 with the LDS
+// of W = 2047, one workgroup: 1,158 us a step against 588).
 constexpr int kPlanKernels = 3;
-constexpr int kPlanMidW = 383;
+constexpr int kPlanMidW = 721;
 
 struct umi_plan {
     int device = 0;
