@@ -74,14 +74,22 @@ typedef enum {
 /* Tuning knobs; zero in a field means "use the library's choice" (its
  * built-in defaults, or the tuning table loaded with umi_set_tuning).  With
  * tile = 0, a batch that the chosen tiles would cut into fewer tiles than the
- * device runs at once takes smaller ones, from 1280 down to 64 output
- * positions, as long as all of them still run at once (below 256 positions: as
- * long as every compute unit has at most one).  Tiles of
- * more than 256 positions give each window one lane and results that do not
- * depend on the tile size; tiles of at most 256 split every window over 2,
- * 4 or 8 lanes (kept in step by cross-lane sums), which orders the sums
- * differently: such results agree with the others to float32 rounding and
- * are themselves deterministic. */
+ * device runs at once (four per compute unit, three with sorted cores, and no
+ * more than groups_per_cu) takes smaller ones, down to 64 output positions, as
+ * long as all of them still run at once (below 256 positions: as long as every
+ * compute unit has at most one); a batch whose windows are all of at most 31
+ * samples also takes tiles of 512 where these make at most three rounds of four
+ * per compute unit, of 1024 up to eight.
+ *
+ * Windows of 117 to 1985 samples with the upper-RMS scale and an alpha of 1/4
+ * to 16 share sorted cores of samples with their neighbours in every tile of 64
+ * positions and more: their results do not depend on the tile.  Other windows,
+ * in tiles of more than 256 positions, take one lane each and sum their samples
+ * in index order, so results do not depend on the tile either; in tiles of at
+ * most 256 (and windows without a core in tiles of fewer than 64) each is split
+ * over 2, 4 or 8 lanes, kept in step by cross-lane sums, which orders the sums
+ * differently: such results agree with the others to float32 rounding and are
+ * themselves deterministic. */
 typedef struct {
     int32_t mode;          /* umi_mode */
     int32_t tile;          /* output positions per tile (0 = auto) */
@@ -291,10 +299,10 @@ int32_t umi_window_from_cadence(double cadence_days, double window_days);
  * is given and > 0, a batch of at most samples_max samples in total; lines
  * are sorted by W_max, then by samples_max, with the lines for any batch
  * size (no or 0 samples_max) last for their W_max.  A batch-size line fixes
- * the tile (tiles of at most 256 positions split each window over 2, 4 or 8
- * lanes); otherwise the small-batch rule of umi_launch applies.  NULL
- * restores the built-in defaults.  Returns UMI_ERR_INVALID_ARG on a
- * malformed table. */
+ * the tile (tiles of at most 256 positions split each window without a sorted
+ * core over 2, 4 or 8 lanes); otherwise the small-batch rule of umi_launch
+ * applies.  NULL restores the built-in defaults.  Returns UMI_ERR_INVALID_ARG
+ * on a malformed table. */
 umi_status umi_set_tuning(const char* table_text);
 
 /* Thread-local message for the last non-OK status on this thread. */

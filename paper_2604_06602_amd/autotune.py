@@ -5,7 +5,8 @@ For each window-size bucket the tuner times every candidate (tile, groups per
 CU) on a large synthetic batch of that W with HIP events on the launch stream
 and keeps the fastest; then, for batches of one, four and sixteen
 20,000-sample curves, it times tiles from the largest down to 64 positions
-(tiles of at most 256 positions split each window over 2, 4 or 8 lanes) and
+(tiles of at most 256 positions split each window without a sorted core over 2, 4
+or 8 lanes) and
 keeps the fastest call for each batch size.  The winners are written as a
 tuning table -- the text format of ``umi_set_tuning`` ("W_max tile
 groups_per_cu [samples_max]" per line) -- to a JSON cache keyed by GPU
@@ -30,7 +31,7 @@ STAGE_MAX = 2048          # largest staged span (tile + W - 1) of the main kerne
 THREADS = 512             # threads per main-kernel workgroup
 BUCKETS = [(31, 25), (127, 121), (383, 361), (767, 721), (2047, 1441)]  # (W_max, W tried)
 GROUPS = [1, 2, 3, 4]
-SPLIT_TILES = [256, 128, 64]   # tiles that split a window over 2, 4 and 8 lanes
+SPLIT_TILES = [256, 128, 64]   # tiles that split a window without a core over 2, 4 and 8 lanes
 # small batches (curves of SMALL_LENGTH samples): (curves, samples_max of the
 # tuning row it decides); larger batches take the bucket's general row
 SMALL_LENGTH = 20000

@@ -254,14 +254,14 @@ constexpr int kSmallBatchCoreSlots = 3;
 // to three rounds of them, of 1024 up to eight, where the largest tile is
 // otherwise the best (W = 25, us a call with tiles of 512, 1024, 1536: 36 curves
 // of 18,000 55, 65, 70; 70 72, 78, 89; 150 109, 114, 121; 400 227, 212, 218; 1000
-// 510, 453, 455).  At W = 61, with a sort per tile, 1536 is the best from 100
+// 510, 453, 455; other W up to 31 follow).  At W = 61, with a sort per tile, 1536 is the best from 100
 // curves on (150, 152, 160).
 constexpr int kNarrowTiles[] = {512, 1024};
 constexpr int kNarrowRounds[] = {3, 8};
 
 // With cores a tile's time grows with the tiles a CU holds: per position about
-// as 25, 35 and 48 for one, two and three (W = 361: tiles of 512 take 30, 37 and
-// 48 us, of 1024 49, 64 and 82).  So of the multiples of 128 that run together
+// as 25, 35 and 48 for one, two and three (measured at W = 361 and taken for all:
+// tiles of 512 take 30, 37 and 48 us, of 1024 49, 64 and 82).  So of the multiples of 128 that run together
 // the one with the least tile times weight is taken, k the tiles per CU rounded
 // up.  Against the smallest that runs together in whole passes of the
 // workgroup, us a call: 16 curves of 20,000 51 -> 49, 24 68 -> 60, 32 83 -> 74,
@@ -904,8 +904,8 @@ CopyPool& copy_pool(int which = 0)
 // Estimate kernels a plan's graphs launch.  Sorted cores take LDS in
 // proportion to the widest window, and LDS is what limits the workgroups per
 // CU, so a run takes the smallest that covers it: no cores (four workgroups
-// per CU), cores of windows up to kPlanMidW (three; LDS allows them up to W =
-// 737), of any window up to max_W (300 curves of 18,000 at W = 601 with the LDS
+// per CU), cores of windows up to kPlanMidW (three; LDS allows them up to about
+// W = 725), of any window up to max_W (300 curves of 18,000 at W = 601 with the LDS
 // of W = 2047, one workgroup: 1,158 us a step against 588).
 constexpr int kPlanKernels = 3;
 constexpr int kPlanMidW = 721;

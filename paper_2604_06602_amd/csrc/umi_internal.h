@@ -29,10 +29,11 @@ constexpr int kFeatBits = 8;                 // the batch's largest core stands 
 // each; the core is that shared run, a whole number of blocks of kCoreBlock.
 // Narrower windows sum their samples directly: what a wave does for a group,
 // and the 33 edge and 16 block samples of a window's iteration, cost the same
-// whatever W.  The line lies between where batches gain (500 curves of 18,000:
-// W = 97 737 us directly, 740 by cores; W = 113 818 and 731) and where one curve
-// of 20,000 does, in small tiles whose windows several lanes share (W = 113 17
-// and 19 us; W = 161 18 and 19; W = 201 19.5 and 19; W = 361 24.5 and 19.5).
+// whatever W.  One line for two: batches gain from about W = 97 (500 curves of
+// 18,000: W = 97 737 us directly, 740 by cores; W = 113 818 and 731), one curve of
+// 20,000, in small tiles whose windows several lanes share, from about 190 (W = 113
+// 17 and 19 us; W = 161 18 and 19; W = 201 19.5 and 19; W = 361 24.5 and 19.5), so
+// that lone curves lose some 1 us between.
 constexpr int kCoreMinW = 117;
 constexpr int kCoreBlock = 8;
 // Tiles smaller than this (an explicit tile, or W > 1985) leave most of a
@@ -43,9 +44,11 @@ constexpr int kCoreBlock = 8;
 // position 653 and 293; with tiles of 64, 40 of 18,000 at W = 117 take 229 and
 // 232, at W = 361 247 and 500).
 constexpr int kCoreMinTile = 64;
-// Waves per SIMD the core instances are built for: LDS (47 KB at W = 361)
-// allows three workgroups per CU, and 80 registers spill little; at 4 waves
-// (128 registers) two workgroups fit and W = 361 took 3.3 ms against 2.5.
+// Waves per SIMD the core instances are built for: three workgroups per CU, with
+// 80 registers that spill little; at 4 waves (128 registers) two fit and W = 361
+// took 3.3 ms against 2.5, with groups of 64 windows.  Up to about W = 480 LDS
+// would allow four (39 KB: the wavelet build's 29 and 10), up to about 725 three,
+// up to about 1250 two.
 // (Edge samples in registers spill some of the tile's own values, outside the
 // groups' loop.)
 constexpr int kCoreWaves = 6;

@@ -1473,8 +1473,8 @@ __device__ __forceinline__ void tile_windows_split(const MainSmem& sm, const Wav
 // and 1.85 ms with groups of 64 windows (a lane each, twice the edge samples),
 // 4.6k and 1.75 ms with pairs of lanes, which also keep twice the waves busy
 // in a small batch (16 x 20,000: 98 us against 84).  The waves' cores take the
-// LDS that the tile sort is done with, so three workgroups fit a CU up to
-// W = 750 (W = 721: 1.42 ms with two, 1.11 with three for 500 x 18,000).
+// LDS that the tile sort is done with, so three workgroups fit a CU up to about
+// W = 725 (W = 721: 1.42 ms with two, 1.11 with three for 500 x 18,000).
 
 struct CoreLds {
     float* cv;      // core samples in value order
